@@ -467,27 +467,47 @@ template <typename Real> struct GateRegs {
     }
 };
 
+// A value in vector registers.  Operations with a scalar-register operand
+// issue at half the rate of those that read vector registers and literals
+// only (4.3 against 2.5 cycles per wave and SIMD, measured with four waves),
+// so the constants of the issue-bound rollout are held in vector registers.
+template <typename T> __device__ __forceinline__ T in_vgpr(T x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
+template <typename Real> __device__ __forceinline__ void in_vgpr(Model<Real> &M)
+{
+    M.inv_m = in_vgpr(M.inv_m); M.g = in_vgpr(M.g); M.arm_s = in_vgpr(M.arm_s); M.c_tau = in_vgpr(M.c_tau);
+    M.ijx = in_vgpr(M.ijx); M.ijy = in_vgpr(M.ijy); M.ijz = in_vgpr(M.ijz);
+    M.gx = in_vgpr(M.gx); M.gy = in_vgpr(M.gy); M.gz = in_vgpr(M.gz);
+}
+
 // One wave: samples 64*blk .. 64*blk+63 (sample K is the noise-free nominal).
 // DRAW: the wave draws its samples itself (the noise, perturbation and clip
-// of the sample kernel, same operations, one step ahead of the dynamics) and
-// stores them for the weighted average with streaming stores; the shifted
-// warm start is staged in LDS from the head that k_head published.
-// Otherwise the wave reads the samples that the sample kernel stored.
-template <int OBJ, typename Real, bool DRAW = false>
-__device__ __forceinline__ void rollout1_body(const KArgs &a, int blk)
+// of the sample kernel, same operations) and stores them for the weighted
+// average with streaming stores; the shifted warm start is staged in LDS from
+// the head h.  Otherwise the wave reads the samples that the sample kernel
+// stored.  PIPE: the costs are summed and the attitude step is closed as in
+// the pipelined rollout, so that the results are those of k_rollout4 bit for
+// bit (for launches with more tiles than the pipeline holds at once).
+template <int OBJ, typename Real, bool DRAW, bool PIPE, bool RATE, bool DRAG, typename Head>
+__device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const Head &h)
 {
     typedef typename Vec4<Real>::T R4;
-    constexpr bool HAS_V = OBJ == OBJ_CONTOUR;
+    constexpr bool GATE = OBJ == OBJ_GATE, CONT = OBJ == OBJ_CONTOUR, TRACK = OBJ == OBJ_TRACK;
+    constexpr bool HAS_V = CONT;
+    static_assert(!(DRAW && RATE) && !(PIPE && RATE), "the rate input reads the sample kernel's rates");
     __shared__ R4 s_us[DRAW ? kNMax : 1];
     __shared__ Real s_vs[DRAW && HAS_V ? kNMax : 1];
     const int m = blk * 64 + (int)(threadIdx.x & 63);
     const int K = a.K, N = a.N;
     const bool active = m <= K;
     const bool nominal = m == K;
-    const DevCur *cur = a.cur;
     Real Jfinal = Real(0);
     if (DRAW) {
-        const int shift = cur->shift, warm = cur->warm;
+        const int shift = h.shift, warm = h.warm;
+        const bool rows = a.regen && blk == (K >> 6);
         for (int k = (int)threadIdx.x; k < N; k += 64) {
             int src = k + shift;
             if (src > N - 1) src = N - 1;
@@ -499,7 +519,7 @@ __device__ __forceinline__ void rollout1_body(const KArgs &a, int blk)
             s_us[k] = o;
             if (HAS_V) s_vs[k] = warm ? (Real)a.wV[src] : Real(0);
             // the weighted average draws the samples again from these rows
-            if (a.regen && blk == (K >> 6)) {
+            if (rows) {
                 ((R4 *)a.nomU)[k] = o;
                 if (HAS_V) ((Real *)a.nomV)[k] = s_vs[k];
             }
@@ -508,52 +528,51 @@ __device__ __forceinline__ void rollout1_body(const KArgs &a, int blk)
     }
 
     if (active) {
-        const Model<Real> M(a);
-        const Real dt = (Real)a.dt;
-        const Real w_max = (Real)a.w_max, w_lim = (Real)a.w_lim;
-        State<Real> st;
-        load_state(st, cur->x0);
-        KSum<Real> J;
+        Model<Real> M(a);
+        in_vgpr(M);
+        const Real dt = in_vgpr((Real)a.dt);
+        const Real h2 = in_vgpr(Real(0.5) * (Real)a.dt);
+        const Real dt6 = in_vgpr((Real)a.dt / Real(6));
+        const Real h4 = in_vgpr(Real(0.5) * h2), dt12 = in_vgpr(Real(0.5) * dt6);
+        const Real w_max = in_vgpr((Real)a.w_max), w_lim = in_vgpr((Real)a.w_lim);
+        Real p[3], v[3], q[4], w[3];
+        for (int i = 0; i < 3; ++i) { p[i] = (Real)h.x0[i]; v[i] = (Real)h.x0[3 + i]; w[i] = (Real)h.x0[10 + i]; }
+        for (int i = 0; i < 4; ++i) q[i] = (Real)h.x0[6 + i];
+        KSum<Real> J;                               // one-wave order: all terms of a step in one sum
+        KSum<Real> J0, J1, J2;                      // pipelined order: body rates, attitude, position (J: the rest)
 
+        // the inputs (u, V) of step k: drawn (and stored, unless the weighted
+        // average draws them again) or read
         const R4 *urow = nominal ? (const R4 *)a.nomU : (const R4 *)a.ctrl + m;
         const size_t ustride = nominal ? 1 : (size_t)K;
         const Real *vrow = nullptr;
-        if (OBJ == OBJ_CONTOUR) vrow = nominal ? (const Real *)a.nomV : (const Real *)a.vctrl + m;
-        // the inputs (u, V) of step k: drawn (and stored, unless the weighted
-        // average draws them again) or read.  Drawing, the nominal clips the
-        // staged rows itself (the values the head kernel wrote to nomU / nomV,
-        // which then hold the unclipped rows of the regenerating average).
-        const bool keep = !a.regen;
-        const uint32_t s_solve = cur->s;
-        const Real tmin = (Real)a.t_min, tmax = (Real)a.t_max;
-        const Real sig0 = (Real)a.sigma[0], sig1 = (Real)a.sigma[1];
-        const Real sig2 = (Real)a.sigma[2], sig3 = (Real)a.sigma[3];
-        auto input = [&](const int k, R4 &uo, Real &vo) {
-            if (DRAW && nominal) {
-                const R4 us = s_us[k];
-                uo.x = clampT(us.x, tmin, tmax);
-                uo.y = clampT(us.y, tmin, tmax);
-                uo.z = clampT(us.z, tmin, tmax);
-                uo.w = clampT(us.w, tmin, tmax);
-                if (HAS_V) vo = clampT(s_vs[k], Real(0), (Real)a.v_max);
-            } else if (DRAW) {
-                const R4 us = s_us[k];
-                const Normal4<Real> z = normals4<Real>((uint32_t)m, (uint32_t)k, s_solve, 0u, a.seed_lo, a.seed_hi);
-                uo.x = clampT(us.x + sig0 * z.z0, tmin, tmax);
-                uo.y = clampT(us.y + sig1 * z.z1, tmin, tmax);
-                uo.z = clampT(us.z + sig2 * z.z2, tmin, tmax);
-                uo.w = clampT(us.w + sig3 * z.z3, tmin, tmax);
-                const size_t idx = (size_t)k * (size_t)K + (size_t)m;
-                if (keep) store_nt(&((R4 *)a.ctrl)[idx], uo);
-                if (HAS_V) {
-                    const Real zv = normal1<Real>((uint32_t)m, (uint32_t)k, s_solve, 1u, a.seed_lo, a.seed_hi);
-                    vo = clampT(s_vs[k] + (Real)a.sigma_v * zv, Real(0), (Real)a.v_max);
-                    if (keep) store_nt(&((Real *)a.vctrl)[idx], vo);
-                }
-            } else {
-                uo = urow[(size_t)k * ustride];
-                if (HAS_V) vo = vrow[(size_t)k * ustride];
+        if (HAS_V) vrow = nominal ? (const Real *)a.nomV : (const Real *)a.vctrl + m;
+        const bool keep = DRAW && !a.regen && !nominal;
+        const uint32_t s_solve = h.s, key0 = a.seed_lo, key1 = a.seed_hi;
+        const Real tmin = (Real)a.t_min, tmax = (Real)a.t_max, vmax = (Real)a.v_max;
+        // the nominal draws with zero noise, so that no step selects
+        const Real sig0 = in_vgpr(nominal ? Real(0) : (Real)a.sigma[0]), sig1 = in_vgpr(nominal ? Real(0) : (Real)a.sigma[1]);
+        const Real sig2 = in_vgpr(nominal ? Real(0) : (Real)a.sigma[2]), sig3 = in_vgpr(nominal ? Real(0) : (Real)a.sigma[3]);
+        const Real sigv = in_vgpr(nominal ? Real(0) : (Real)a.sigma_v);
+        R4 *urec = (R4 *)a.ctrl + m;                // of the step's record, advanced step by step
+        Real *vrec = HAS_V ? (Real *)a.vctrl + m : nullptr;
+        auto draw = [&](const int k, R4 &uo, Real &vo) {
+            const R4 us = s_us[k];
+            const Normal4<Real> z = normals4<Real>((uint32_t)m, (uint32_t)k, s_solve, 0u, key0, key1);
+            uo.x = clamp_finite(us.x + sig0 * z.z0, tmin, tmax);
+            uo.y = clamp_finite(us.y + sig1 * z.z1, tmin, tmax);
+            uo.z = clamp_finite(us.z + sig2 * z.z2, tmin, tmax);
+            uo.w = clamp_finite(us.w + sig3 * z.z3, tmin, tmax);
+            if (HAS_V) {
+                const Real zv = normal1<Real>((uint32_t)m, (uint32_t)k, s_solve, 1u, key0, key1);
+                vo = clamp_finite(s_vs[k] + sigv * zv, Real(0), vmax);
             }
+            if (keep) {
+                store_nt(urec, uo);
+                if (HAS_V) store_nt(vrec, vo);
+            }
+            urec += K;
+            if (HAS_V) vrec += K;
         };
 
         // gate objective state
@@ -561,54 +580,69 @@ __device__ __forceinline__ void rollout1_body(const KArgs &a, int blk)
         GateRegs<Real> gt, g0r;
         int g = 0, passes = 0;
         Real q_near = 0, r_near2 = 0, half = 0;
-        if (OBJ == OBJ_GATE) {
-            g = cur->g0;
+        if (GATE) {
+            g = h.g0;
             gt.load(gtab, g);
             g0r = gt;
-            q_near = (Real)a.q_near;
-            r_near2 = (Real)(a.r_near * a.r_near);
+            q_near = in_vgpr((Real)a.q_near);
+            r_near2 = in_vgpr((Real)(a.r_near * a.r_near));
             half = (Real)a.gate_half;
         }
         // tracking / contouring state
         Real up[4];
-        for (int i = 0; i < 4; ++i) up[i] = (Real)cur->u_prev[i];
-        Real vp = (Real)cur->v_prev;
+        for (int i = 0; i < 4; ++i) up[i] = (Real)h.u_prev[i];
+        Real vp = (Real)h.v_prev;
         Real rdt[4];
-        for (int i = 0; i < 4; ++i) rdt[i] = (Real)(a.R_dT[i] / (a.dt * a.dt));
-        const int i0 = cur->i0;
+        for (int i = 0; i < 4; ++i) rdt[i] = in_vgpr((Real)(a.R_dT[i] / (a.dt * a.dt)));
+        const int i0 = h.i0, R = a.R;
         const Real *xref = (const Real *)a.xref_r;
         const Real *path = (const Real *)a.path_r;
         // arc length theta = th_hi + th_lo (th_lo stays 0 in binary64)
         Real th_hi = 0, th_lo = 0;
-        Real ds = 0, inv_ds = 0, L = 0;
-        if (OBJ == OBJ_CONTOUR) {
-            th_hi = (Real)cur->theta0;
-            if (sizeof(Real) == 4) th_lo = (Real)(cur->theta0 - (double)th_hi);
-            L = (Real)a.path_len;
-            ds = (Real)(a.path_len / (double)a.P);
-            inv_ds = (Real)((double)a.P / a.path_len);
+        Real ds = 0, inv_ds = 0, L = 0, q_l = 0, q_c = 0, qw[3] = {}, r_dv = 0, mu = 0;
+        if (CONT) {
+            th_hi = (Real)h.theta0;
+            if (sizeof(Real) == 4) th_lo = (Real)(h.theta0 - (double)th_hi);
+            L = in_vgpr((Real)a.path_len);
+            ds = in_vgpr((Real)(a.path_len / (double)a.P));
+            inv_ds = in_vgpr((Real)((double)a.P / a.path_len));
+            q_l = in_vgpr((Real)a.q_l); q_c = in_vgpr((Real)a.q_c);
+            for (int i = 0; i < 3; ++i) qw[i] = in_vgpr((Real)a.Q_w[i]);
+            r_dv = in_vgpr(RATE ? (Real)a.r_dv : (Real)(a.r_dv / (a.dt * a.dt)));
+            mu = in_vgpr((Real)a.mu);
         }
 
         // rate model: the thrust states and the progress speed state, carried
         // in binary64 in every precision (integrators: in binary32 their
         // rounding over the horizon reaches the attitude through the small
         // inertia and the position through the attitude)
-        const bool rate = a.input_model == INPUT_RATE;
         double T[4];
-        for (int i = 0; i < 4; ++i) T[i] = rate ? a.req[kReqThrust + i] : 0.0;
-        double vs = rate ? cur->v_prev : 0.0;
-
+        for (int i = 0; i < 4; ++i) T[i] = RATE ? a.req[kReqThrust + i] : 0.0;
+        double vs = RATE ? h.v_prev : 0.0;
         // the rate input's range clips (multiplied by 1/dt: the bound can
         // differ from the quotient in the last binary64 place)
         const double inv_dt = 1.0 / a.dt;
-        R4 u;
-        Real v = Real(0);
-        input(0, u, v);
+        R4 un;
+        Real vn = Real(0);
+        if (!DRAW) {
+            un = urow[0];
+            if (HAS_V) vn = vrow[0];
+        }
         for (int k = 0; k < N; ++k) {
-            R4 un = u;
-            Real vn = v;
-            if (k + 1 < N) input(k + 1, un, vn);
-            if (rate) {
+            R4 u;
+            Real V = Real(0);
+            if (DRAW) {
+                draw(k, u, V);
+            } else {
+                // the inputs of the next step are in flight while this one computes
+                u = un;
+                V = vn;
+                if (k + 1 < N) {
+                    un = urow[(size_t)(k + 1) * ustride];
+                    if (HAS_V) vn = vrow[(size_t)(k + 1) * ustride];
+                }
+            }
+            if (RATE) {
                 // clip the drawn rates to the range that keeps each thrust of
                 // this sample's chain within [t_min, t_max] over the step (the
                 // progress acceleration: the speed within [0, v_max]); the
@@ -617,39 +651,69 @@ __device__ __forceinline__ void rollout1_body(const KArgs &a, int blk)
                 u.y = (Real)clampT((double)u.y, (a.t_min - T[1]) * inv_dt, (a.t_max - T[1]) * inv_dt);
                 u.z = (Real)clampT((double)u.z, (a.t_min - T[2]) * inv_dt, (a.t_max - T[2]) * inv_dt);
                 u.w = (Real)clampT((double)u.w, (a.t_min - T[3]) * inv_dt, (a.t_max - T[3]) * inv_dt);
-                if (HAS_V) v = (Real)clampT((double)v, (0.0 - vs) * inv_dt, (a.v_max - vs) * inv_dt);
+                if (HAS_V) V = (Real)clampT((double)V, (0.0 - vs) * inv_dt, (a.v_max - vs) * inv_dt);
                 if (nominal) {
                     ((R4 *)a.nomU)[k] = u;
-                    if (HAS_V) ((Real *)a.nomV)[k] = v;
+                    if (HAS_V) ((Real *)a.nomV)[k] = V;
                 } else {
                     ((R4 *)a.ctrl)[(size_t)k * (size_t)K + (size_t)m] = u;
-                    if (HAS_V) ((Real *)a.vctrl)[(size_t)k * (size_t)K + (size_t)m] = v;
+                    if (HAS_V) ((Real *)a.vctrl)[(size_t)k * (size_t)K + (size_t)m] = V;
                 }
             }
             Real term = Real(0);
 
             // ---- stage terms at state k
             Real ax = 0, ay = 0, az = 0;  // p_k - c_g (gate)
-            if (OBJ == OBJ_GATE) {
-                ax = st.x[0] - gt.cx;
-                ay = st.x[1] - gt.cy;
-                az = st.x[2] - gt.cz;
-                const Real bx = st.x[0] - g0r.cx;
-                const Real by = st.x[1] - g0r.cy;
-                const Real bz = st.x[2] - g0r.cz;
+            if (GATE) {
+                ax = p[0] - gt.cx;
+                ay = p[1] - gt.cy;
+                az = p[2] - gt.cz;
+                const Real bx = p[0] - g0r.cx;
+                const Real by = p[1] - g0r.cy;
+                const Real bz = p[2] - g0r.cz;
                 const Real d2 = bx * bx + by * by + bz * bz;
                 if (d2 < r_near2) term += q_near * d2;  // Eq. (7), current gate
                 if (nominal) a.front8[k] = (bx * g0r.nx + by * g0r.ny) < Real(0);
-            } else if (OBJ == OBJ_TRACK) {
+            } else if (TRACK) {
                 int r = i0 + k;
-                if (r > a.R - 1) r = a.R - 1;
+                if (r > R - 1) r = R - 1;
                 const Real *xr = xref + 16 * r;
+                if (PIPE) {
 #pragma unroll
-                for (int i = 0; i < 13; ++i) {
-                    const Real e = st.x[i] - xr[i];
-                    term += (Real)a.Q[i] * e * e;
+                    for (int i = 0; i < 3; ++i) {
+                        const Real e = w[i] - xr[10 + i];
+                        term += (Real)a.Q[10 + i] * e * e;
+                    }
+                    J0.add(term);
+                    term = Real(0);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const Real e = q[i] - xr[6 + i];
+                        term += (Real)a.Q[6 + i] * e * e;
+                    }
+                    J1.add(term);
+                    term = Real(0);
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) {
+                        const Real e = p[i] - xr[i];
+                        term += (Real)a.Q[i] * e * e;
+                    }
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) {
+                        const Real e = v[i] - xr[3 + i];
+                        term += (Real)a.Q[3 + i] * e * e;
+                    }
+                    J2.add(term);
+                    term = Real(0);
+                } else {
+                    const Real x[13] = {p[0], p[1], p[2], v[0], v[1], v[2], q[0], q[1], q[2], q[3], w[0], w[1], w[2]};
+#pragma unroll
+                    for (int i = 0; i < 13; ++i) {
+                        const Real e = x[i] - xr[i];
+                        term += (Real)a.Q[i] * e * e;
+                    }
                 }
-                if (rate) {  // Eq. (8)'s u_k is the sampled thrust rate
+                if (RATE) {  // Eq. (8)'s u_k is the sampled thrust rate
                     term += (Real)a.R_dT[0] * u.x * u.x + (Real)a.R_dT[1] * u.y * u.y + (Real)a.R_dT[2] * u.z * u.z +
                             (Real)a.R_dT[3] * u.w * u.w;
                 } else {
@@ -657,6 +721,16 @@ __device__ __forceinline__ void rollout1_body(const KArgs &a, int blk)
                     term += rdt[0] * d0 * d0 + rdt[1] * d1 * d1 + rdt[2] * d2 * d2 + rdt[3] * d3 * d3;
                 }
             } else {  // contouring
+                Real tq = Real(0);
+                if (PIPE) {
+                    tq += qw[0] * w[0] * w[0] + qw[1] * w[1] * w[1] + qw[2] * w[2] * w[2];
+                    J0.add(tq);
+                    const Real d0 = u.x - up[0], d1 = u.y - up[1], d2 = u.z - up[2], d3 = u.w - up[3];
+                    term += rdt[0] * d0 * d0 + rdt[1] * d1 * d1 + rdt[2] * d2 * d2 + rdt[3] * d3 * d3;
+                    const Real dv = V - vp;
+                    term += r_dv * dv * dv;
+                    term -= mu * V;
+                }
                 const Real fl = floor(th_hi * inv_ds);
                 const Real f = ((th_hi - fl * ds) + th_lo) * inv_ds;
                 // table row of theta, always inside [0, P)
@@ -668,39 +742,41 @@ __device__ __forceinline__ void rollout1_body(const KArgs &a, int blk)
                 Real tx = g1 * A[3] + f * B[3], ty = g1 * A[4] + f * B[4], tz = g1 * A[5] + f * B[5];
                 const Real tn = inv_sqrt(tx * tx + ty * ty + tz * tz);
                 tx *= tn; ty *= tn; tz *= tn;
-                const Real ex = st.x[0] - px;
-                const Real ey = st.x[1] - py;
-                const Real ez = st.x[2] - pz;
+                const Real ex = p[0] - px;
+                const Real ey = p[1] - py;
+                const Real ez = p[2] - pz;
                 const Real et = ex * tx + ey * ty + ez * tz;
                 const Real lx = et * tx, ly = et * ty, lz = et * tz;
                 const Real cxe = ex - lx, cye = ey - ly, cze = ez - lz;
-                term += (Real)a.q_l * (lx * lx + ly * ly + lz * lz);
-                term += (Real)a.q_c * (cxe * cxe + cye * cye + cze * cze);
-                term += (Real)a.Q_w[0] * st.x[10] * st.x[10] + (Real)a.Q_w[1] * st.x[11] * st.x[11] +
-                        (Real)a.Q_w[2] * st.x[12] * st.x[12];
-                const Real vk = v;
+                term += q_l * (lx * lx + ly * ly + lz * lz);
+                term += q_c * (cxe * cxe + cye * cye + cze * cze);
+                if (!PIPE) term += qw[0] * w[0] * w[0] + qw[1] * w[1] * w[1] + qw[2] * w[2] * w[2];
                 Real adv;  // arc length advanced over the step
-                if (rate) {
+                if (RATE) {
                     // Eq. (9) with the progress acceleration as the input and
                     // the speed as a state, which moves linearly over the step
-                    term += (Real)a.r_dv * vk * vk;
+                    term += r_dv * V * V;
                     term += (Real)a.R_dT[0] * u.x * u.x + (Real)a.R_dT[1] * u.y * u.y + (Real)a.R_dT[2] * u.z * u.z +
                             (Real)a.R_dT[3] * u.w * u.w;
-                    term -= (Real)a.mu * (Real)vs;
-                    const double vsn = vs + a.dt * (double)vk;
+                    term -= mu * (Real)vs;
+                    const double vsn = vs + a.dt * (double)V;
                     adv = (Real)(0.5 * a.dt * (vs + vsn));
                     vs = vsn;
                 } else {
-                    const Real dv = vk - vp;
-                    term += (Real)(a.r_dv / (a.dt * a.dt)) * dv * dv;
-                    const Real d0 = u.x - up[0], d1 = u.y - up[1], d2 = u.z - up[2], d3 = u.w - up[3];
-                    term += rdt[0] * d0 * d0 + rdt[1] * d1 * d1 + rdt[2] * d2 * d2 + rdt[3] * d3 * d3;
-                    term -= (Real)a.mu * vk;
-                    adv = vk * dt;
+                    if (!PIPE) {
+                        const Real dv = V - vp;
+                        term += r_dv * dv * dv;
+                        const Real d0 = u.x - up[0], d1 = u.y - up[1], d2 = u.z - up[2], d3 = u.w - up[3];
+                        term += rdt[0] * d0 * d0 + rdt[1] * d1 * d1 + rdt[2] * d2 * d2 + rdt[3] * d3 * d3;
+                        term -= mu * V;
+                    }
+                    adv = V * dt;
                 }
-                vp = vk;
+                vp = V;
                 {   // theta_{k+1} = theta_k + advance (mod L), compensated in binary32
-                    const Real y = adv + th_lo;
+                    Real y;
+                    if (PIPE) y = V * dt + th_lo;
+                    else y = adv + th_lo;
                     const Real t = th_hi + y;
                     th_lo = (sizeof(Real) == 4) ? y - (t - th_hi) : Real(0);
                     th_hi = t;
@@ -708,39 +784,103 @@ __device__ __forceinline__ void rollout1_body(const KArgs &a, int blk)
                 }
             }
 
-            // ---- dynamics
-            Real dx[13];
-            if (rate) {
-                // the thrusts move linearly over the step: RK4 of the 17-state
-                // system sees them at the start, middle and end of the step
+            // ---- dynamics: RK4 of Eq. (2).  The rate model's thrusts move
+            // linearly over the step: its stages see them at the start, middle
+            // and end of it.
+            StepInput<Real> in[3];
+            if (RATE) {
                 const double h = 0.5 * a.dt, ur[4] = {(double)u.x, (double)u.y, (double)u.z, (double)u.w};
-                const StepInput<Real> in1 = step_input(M, (Real)T[0], (Real)T[1], (Real)T[2], (Real)T[3]);
-                const StepInput<Real> in2 = step_input(M, (Real)(T[0] + h * ur[0]), (Real)(T[1] + h * ur[1]),
-                                                       (Real)(T[2] + h * ur[2]), (Real)(T[3] + h * ur[3]));
-                const StepInput<Real> in4 = step_input(M, (Real)(T[0] + a.dt * ur[0]), (Real)(T[1] + a.dt * ur[1]),
-                                                       (Real)(T[2] + a.dt * ur[2]), (Real)(T[3] + a.dt * ur[3]));
-                rk4_increment_stages(M, in1, in2, in4, st.x, dt, dx);
+                in[0] = step_input(M, (Real)T[0], (Real)T[1], (Real)T[2], (Real)T[3]);
+                in[1] = step_input(M, (Real)(T[0] + h * ur[0]), (Real)(T[1] + h * ur[1]), (Real)(T[2] + h * ur[2]),
+                                   (Real)(T[3] + h * ur[3]));
+                in[2] = step_input(M, (Real)(T[0] + a.dt * ur[0]), (Real)(T[1] + a.dt * ur[1]),
+                                   (Real)(T[2] + a.dt * ur[2]), (Real)(T[3] + a.dt * ur[3]));
                 for (int i = 0; i < 4; ++i) T[i] += a.dt * ur[i];
             } else {
-                const StepInput<Real> in = step_input(M, u.x, u.y, u.z, u.w);
-                rk4_increment(M, in, st.x, dt, dx);
+                in[0] = step_input(M, u.x, u.y, u.z, u.w);
             }
-            commit(st, dx);
+            Real dp[3], dv[3], dq[4], dw[3];
+            {
+                Real vst[3], qs[4], ws[3];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) { vst[i] = v[i]; ws[i] = w[i]; }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) qs[i] = q[i];
+#pragma unroll
+                for (int st = 0; st < 4; ++st) {
+                    const StepInput<Real> &si = in[RATE ? (st == 0 ? 0 : (st < 3 ? 1 : 2)) : 0];
+                    Real kv[3], kw[3], kq[4];
+                    stage_accel<DRAG>(M, si.fm, qs, vst, kv);
+                    kw[0] = si.tx - M.gx * ws[1] * ws[2];
+                    kw[1] = si.ty - M.gy * ws[2] * ws[0];
+                    kw[2] = si.tz - M.gz * ws[0] * ws[1];
+                    // kq is twice the quaternion rate; the factor 1/2 is
+                    // carried by the step sizes (exact: a power of two)
+                    kq[0] = -qs[1] * ws[0] - qs[2] * ws[1] - qs[3] * ws[2];
+                    kq[1] = qs[0] * ws[0] + qs[2] * ws[2] - qs[3] * ws[1];
+                    kq[2] = qs[0] * ws[1] - qs[1] * ws[2] + qs[3] * ws[0];
+                    kq[3] = qs[0] * ws[2] + qs[1] * ws[1] - qs[2] * ws[0];
+                    if (st == 0) {
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) { dp[i] = vst[i]; dv[i] = kv[i]; dw[i] = kw[i]; }
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) dq[i] = kq[i];
+                    } else if (st < 3) {
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) {
+                            dp[i] += Real(2) * vst[i];
+                            dv[i] += Real(2) * kv[i];
+                            dw[i] += Real(2) * kw[i];
+                        }
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) dq[i] += Real(2) * kq[i];
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) {
+                            dp[i] = dt6 * (dp[i] + vst[i]);
+                            dv[i] = dt6 * (dv[i] + kv[i]);
+                            dw[i] = dt6 * (dw[i] + kw[i]);
+                        }
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            if (PIPE) {
+                                q[i] = q[i] + dt12 * (dq[i] + kq[i]);
+                            } else {
+                                dq[i] = dt12 * (dq[i] + kq[i]);
+                                q[i] += dq[i];
+                            }
+                        }
+                    }
+                    if (st < 3) {
+                        const Real hh = st < 2 ? h2 : dt, hq = st < 2 ? h4 : h2;
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) {
+                            vst[i] = v[i] + hh * kv[i];
+                            ws[i] = w[i] + hh * kw[i];
+                        }
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) qs[i] = q[i] + hq * kq[i];
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 3; ++i) { p[i] += dp[i]; v[i] += dv[i]; w[i] += dw[i]; }
+            renormalize(q);
 
             // ---- progress and switching (gate)
-            if (OBJ == OBJ_GATE) {
+            if (GATE) {
                 // |p_{k+1} - c|^2 - |p_k - c|^2 = dp . (2 (p_k - c) + dp)
-                term += dx[0] * (Real(2) * ax + dx[0]) + dx[1] * (Real(2) * ay + dx[1]) +
-                        dx[2] * (Real(2) * az + dx[2]);
+                term += dp[0] * (Real(2) * ax + dp[0]) + dp[1] * (Real(2) * ay + dp[1]) +
+                        dp[2] * (Real(2) * az + dp[2]);
                 const Real sa = ax * gt.nx + ay * gt.ny;
-                const Real sb = (ax + dx[0]) * gt.nx + (ay + dx[1]) * gt.ny;
+                const Real sb = (ax + dp[0]) * gt.nx + (ay + dp[1]) * gt.ny;
                 if (sa < Real(0) && sb >= Real(0)) {
                     const Real t = sa / (sa - sb);
-                    const Real yx = ax + t * dx[0], yy = ay + t * dx[1], yz = az + t * dx[2];
+                    const Real yx = ax + t * dp[0], yy = ay + t * dp[1], yz = az + t * dp[2];
                     const Real lat = yx * gt.hx + yy * gt.hy;
                     const bool inside = fabs(lat) <= half && fabs(yz) <= half;
                     const int j = k + 1;
-                    const bool allowed = passes > 0 || ((cur->allow[j >> 5] >> (j & 31)) & 1u);
+                    const bool allowed = passes > 0 || ((h.allow[j >> 5] >> (j & 31)) & 1u);
                     if (inside && allowed) {
                         g = (g + 1 == a.G) ? 0 : g + 1;
                         ++passes;
@@ -749,34 +889,68 @@ __device__ __forceinline__ void rollout1_body(const KArgs &a, int blk)
                 }
             }
             // ---- body-rate penalty on the new state
+            if (PIPE) {
+                Real rl = Real(0);
 #pragma unroll
-            for (int i = 10; i < 13; ++i) {
-                const Real e = fmax(fabs(st.x[i]) - w_max, Real(0));
-                term += w_lim * e * e;
+                for (int i = 0; i < 3; ++i) {
+                    const Real e = fmax(fabs(w[i]) - w_max, Real(0));
+                    rl += w_lim * e * e;
+                }
+                J0.add(rl);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    const Real e = fmax(fabs(w[i]) - w_max, Real(0));
+                    term += w_lim * e * e;
+                }
             }
             J.add(term);
-            up[0] = u.x; up[1] = u.y; up[2] = u.z; up[3] = u.w;
-            u = un;
-            v = vn;
+            if (!GATE && !RATE) { up[0] = u.x; up[1] = u.y; up[2] = u.z; up[3] = u.w; }
         }
-        if (OBJ == OBJ_TRACK) {
+        if (TRACK) {
             int r = i0 + N;
-            if (r > a.R - 1) r = a.R - 1;
+            if (r > R - 1) r = R - 1;
             const Real *xr = xref + 16 * r;
             Real term = 0;
+            if (PIPE) {
 #pragma unroll
-            for (int i = 0; i < 13; ++i) {
-                const Real e = st.x[i] - xr[i];
-                term += (Real)a.QN[i] * e * e;
+                for (int i = 0; i < 3; ++i) {
+                    const Real e = w[i] - xr[10 + i];
+                    term += (Real)a.QN[10 + i] * e * e;
+                }
+                J0.add(term);
+                term = 0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const Real e = q[i] - xr[6 + i];
+                    term += (Real)a.QN[6 + i] * e * e;
+                }
+                J1.add(term);
+                term = 0;
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    const Real e = p[i] - xr[i];
+                    term += (Real)a.QN[i] * e * e;
+                    const Real f = v[i] - xr[3 + i];
+                    term += (Real)a.QN[3 + i] * f * f;
+                }
+                J2.add(term);
+            } else {
+                const Real x[13] = {p[0], p[1], p[2], v[0], v[1], v[2], q[0], q[1], q[2], q[3], w[0], w[1], w[2]};
+#pragma unroll
+                for (int i = 0; i < 13; ++i) {
+                    const Real e = x[i] - xr[i];
+                    term += (Real)a.QN[i] * e * e;
+                }
+                J.add(term);
             }
-            J.add(term);
         }
-        if (OBJ == OBJ_GATE && nominal) {
-            const Real bx = st.x[0] - g0r.cx;
-            const Real by = st.x[1] - g0r.cy;
+        if (GATE && nominal) {
+            const Real bx = p[0] - g0r.cx;
+            const Real by = p[1] - g0r.cy;
             a.front8[N] = (bx * g0r.nx + by * g0r.ny) < Real(0);
         }
-        Jfinal = J.value();
+        Jfinal = PIPE ? ((J0.value() + J1.value()) + J2.value()) + J.value() : J.value();
         if (nominal) a.cur->J_nom = (double)Jfinal;
         else ((Real *)a.J)[m] = Jfinal;
     }
@@ -784,9 +958,22 @@ __device__ __forceinline__ void rollout1_body(const KArgs &a, int blk)
     store_tile_min(Jfinal, active && !nominal && isfinite(Jfinal), a.tmin, blk);
 }
 
+// The variant of a launch: input model and drag are launch constants.
+template <int OBJ, typename Real, bool DRAW, bool PIPE = false, typename Head>
+__device__ __forceinline__ void rollout1_body(const KArgs &a, int blk, const Head &h)
+{
+    if (!DRAW && !PIPE && a.input_model == INPUT_RATE) {
+        if (a.has_drag) rollout1_steps<OBJ, Real, false, false, !DRAW && !PIPE, true>(a, blk, h);
+        else rollout1_steps<OBJ, Real, false, false, !DRAW && !PIPE, false>(a, blk, h);
+    } else {
+        if (a.has_drag) rollout1_steps<OBJ, Real, DRAW, PIPE, false, true>(a, blk, h);
+        else rollout1_steps<OBJ, Real, DRAW, PIPE, false, false>(a, blk, h);
+    }
+}
+
 template <int OBJ, typename Real, bool DRAW> __global__ __launch_bounds__(64) void k_rollout(KArgs a)
 {
-    rollout1_body<OBJ, Real, DRAW>(a, blockIdx.x);
+    rollout1_body<OBJ, Real, DRAW>(a, blockIdx.x, *(const DevCur *)a.cur);
 }
 
 // ---------------------------------------------------------------- rollout, two waves
@@ -2609,7 +2796,7 @@ template <int OBJ, typename Real, int WAVES> __global__ __launch_bounds__(64 * W
         stage_args(s_a, s_ctx, b, item);
         const int blk = u - b.tile_prefix[item];
         if (WAVES == 2) rollout2_body<OBJ, Real>(s_a, blk);
-        else rollout1_body<OBJ, Real>(s_a, blk);
+        else rollout1_body<OBJ, Real, false>(s_a, blk, *(const DevCur *)s_a.cur);
     }
 }
 

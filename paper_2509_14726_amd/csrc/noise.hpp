@@ -42,6 +42,13 @@ template <typename Real> __device__ __forceinline__ Real unit_open(uint32_t w)
 {
     return (Real)(int32_t)(2u * (w >> 9) + 1u) * (Real)(1.0 / 16777216.0);
 }
+// binary32 in two instructions instead of four: the 23 bits as the fraction of
+// a number in [1, 2), 1 + (w >> 9) 2^-23, less 1 - 2^-24.  Both terms and the
+// difference (2 (w >> 9) + 1) 2^-24 are binary32 numbers, so it is exact.
+template <> __device__ __forceinline__ float unit_open<float>(uint32_t w)
+{
+    return __uint_as_float(__builtin_amdgcn_alignbit(127u, w, 9u)) - 0x1.fffffep-1f;
+}
 
 template <typename Real> struct Normal4 { Real z0, z1, z2, z3; };
 

@@ -41,6 +41,33 @@ __device__ __forceinline__ StepInput<Real> step_input(const Model<Real> &M, Real
     return s;
 }
 
+// Acceleration of one RK4 stage: F/m times the thrust direction (third column
+// of R(q); the factor 2 of its first two components rides on F/m, exact: a
+// power of two), gravity and the rotor drag - R D R^T v.
+template <bool DRAG, typename Real>
+__device__ __forceinline__ void stage_accel(const Model<Real> &M, Real fm, const Real *q, const Real *v, Real *kv)
+{
+    const Real fm2 = Real(2) * fm;
+    const Real r3z = Real(1) - Real(2) * (q[1] * q[1] + q[2] * q[2]);
+    kv[0] = fm2 * (q[1] * q[3] + q[0] * q[2]);
+    kv[1] = fm2 * (q[2] * q[3] - q[0] * q[1]);
+    kv[2] = fm * r3z - M.g;
+    if (DRAG) {
+        const Real qw = q[0], qx = q[1], qy = q[2], qz = q[3];
+        const Real r3x = Real(2) * (q[1] * q[3] + q[0] * q[2]);
+        const Real r3y = Real(2) * (q[2] * q[3] - q[0] * q[1]);
+        const Real r11 = Real(1) - Real(2) * (qy * qy + qz * qz), r12 = Real(2) * (qx * qy - qw * qz);
+        const Real r21 = Real(2) * (qx * qy + qw * qz), r22 = Real(1) - Real(2) * (qx * qx + qz * qz);
+        const Real r31 = Real(2) * (qx * qz - qw * qy), r32 = Real(2) * (qy * qz + qw * qx);
+        const Real b0 = M.d0 * (r11 * v[0] + r21 * v[1] + r31 * v[2]);
+        const Real b1 = M.d1 * (r12 * v[0] + r22 * v[1] + r32 * v[2]);
+        const Real b2 = M.d2 * (r3x * v[0] + r3y * v[1] + r3z * v[2]);
+        kv[0] -= r11 * b0 + r12 * b1 + r3x * b2;
+        kv[1] -= r21 * b0 + r22 * b1 + r3y * b2;
+        kv[2] -= r31 * b0 + r32 * b1 + r3z * b2;
+    }
+}
+
 template <typename Real>
 __device__ __forceinline__ void deriv(const Model<Real> &M, const StepInput<Real> &in, const Real *x,
                                       Real *d)
