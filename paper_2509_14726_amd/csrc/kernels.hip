@@ -2925,6 +2925,33 @@ template <int OBJ, typename Real, int B> __global__ __launch_bounds__(256) void 
     }
 }
 
+// One-wave rollouts that draw their samples (binary32, thrust input): no
+// sample kernel.  PIPE: with the pipelined rollout's arithmetic, for launches
+// whose tiles fill the chip several times over: a tile then costs the issue
+// of one wave's operations instead of the pipeline's latency and handoffs.
+template <int OBJ, typename Real, bool PIPE> __global__ __launch_bounds__(64, 4) void kb_rollout_draw(BArgs b)
+{
+    __shared__ KArgs s_a;
+    __shared__ HeadVals h;
+    __shared__ int s_ctx, s_unit;
+    if (threadIdx.x == 0) s_ctx = -1;
+    const int n = b.desc->n, total = b.desc->n_tiles;
+    int item = 0;
+    for (;;) {
+        __syncthreads();
+        if (threadIdx.x == 0) s_unit = (int)atomicAdd(&b.desc->queue, 1u);
+        __syncthreads();
+        const int u = s_unit;
+        if (u >= total) break;
+        item = advance_item(b.tile_prefix, n, u, item);
+        stage_args(s_a, s_ctx, b, item);
+        const int blk = u - b.tile_prefix[item];
+        compute_head<OBJ == OBJ_CONTOUR>(s_a, h);
+        if (blk == 0 && threadIdx.x == 0) publish_head(s_a, h);
+        rollout1_body<OBJ, Real, true, PIPE>(s_a, blk, h);
+    }
+}
+
 // One unit per (item, 64-sample tile) of the control-cost term; items
 // without the term are skipped.
 template <typename Real, bool HAS_V> __global__ __launch_bounds__(64) void kb_ctrl_cost(BArgs b)
@@ -2973,9 +3000,20 @@ template <typename Real, int OBJ>
 static hipError_t launch_batch_t(const BArgs &b, const BatchLaunch &L, hipStream_t st)
 {
     constexpr bool HAS_V = OBJ == OBJ_CONTOUR;
-    if (L.rollout_waves < 3)
+    if constexpr (sizeof(Real) == 4) {
+        if (L.draw) {
+            if (L.rollout_waves == 4)
+                hipLaunchKernelGGL((kb_rollout_draw<OBJ, Real, true>), dim3(L.draw_groups), dim3(64), 0, st, b);
+            else
+                hipLaunchKernelGGL((kb_rollout_draw<OBJ, Real, false>), dim3(L.draw_groups), dim3(64), 0, st, b);
+        }
+    }
+    if (L.draw) {
+    } else if (L.rollout_waves < 3) {
         hipLaunchKernelGGL((kb_sample<Real, HAS_V>), dim3(L.sample_groups), dim3(256), 0, st, b);
-    if (L.rollout_waves == 4) {
+    }
+    if (L.draw) {
+    } else if (L.rollout_waves == 4) {
         if constexpr (sizeof(Real) == 4) {
             if (L.ring4_b == 4)
                 hipLaunchKernelGGL((kb_rollout4<OBJ, Real, 4>), dim3(L.rollout_groups), dim3(256), 0, st, b);

@@ -27,7 +27,10 @@ struct BatchLaunch {
     bool fp64, acc64;
     int rollout_waves;    // 1..4 (see mppi_batch_cfg)
     int ring4_b;          // four-wave chunk (binary32): 4, one workgroup per CU; 2, two
+    bool draw;            // one-wave rollouts that draw their samples (binary32); with rollout_waves 4
+                          // in the pipeline's arithmetic
     int rollout_groups;   // persistent rollout workgroups
+    int draw_groups;      // the same for the drawing one-wave rollouts
     int sample_groups;    // grid-stride workgroups of the sample kernel
     int final_groups;     // grid-stride workgroups of the weighted-average kernel
     int ctrl_groups;      // grid-stride workgroups of the control-cost kernel (0: no item has the term)

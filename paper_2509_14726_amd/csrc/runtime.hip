@@ -997,8 +997,8 @@ struct mppi_batch {
     std::vector<KArgs> h_table;  // host copy of d_table
     std::vector<BatchGroup> groups;
     mppi_batch_cfg cfg{};
-    hipGraphExec_t exec = nullptr;
-    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec[2] = {};  // captured launch sequences: [1] for steps with wide groups
+    hipGraph_t graph[2] = {};
     hipEvent_t copy_done = nullptr;
     bool copy_pending = false;
     int n_cu = 256;
@@ -1031,10 +1031,12 @@ static mppi_status bfail(mppi_batch *b, mppi_status s, const char *fmt, ...)
 
 static void drop_graph(mppi_batch *b)
 {
-    if (b->exec) (void)hipGraphExecDestroy(b->exec);
-    if (b->graph) (void)hipGraphDestroy(b->graph);
-    b->exec = nullptr;
-    b->graph = nullptr;
+    for (int w = 0; w < 2; ++w) {
+        if (b->exec[w]) (void)hipGraphExecDestroy(b->exec[w]);
+        if (b->graph[w]) (void)hipGraphDestroy(b->graph[w]);
+        b->exec[w] = nullptr;
+        b->graph[w] = nullptr;
+    }
 }
 
 // Resolve automatic fields of the launch shape for this batch.
@@ -1079,7 +1081,13 @@ static hipError_t resolve_cfg(mppi_batch *b)
         g.launch.acc64 = g.acc64;
         g.launch.rollout_waves = waves;
         g.launch.ring4_b = ring;
+        // one-wave rollouts of thrust contexts draw their samples themselves
+        // in binary32 (no sample pass); where a context takes rates, the
+        // sample kernel draws for all
+        g.launch.draw = waves == 1 && !b->fp64 && !b->has_rate;
         g.launch.rollout_groups = rg;
+        // one-wave workgroups, four per SIMD
+        g.launch.draw_groups = c.rollout_groups > 0 && waves == 1 ? c.rollout_groups : 16 * cu;
         g.launch.sample_groups = sg;
         // kFinalThreads-thread workgroups, two per CU
         g.launch.final_groups = 2 * b->n_cu;
@@ -1247,14 +1255,16 @@ mppi_status mppi_batch_get_cfg(const mppi_batch *b, mppi_batch_cfg *cfg)
 // The launch sequence of one step: n_iter iterations, the later ones reading
 // the inner copy of the argument table (no shift, the first iteration's last
 // applied input), each group's kernels in turn.
-static mppi_status enqueue_groups(mppi_batch *b, bool skip_empty)
+static mppi_status enqueue_groups(mppi_batch *b, bool skip_empty, bool wide)
 {
     for (int it = 0; it < b->n_iter; ++it) {
         for (auto &g : b->groups) {
             if (skip_empty && g.active == 0) continue;
             BArgs ba = g.bargs;
             if (it > 0) ba.table = b->d_table + b->ctxs.size();
-            BHIP_TRY(b, launch_batch(ba, g.launch, b->stream));
+            BatchLaunch l = g.launch;
+            if (wide) l.draw = true;
+            BHIP_TRY(b, launch_batch(ba, l, b->stream));
         }
     }
     return MPPI_OK;
@@ -1275,6 +1285,7 @@ static mppi_status batch_solve(mppi_batch *b, const int32_t *active, int32_t n_a
     std::vector<char> seen(n, 0);
     for (auto &g : b->groups) g.active = 0;
     std::vector<std::vector<std::pair<int, int>>> per(b->groups.size());  // (registered index, slot)
+    int64_t most_tiles = 0;      // of one group's launch
     for (int i = 0; i < n_active; ++i) {
         const int r = active ? active[i] : i;
         if (r < 0 || r >= n) return bfail(b, MPPI_E_INVAL, "active[%d]=%d outside [0, %d)", i, r, n);
@@ -1322,6 +1333,7 @@ static mppi_status batch_solve(mppi_batch *b, const int32_t *active, int32_t n_a
         desc->n = (int32_t)lst.size();
         desc->n_sample_units = (int32_t)s_units;
         desc->n_tiles = (int32_t)t_units;
+        if (t_units > most_tiles) most_tiles = t_units;
         desc->n_steps = (int32_t)a_units;
         desc->queue = 0u;
         desc->sample_queue = 0u;
@@ -1330,21 +1342,27 @@ static mppi_status batch_solve(mppi_batch *b, const int32_t *active, int32_t n_a
     }
     BHIP_TRY(b, hipEventRecord(b->copy_done, b->stream));
     b->copy_pending = true;
+    // Pipelined contexts in a step with more tiles than the chip holds
+    // pipelines (two per CU) run one-wave rollouts in the pipeline's
+    // arithmetic: the same results.
+    const bool wide = !b->groups.empty() && b->groups[0].launch.rollout_waves == 4 && !b->fp64 &&
+                      most_tiles > 2 * b->n_cu;
     if (b->cfg.use_graph) {
-        if (!b->exec) {
+        hipGraphExec_t &exec = b->exec[wide ? 1 : 0];
+        if (!exec) {
             BHIP_TRY(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-            mppi_status st = enqueue_groups(b, false);
+            mppi_status st = enqueue_groups(b, false, wide);
             hipGraph_t graph = nullptr;
             hipError_t e = hipStreamEndCapture(b->stream, &graph);
             if (st != MPPI_OK) { if (graph) (void)hipGraphDestroy(graph); return st; }
             if (e != hipSuccess) return bfail(b, MPPI_E_DEVICE, "graph capture failed: %s", hipGetErrorString(e));
-            b->graph = graph;
-            BHIP_TRY(b, hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0));
+            b->graph[wide ? 1 : 0] = graph;
+            BHIP_TRY(b, hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
         }
-        BHIP_TRY(b, hipGraphLaunch(b->exec, b->stream));
+        BHIP_TRY(b, hipGraphLaunch(exec, b->stream));
         return MPPI_OK;
     }
-    return enqueue_groups(b, true);
+    return enqueue_groups(b, true, wide);
 }
 
 extern "C" {
