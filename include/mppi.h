@@ -348,11 +348,11 @@ typedef struct mppi_batch mppi_batch;
 typedef struct {
     int32_t rollout_waves;     /* waves per 64-sample tile: 1 (separate sampling
                                   kernel), 2 (attitude / translation split), 3
-                                  (sampling joins the rollout) or 4 (four-stage
-                                  pipeline: sampling with body rates, attitude,
-                                  translation, sampling with position costs;
-                                  chunks of 4 steps with one workgroup per CU,
-                                  of 2 with two, the same results);
+                                  (sampling joins the rollout) or 4 (pipeline:
+                                  body rates, attitude, translation, costs and
+                                  the draws on waves of their own, coupled by
+                                  LDS rings of 8 steps with one workgroup per
+                                  CU, of 4 with two, the same results);
                                   0: automatic (binary32: 4 for at most two
                                   64-sample tiles per CU, else 1; binary64: 4
                                   for at most one, 2 for at most two, else 1;
@@ -423,7 +423,7 @@ const char *mppi_batch_last_error(const mppi_batch *b);
  * tile minima) fits in the free part of a device arena of budget_bytes, and
  * launches them as one batch.  A launch holds the drones of one class, that of
  * the oldest queued head: one rollout layout (mppi_info.rollout_waves and the
- * four-wave chunk, which each context picks from K at creation, or from
+ * pipeline's ring size, which each context picks from K at creation, or from
  * MPPI_ROLLOUT_WAVES) and one n_iter, and runs them in that layout.  Requests that arrive
  * while others run are admitted as slots and memory free up; the slots' work
  * overlaps on the device.  A solve's result is the same as that of the

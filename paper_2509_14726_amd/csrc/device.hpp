@@ -65,9 +65,10 @@ struct KArgs {
     int32_t K, N, G, P, R, objective;
     int32_t C, real_bytes;      // channels (4, 5 contouring); bytes of Real (for ws_layout)
     int32_t n_tiles;            // 64-sample rollout tiles: ceil((K + 1) / 64)
-    int32_t ring4_b;            // chunk of the four-wave rollout: 4 or 2 steps (binary32)
+    int32_t ring_steps;         // LDS rings of the pipelined rollout: 8 or 4 steps (binary64: 4)
     int32_t proj_window, has_drag;
-    int32_t rollout_waves;      // 1: one wave per 64 samples; 2: attitude and translation on two waves; 3, 4
+    int32_t rollout_waves;      // 1: one wave per 64 samples; 2: attitude and translation on two waves; 3;
+                                // 4: the pipeline
     int32_t regen;              // 1: no sample tensor; the weighted average draws the samples again
                                 // (three- and four-wave layouts, whose rollout draws them)
     int32_t rollout_draw;       // 1: the one-wave rollout draws its samples (no sample kernel)

@@ -2,12 +2,12 @@
 //
 //   k_setup          once per context: problem tables -> device layout in Real
 //   k_rollout4       (default for small K) a 64-sample tile per workgroup, the
-//                    step pipelined over four waves: noise and clipped samples
+//                    step pipelined over its waves: noise and clipped samples
 //                    (Eq. (3)), RK4 of Eq. (2) split into body rates, attitude
 //                    and translation, per-step costs fused in (gate Eq. (6)-(7),
 //                    tracking Eq. (8), contouring Eq. (9)); cost write and the
 //                    smallest cost of the tile
-//   k_rollout3       the same over three waves
+//   k_rollout3       three waves, chunks of steps between barriers
 //   k_sample +       (large K) noise and clipped samples for all (m, k), then
 //   k_rollout /      one sample per lane (k_rollout) or attitude and
 //   k_rollout_split  translation on two waves (k_rollout_split)
@@ -149,7 +149,43 @@ __device__ __forceinline__ double rate_speed0(const KArgs &a, const DevWarm *w, 
     return v;
 }
 
-// Run by all threads of one block (any size up to 512); h is in LDS.  A
+// Minimum over the 64 lanes of a wave (all lanes active), returned to every
+// lane.  Binary32 goes through DPP moves, each a few cycles instead of an
+// LDS-crossbar round trip: two quad permutes ([1,0,3,2], [2,3,0,1]), row
+// shifts by 4 and 8 (lane 15 of each row then holds the row's minimum), the
+// broadcast of lane 15 into rows 1 and 3 and of lane 31 into rows 2 and 3
+// (lane 63 then holds the wave's minimum); a lane without a source keeps
+// +inf.  Binary64 and integers use lane shuffles.  A minimum does not depend
+// on the order of the comparisons, so either way every caller sees the same
+// value.
+template <int CTRL, int ROW_MASK = 0xf> __device__ __forceinline__ float dpp_or_inf(float v)
+{
+    return __int_as_float(
+        __builtin_amdgcn_update_dpp(__float_as_int(INFINITY), __float_as_int(v), CTRL, ROW_MASK, 0xf, false));
+}
+
+__device__ __forceinline__ float wave_min(float v)
+{
+    float o;
+    o = dpp_or_inf<0xb1>(v);       v = o < v ? o : v;
+    o = dpp_or_inf<0x4e>(v);       v = o < v ? o : v;
+    o = dpp_or_inf<0x114>(v);      v = o < v ? o : v;
+    o = dpp_or_inf<0x118>(v);      v = o < v ? o : v;
+    o = dpp_or_inf<0x142, 0xa>(v); v = o < v ? o : v;
+    o = dpp_or_inf<0x143, 0xc>(v); v = o < v ? o : v;
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+template <typename T> __device__ __forceinline__ T wave_min(T v)
+{
+    for (int off = 32; off > 0; off >>= 1) {
+        const T o = __shfl_xor(v, off, 64);
+        v = o < v ? o : v;
+    }
+    return v;
+}
+
+// Run by all threads of one block (whole waves, up to 1024 threads); h is in LDS.  A
 // kernel built for another objective than contouring passes CONTOUR = false
 // and allocates no LDS for the projection.
 template <bool CONTOUR = true> __device__ void compute_head(const KArgs &a, HeadVals &h)
@@ -160,9 +196,8 @@ template <bool CONTOUR = true> __device__ void compute_head(const KArgs &a, Head
 
     double theta0 = 0.0;
     if (CONTOUR && a.objective == OBJ_CONTOUR) {
-        __shared__ double s_d2[512];   // one entry per thread, up to 512 threads
-        __shared__ double s_th[512];
-        __shared__ int s_j[512];
+        __shared__ double s_d2[16], s_th[16];   // one entry per wave
+        __shared__ int s_j[16];
         // the block size, read once (a read from the dispatch's implicit
         // arguments, which inside the barrier loop below would be repeated
         // at every barrier)
@@ -193,20 +228,20 @@ template <bool CONTOUR = true> __device__ void compute_head(const KArgs &a, Head
             const double dd = d0 * d0 + d1 * d1 + d2 * d2;
             if (dd < best) { best = dd; best_th = ((double)i + t) * ds; best_j = j; }
         }
-        s_d2[tid] = best; s_th[tid] = best_th; s_j[tid] = best_j;
+        // smallest distance, ties to the first candidate in search order: in
+        // each wave, then over the waves' results, with one barrier (a tree of
+        // barriers over all threads took nine, and 10 KB of LDS)
+        const double wd = wave_min(best);
+        const int wj = wave_min(best == wd ? best_j : 0x7fffffff);
+        if (best == wd && best_j == wj) { s_d2[tid >> 6] = wd; s_th[tid >> 6] = best_th; s_j[tid >> 6] = wj; }
         __syncthreads();
-        // smallest distance, ties to the first candidate in search order
-        for (int st = 256; st > 0; st >>= 1) {
-            if (tid < st && tid + st < nthr) {
-                const double d_o = s_d2[tid + st];
-                const int j_o = s_j[tid + st];
-                if (d_o < s_d2[tid] || (d_o == s_d2[tid] && j_o < s_j[tid])) {
-                    s_d2[tid] = d_o; s_th[tid] = s_th[tid + st]; s_j[tid] = j_o;
-                }
-            }
-            __syncthreads();
+        double md = s_d2[0], mt = s_th[0];
+        int mj = s_j[0];
+        for (int i = 1; i < (nthr >> 6); ++i) {
+            const double d_o = s_d2[i];
+            if (d_o < md || (d_o == md && s_j[i] < mj)) { md = d_o; mj = s_j[i]; mt = s_th[i]; }
         }
-        theta0 = wrap_len_d(s_th[0], L);
+        theta0 = wrap_len_d(mt, L);
     }
 
     if (tid == 0) {
@@ -413,41 +448,6 @@ template <typename Real, bool HAS_V> __global__ __launch_bounds__(256) void k_he
 }
 
 // ---------------------------------------------------------------- rollout
-
-// Minimum over the 64 lanes of a wave (all lanes active), returned to every
-// lane.  Binary32 goes through DPP moves, each a few cycles instead of an
-// LDS-crossbar round trip: two quad permutes ([1,0,3,2], [2,3,0,1]), row
-// shifts by 4 and 8 (lane 15 of each row then holds the row's minimum), the
-// broadcast of lane 15 into rows 1 and 3 and of lane 31 into rows 2 and 3
-// (lane 63 then holds the wave's minimum); a lane without a source keeps
-// +inf.  Binary64 uses lane shuffles.  A minimum does not depend on the
-// order of the comparisons, so either way every caller sees the same value.
-template <int CTRL, int ROW_MASK = 0xf> __device__ __forceinline__ float dpp_or_inf(float v)
-{
-    return __int_as_float(
-        __builtin_amdgcn_update_dpp(__float_as_int(INFINITY), __float_as_int(v), CTRL, ROW_MASK, 0xf, false));
-}
-
-__device__ __forceinline__ float wave_min(float v)
-{
-    float o;
-    o = dpp_or_inf<0xb1>(v);       v = o < v ? o : v;
-    o = dpp_or_inf<0x4e>(v);       v = o < v ? o : v;
-    o = dpp_or_inf<0x114>(v);      v = o < v ? o : v;
-    o = dpp_or_inf<0x118>(v);      v = o < v ? o : v;
-    o = dpp_or_inf<0x142, 0xa>(v); v = o < v ? o : v;
-    o = dpp_or_inf<0x143, 0xc>(v); v = o < v ? o : v;
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-}
-
-__device__ __forceinline__ double wave_min(double v)
-{
-    for (int off = 32; off > 0; off >>= 1) {
-        const double o = __shfl_xor(v, off, 64);
-        v = o < v ? o : v;
-    }
-    return v;
-}
 
 // Smallest finite sample cost of a 64-sample tile (+inf when there is none),
 // stored by lane 0 of the wave that holds the tile's costs.  The weighted
@@ -1783,102 +1783,175 @@ __device__ __forceinline__ void rollout3_body(const KArgs &a, int blk, const Hea
     __syncthreads();
 }
 
-// ---------------------------------------------------------------- rollout, four-wave pipeline
+// ---------------------------------------------------------------- rollout, pipelined
 
-// The step of Eq. (2) split into four pipeline stages over four waves (one
-// per SIMD), a 64-sample tile per workgroup, chunks of B steps between
-// workgroup barriers.  At chunk iteration c:
-//   wave 0  draws the noise of the even steps of chunk c (Eq. (3)) and
-//           integrates the body rates over chunk c-1 (they depend on the
-//           torques only), with the rate-limit and body-rate cost terms;
-//   wave 3  draws the noise of the odd steps of chunk c and adds the
-//           position cost terms of chunk c-4 (gate progress, near-gate
-//           term, crossing and switch; contouring) and the input-rate terms;
-//   wave 1  integrates the attitude over chunk c-2 from the stage body rates;
-//   wave 2  integrates position and velocity over chunk c-3 from the stage
-//           attitudes, with the tracking terms of position and velocity.
-// Each stage hands its stage values on through LDS rings; every quantity is
-// computed with the same operations as in the three-wave layout, whatever the
-// chunk size B: the chunking only moves the barriers.  B = 4 for binary32
-// with one workgroup per CU; B = 2 halves the rings so that two workgroups
-// share a CU (binary32 with more tiles than CUs; always for binary64, whose
-// rings are twice as large).
-template <int OBJ, typename Real, int B>
+// The step of Eq. (2) split into pipeline stages over the waves of one
+// workgroup, a 64-sample tile per workgroup:
+//   rates        integrates the body rates (they depend on the torques only),
+//                for the gate objective with their rate-limit term;
+//   attitude     integrates the attitude from the stage body rates;
+//   position     integrates position and velocity from the stage attitudes;
+//   costs        adds the cost terms of position (gate progress, near-gate
+//                term, crossing and switch; contouring; tracking of position
+//                and velocity) and, for contouring, of the body rates;
+//   terms        (tracking) the cost terms of attitude and body rates;
+//                (contouring) the path point and tangent of each step, which
+//                depend on the drawn progress speeds only, and the input terms;
+//   draws        the noise and the clipped inputs (Eq. (3)), four waves.
+// Each stage hands its stage values on through an LDS ring of steps and runs
+// as far ahead as the rings allow: a stage publishes how many steps it has
+// done in a counter in LDS, its consumer starts a step once the counter has
+// passed it, and a producer waits while the ring slot that it would overwrite
+// has not been read.  No workgroup barrier falls inside the horizon: with
+// barriers between chunks of 4 steps every stage paid about 1,100 cycles per
+// chunk for the handoff (LDS latency at its start, the drain at its end, the
+// slowest stage).  What bounds a step now is the issue of the busiest wave:
+// the attitude's 85 operations at 5 cycles and its 4 LDS writes at 28 make
+// 630 cycles a step (binary32).  Solves on 129 tiles, gate, N = 100: 46.5 ->
+// 43.0 us; contouring, 94 tiles: 53.8 -> 50.5; tracking, 470 tiles, N = 50:
+// 53.5 -> 43.9; binary64, 129 tiles, N = 100: 130 -> 64 us (there the draws
+// moved to waves of their own as well).
+
+// Progress counters of the pipeline, one set per workgroup in LDS.  The
+// drawing waves publish the next step they will draw, the stages the number
+// of steps they have done.
+enum PipeCounter { PC_DRAW = 0, PC_RATE = 4, PC_ATT = 5, PC_POS = 6, PC_COST = 7, PC_TERM = 8, PC_N = 16 };
+
+// What a wave waits for before it starts a step: each lane watches one
+// counter; step k may start once every lane's counter plus its offset is
+// above k (offset 0: the producer has done step k; a ring's size: the slot of
+// step k has been read).  LDS operations of one wave execute in order, so a
+// data read issued after the counter read sees what was written before the
+// counter was, and a counter written after the data never overtakes it: the
+// compiler is held to that order, the hardware needs no wait for it.
+struct PipeWatch {
+    const int *c;
+    int off;
+    __device__ __forceinline__ int peek() const
+    {
+        return __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) + off;
+    }
+    static __device__ __forceinline__ bool may_start(int seen, int k)
+    {
+        const bool r = __builtin_amdgcn_ballot_w64(seen > k) == ~0ull;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "singlethread");
+        return r;
+    }
+    template <int SLEEP> __device__ __forceinline__ void wait(int k) const
+    {
+        while (!may_start(peek(), k)) __builtin_amdgcn_s_sleep(SLEEP);
+    }
+};
+// Lane 0 writes the counter, the other lanes a word that nothing reads: no
+// change of the execution mask, so the steps around it stay one block.
+__device__ __forceinline__ void pipe_publish(int *c, int v)
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "singlethread");
+    __hip_atomic_store(c, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "singlethread");
+}
+
+// One stage of the pipeline over the steps 0..N-1: load(k, in) reads the
+// inputs of step k from the rings, step(k, in) computes it and writes its
+// output.  The counters and then the inputs of step k + 1 are read while step
+// k computes: if the counters show that the inputs were there, the next step
+// finds them in registers, else both are read again.
+// A step may also prepare its successor's inputs (nxt); first does so for step 0.
+template <typename In, typename Load, typename Step, typename First>
+__device__ __forceinline__ void pipe_run(const int N, const PipeWatch watch, int *const mine, Load load, Step step,
+                                         First first)
+{
+    In a, b;
+    watch.wait<0>(0);
+    load(0, a);
+    first(a);
+    int k = 0;
+    auto one = [&](In &cur, In &nxt) {
+        int seen = watch.peek();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "singlethread");
+        load(k + 1, nxt);
+        step(k, cur, nxt);
+        pipe_publish(mine, ++k);
+        if (k == N) return false;
+        __builtin_amdgcn_sched_barrier(0);
+        if (!PipeWatch::may_start(seen, k)) {
+            watch.wait<0>(k);
+            load(k, nxt);
+        }
+        return true;
+    };
+    while (one(a, b) && one(b, a)) {}
+}
+template <typename In, typename Load, typename Step>
+__device__ __forceinline__ void pipe_run(const int N, const PipeWatch watch, int *const mine, Load load, Step step)
+{
+    pipe_run<In>(N, watch, mine, load, step, [](In &) {});
+}
+
+// Drawing waves of the pipeline: as many as keep the workgroup at eight waves
+// in binary32 (two workgroups then share a CU), four in binary64, whose draws
+// take several times as long.
+constexpr int pipe_draws(int obj, size_t real) { return obj == OBJ_GATE || real == 8 ? 4 : 3; }
+// waves of a workgroup: rates, attitude, position, costs, terms (not for the
+// gate objective), draws
+constexpr int pipe_waves(int obj, size_t real) { return (obj == OBJ_GATE ? 4 : 5) + pipe_draws(obj, real); }
+
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+// The scheduler would otherwise place an operation right behind the one it
+// depends on: a wave issues independent operations every 5 cycles, dependent
+// ones every 10 (measured), so the recurrences are written level by level.
+template <typename Real> __device__ __forceinline__ void level()
+{
+    if (sizeof(Real) == 8) __builtin_amdgcn_sched_barrier(0);
+}
+
+// R: steps of the stage rings (a power of two); the input rings, which span
+// all stages, hold 2 R.
+template <int OBJ, typename Real, int R>
 __device__ __forceinline__ void rollout4_body(const KArgs &a, int blk, const HeadVals &h)
 {
     typedef typename Vec4<Real>::T R4;
-    constexpr bool HAS_V = OBJ == OBJ_CONTOUR;
-    constexpr bool RATE = OBJ != OBJ_GATE;
-    constexpr bool POS = OBJ != OBJ_TRACK;        // position costs in wave 3
-    __shared__ R4 s_in[4][B][64];                  // (F/m, tau_x/J_x, tau_y/J_y, tau_z/J_z), chunk c at c % 4
-    __shared__ R4 s_w[2][B][4][64];                // stage body rates, chunk c at c % 2
-    __shared__ R4 s_q[2][B][4][64];                // stage quaternions, chunk c at c % 2
-    __shared__ R4 s_p[POS ? 2 : 1][B][2][64];      // p_k and its increment; chunk c at c % 2
-    __shared__ R4 s_u[RATE ? 5 : 1][B][64];        // clipped inputs, chunk c at c % 5
-    __shared__ Real s_v[HAS_V ? 5 : 1][B][64];     // progress speed, chunk c at c % 5
+    constexpr bool GATE = OBJ == OBJ_GATE, CONT = OBJ == OBJ_CONTOUR, TRACK = OBJ == OBJ_TRACK;
+    constexpr bool HAS_V = CONT;
+    constexpr int RS = R, RI = 2 * R;
+    static_assert((R & (R - 1)) == 0, "slots are taken modulo a power of two");
+    constexpr int kDrawWaves = pipe_draws(OBJ, sizeof(Real));
+    constexpr int W_DRAW = GATE ? 4 : 5;           // first drawing wave
+    __shared__ R4 s_in[RI][64];                    // (F/m, tau_x/J_x, tau_y/J_y, tau_z/J_z)
+    __shared__ R4 s_w[RS][4][64];                  // stage body rates
+    __shared__ R4 s_q[RS][4][64];                  // stage quaternions
+    __shared__ R4 s_p[RS][2][64];                  // p_k and its increment (tracking: v_k)
+    __shared__ R4 s_u[GATE ? 1 : RI][64];          // clipped inputs
+    __shared__ Real s_v[HAS_V ? RI : 1][64];       // progress speed
+    __shared__ R4 s_t[CONT ? RS : 1][2][64];      // path point and input term; path tangent (tracking: p_N, v_N)
     __shared__ R4 s_us[kNMax];                     // shifted warm-start thrusts per step
     __shared__ Real s_vs[HAS_V ? kNMax : 1];       // shifted warm-start progress speed
-    __shared__ Real s_jp[3][64];                   // partial costs of waves 0, 1, 2
+    __shared__ Real s_jp[3][64];                   // partial costs of the other waves
     __shared__ R4 s_pN[64];                        // p_N (front flag of the nominal)
-    __shared__ Real s_gtab[OBJ == OBJ_GATE ? 8 * kGMax : 1];   // the gate table, staged once
-    __shared__ uint8_t s_f8[OBJ == OBJ_GATE ? kNMax : 1];      // front flags of the nominal, steps 0..N-1
+    __shared__ Real s_gtab[GATE ? 8 * kGMax : 1];  // the gate table, staged once
+    __shared__ uint8_t s_f8[GATE ? kNMax : 1];     // front flags of the nominal, steps 0..N-1
+    __shared__ int s_cnt[PC_N + 64];               // progress counters; then a word per lane that nothing reads
 
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int m = blk * 64 + lane;
     const int K = a.K, N = a.N;
     const bool active = m <= K;
     const bool nominal = m == K;
     const bool sampled = m < K;
-    const Model<Real> M(a);
     const Real dt = (Real)a.dt;
     const Real h2 = Real(0.5) * dt;
     const Real dt6 = dt / Real(6);
     const Real h4 = Real(0.5) * h2, dt12 = Real(0.5) * dt6;
-    const Real w_max = (Real)a.w_max, w_lim = (Real)a.w_lim;
     const Real *xref = (const Real *)a.xref_r;
     const int i0 = h.i0;
-    Real rdt[4];
-    for (int i = 0; i < 4; ++i) rdt[i] = (Real)(a.R_dT[i] / (a.dt * a.dt));
-    const Real r_dv = (Real)(a.r_dv / (a.dt * a.dt));
-
-    KSum<Real> J;
-    Real up[4], vp = (Real)h.v_prev;
-    for (int i = 0; i < 4; ++i) up[i] = (Real)h.u_prev[i];
-    Real q[4], w[3], p[3], v[3];
-    for (int i = 0; i < 4; ++i) {
-        q[i] = (Real)h.x0[6 + i];
-    }
-    for (int i = 0; i < 3; ++i) {
-        w[i] = (Real)h.x0[10 + i];
-        p[i] = (Real)h.x0[i];
-        v[i] = (Real)h.x0[3 + i];
-    }
-    GateRegs<Real> gt, g0r;
-    int g = 0, passes = 0;
-    const Real *gtab = (const Real *)a.gates_r;
-    const Real *path = (const Real *)a.path_r;
-    Real th_hi = 0, th_lo = 0, ds = 0, inv_ds = 0, L = 0;
-    if (OBJ == OBJ_GATE) g = h.g0;
-    if (OBJ == OBJ_CONTOUR) {
-        th_hi = (Real)h.theta0;
-        if (sizeof(Real) == 4) th_lo = (Real)(h.theta0 - (double)th_hi);
-        L = (Real)a.path_len;
-        ds = (Real)(a.path_len / (double)a.P);
-        inv_ds = (Real)((double)a.P / a.path_len);
-    }
-    const Real q_near = (Real)a.q_near, r_near2 = (Real)(a.r_near * a.r_near), half = (Real)a.gate_half;
-    const Real tmin = (Real)a.t_min, tmax = (Real)a.t_max, vmax = (Real)a.v_max;
-    const Real sig0 = (Real)a.sigma[0], sig1 = (Real)a.sigma[1], sig2 = (Real)a.sigma[2], sig3 = (Real)a.sigma[3];
-    const Real sigv = (Real)a.sigma_v, hover = (Real)a.hover;
-    typedef typename Vec4<Real>::T R4g;
-    R4g *ctrl = (R4g *)a.ctrl;
-    Real *vctrl = (Real *)a.vctrl;
+    const Real hover = (Real)a.hover;
 
     // the gate table in LDS: a gate switch inside the pipeline then waits on
     // no global load (which would also wait on the wave's sample stores)
-    if (OBJ == OBJ_GATE)
-        for (int i = threadIdx.x; i < 8 * a.G; i += blockDim.x) s_gtab[i] = gtab[i];
+    if (GATE)
+        for (int i = threadIdx.x; i < 8 * a.G; i += blockDim.x) s_gtab[i] = ((const Real *)a.gates_r)[i];
     // the shifted warm start of every step, staged once
     for (int k = threadIdx.x; k < N; k += blockDim.x) {
         int src = k + h.shift;
@@ -1896,502 +1969,587 @@ __device__ __forceinline__ void rollout4_body(const KArgs &a, int blk, const Hea
             if (HAS_V) ((Real *)a.nomV)[k] = s_vs[k];
         }
     }
+    if (threadIdx.x < PC_N) s_cnt[threadIdx.x] = (int)threadIdx.x < kDrawWaves ? (int)threadIdx.x : 0;
     __syncthreads();
-    if (OBJ == OBJ_GATE) {
-        gt.load(s_gtab, g);
-        g0r = gt;
-    }
 
-    const int nch = (N + B - 1) / B;
-    for (int c = 0; c <= nch + 3; ++c) {
-        // The draws.  With eight waves (one workgroup per CU), waves 4-7 draw
-        // one step of each chunk each and share the SIMDs with the four
-        // integration waves: the Philox products and the Box-Muller
-        // transcendentals run at a quarter of the vector rate and fill issue
-        // slots the latency-bound integration leaves free.  With four waves,
-        // waves 0 and 3 draw every second step.
-        const bool eight = blockDim.x == 8 * 64;
-        constexpr int ND8 = B >= 4 ? 4 : 2;
-        const int ND = eight ? ND8 : 2;
-        const int dslot = eight ? (wave >= 4 && wave - 4 < ND8 ? wave - 4 : -1)
-                                : (wave == 3 ? 1 : (wave == 0 ? 0 : -1));
-        if (dslot >= 0 && c < nch) {
-            // noise, clipped inputs and the per-step thrust and torques
-            const int kb = c * B, ke = min(N, kb + B);
-            const int k_first = dslot;
-            // a step's draw: the clipped inputs (u, V) of sample m at step k;
-            // every lane draws (no branch around the arithmetic, so the steps
-            // of a chunk interleave), the noise-free nominal and the idle
-            // lanes past it with zero noise
-            auto draw = [&](const int k, R4 &u, Real &V) {
-                const R4 w4 = s_us[k];
-                const Real us[4] = {w4.x, w4.y, w4.z, w4.w};
-                const Normal4<Real> z = normals4<Real>((uint32_t)m, (uint32_t)k, h.s, 0u, a.seed_lo, a.seed_hi);
-                const Real p0 = us[0] + sig0 * z.z0, p1 = us[1] + sig1 * z.z1;
-                const Real p2 = us[2] + sig2 * z.z2, p3 = us[3] + sig3 * z.z3;
-                u.x = clamp_finite(sampled ? p0 : us[0], tmin, tmax);
-                u.y = clamp_finite(sampled ? p1 : us[1], tmin, tmax);
-                u.z = clamp_finite(sampled ? p2 : us[2], tmin, tmax);
-                u.w = clamp_finite(sampled ? p3 : us[3], tmin, tmax);
-                V = Real(0);
-                if (HAS_V) {
-                    const Real vs = s_vs[k];
-                    const Real zv = normal1<Real>((uint32_t)m, (uint32_t)k, h.s, 1u, a.seed_lo, a.seed_hi);
-                    const Real pv = vs + sigv * zv;
-                    V = clamp_finite(sampled ? pv : vs, Real(0), vmax);
-                }
-            };
-            // store the samples, hand the inputs on
-            auto put = [&](const int k, const int j, const R4 u, const Real V) {
-                if (sampled && !a.regen) {
-                    const size_t idx = (size_t)k * (size_t)K + (size_t)m;
-                    store_nt(&ctrl[idx], u);
-                    if (HAS_V) store_nt(&vctrl[idx], V);
-                }
-                if (HAS_V) s_v[c % 5][j][lane] = V;
-                if (RATE) s_u[c % 5][j][lane] = u;
-                const StepInput<Real> in = step_input(M, u.x, u.y, u.z, u.w);
-                R4 o;
-                o.x = in.fm; o.y = in.tx; o.z = in.ty; o.w = in.tz;
-                s_in[c % 4][j][lane] = o;
-            };
-            if (ke - kb == B && !eight) {
-                static_assert(B % 2 == 0, "each of two drawing waves takes B / 2 steps of a chunk");
-                constexpr int NS = B / 2;
-                R4 uu[NS];
-                Real vv[NS];
+    auto counter = [&](const int c) { return lane == 0 ? &s_cnt[c] : &s_cnt[PC_N + lane]; };
+    // rate limit on the body rates after a step
+    const Real w_max = (Real)a.w_max, w_lim = (Real)a.w_lim;
+    auto rate_limit = [&](const Real wx, const Real wy, const Real wz) {
+        const Real ww[3] = {wx, wy, wz};
+        Real rl = Real(0);
 #pragma unroll
-                for (int i = 0; i < NS; ++i) draw(kb + k_first + 2 * i, uu[i], vv[i]);
-#pragma unroll
-                for (int i = 0; i < NS; ++i) put(kb + k_first + 2 * i, k_first + 2 * i, uu[i], vv[i]);
-            } else if (ke - kb == B) {
-                static_assert(B % ND8 == 0, "each drawing wave takes B / ND8 steps of a chunk");
-                constexpr int NS = B / ND8;
-                R4 uu[NS];
-                Real vv[NS];
-#pragma unroll
-                for (int i = 0; i < NS; ++i) draw(kb + k_first + ND8 * i, uu[i], vv[i]);
-#pragma unroll
-                for (int i = 0; i < NS; ++i) put(kb + k_first + ND8 * i, k_first + ND8 * i, uu[i], vv[i]);
-            } else {
-                for (int k = kb + k_first; k < ke; k += ND) {
-                    R4 u1;
-                    Real v1;
-                    draw(k, u1, v1);
-                    put(k, k - kb, u1, v1);
-                }
-            }
+        for (int i = 0; i < 3; ++i) {
+            const Real e = fmax(fabs(ww[i]) - w_max, Real(0));
+            rl += w_lim * e * e;
         }
-        if (wave == 0 && c >= 1 && c <= nch) {
-            // body rates over chunk c - 1
-            const int kb = (c - 1) * B, ke = min(N, kb + B);
-            auto omega_step = [&](const int k, const int j, const R4 in) {
-                R4 (*slot)[64] = s_w[(c - 1) & 1][j];
-                Real term = Real(0);
-                if (OBJ == OBJ_TRACK) {
-                    int r = i0 + k;
-                    if (r > a.R - 1) r = a.R - 1;
-                    const Real *xr = xref + 16 * r;
-#pragma unroll
-                    for (int i = 0; i < 3; ++i) {
-                        const Real e = w[i] - xr[10 + i];
-                        term += (Real)a.Q[10 + i] * e * e;
-                    }
-                }
-                if (OBJ == OBJ_CONTOUR)
-                    term += (Real)a.Q_w[0] * w[0] * w[0] + (Real)a.Q_w[1] * w[1] * w[1] +
-                            (Real)a.Q_w[2] * w[2] * w[2];
-                Real ws[3], kw[3], dw[3];
-                R4 stv[4];   // stage body rates, stored once the step is done
-#pragma unroll
-                for (int i = 0; i < 3; ++i) ws[i] = w[i];
-#pragma unroll
-                for (int st = 0; st < 4; ++st) {
-                    stv[st].x = ws[0]; stv[st].y = ws[1]; stv[st].z = ws[2];
-                    kw[0] = in.y - M.gx * ws[1] * ws[2];
-                    kw[1] = in.z - M.gy * ws[2] * ws[0];
-                    kw[2] = in.w - M.gz * ws[0] * ws[1];
-                    if (st == 0) {
-#pragma unroll
-                        for (int i = 0; i < 3; ++i) dw[i] = kw[i];
-                    } else if (st < 3) {
-#pragma unroll
-                        for (int i = 0; i < 3; ++i) dw[i] += Real(2) * kw[i];
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < 3; ++i) dw[i] = dt6 * (dw[i] + kw[i]);
-                    }
-                    if (st < 3) {
-                        const Real hh = st < 2 ? h2 : dt;
-#pragma unroll
-                        for (int i = 0; i < 3; ++i) ws[i] = w[i] + hh * kw[i];
-                    }
-                }
-#pragma unroll
-                for (int i = 0; i < 3; ++i) w[i] += dw[i];
-#pragma unroll
-                for (int st = 0; st < 4; ++st) {
-                    stv[st].w = Real(0);
-                    slot[st][lane] = stv[st];
-                }
-                if (OBJ != OBJ_GATE) J.add(term);
-                // rate limit on the body rates after the step (here rather than
-                // on the attitude wave, whose recurrence sets the pipeline's pace)
-                Real rl = Real(0);
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    const Real e = fmax(fabs(w[i]) - w_max, Real(0));
-                    rl += w_lim * e * e;
-                }
-                J.add(rl);
-            };
-            // the chunk's LDS inputs are loaded before the first step uses them
-            if (ke - kb == B) {
-                R4 inp[B];
-#pragma unroll
-                for (int j = 0; j < B; ++j) inp[j] = s_in[(c - 1) % 4][j][lane];
-#pragma unroll
-                for (int j = 0; j < B; ++j) omega_step(kb + j, j, inp[j]);
-            } else {
-                for (int k = kb; k < ke; ++k) omega_step(k, k - kb, s_in[(c - 1) % 4][k - kb][lane]);
+        return rl;
+    };
+    // row of the tracking reference at state k
+    auto ref_row = [&](const int k) {
+        int r = i0 + k;
+        if (r > a.R - 1) r = a.R - 1;
+        return xref + 16 * r;
+    };
+
+    KSum<Real> J;       // costs: this wave's own part of the cost (wave 3 holds J_3)
+    // two workgroups on a CU: the stages ahead of the draws (tracking, 470
+    // tiles, N = 50: 45.4 -> 43.9 us a solve); with one workgroup the issue
+    // slots are not short (binary64: 64.6 -> 69.9 us, gate 42.9 -> 43.4)
+    if (sizeof(Real) == 4 && R == 4 && wave < W_DRAW) __builtin_amdgcn_s_setprio(3);
+    if (wave >= W_DRAW) {
+        // the draws: drawing wave i takes the steps i, i + kDrawWaves, ...
+        const Model<Real> M(a);
+        const Real tmin = (Real)a.t_min, tmax = (Real)a.t_max, vmax = (Real)a.v_max;
+        // the noise-free nominal and the idle lanes past it draw with zero
+        // noise, so that no step selects between two values
+        const Real sig0 = sampled ? (Real)a.sigma[0] : Real(0), sig1 = sampled ? (Real)a.sigma[1] : Real(0);
+        const Real sig2 = sampled ? (Real)a.sigma[2] : Real(0), sig3 = sampled ? (Real)a.sigma[3] : Real(0);
+        const Real sigv = sampled ? (Real)a.sigma_v : Real(0);
+        R4 *ctrl = (R4 *)a.ctrl;
+        Real *vctrl = (Real *)a.vctrl;
+        const uint32_t s_solve = __builtin_amdgcn_readfirstlane(h.s);
+        const uint32_t key0 = __builtin_amdgcn_readfirstlane(a.seed_lo);
+        const uint32_t key1 = __builtin_amdgcn_readfirstlane(a.seed_hi);
+        const bool keep = sampled && !a.regen;
+        // the slot is free once the position stage and the reader of the inputs have read it
+        const PipeWatch watch = {&s_cnt[GATE || (lane & 1) == 0 ? PC_POS : (CONT ? PC_TERM : PC_COST)], RI};
+        int *const mine = counter(PC_DRAW + wave - W_DRAW);
+        for (int k = wave - W_DRAW; k < N; k += kDrawWaves) {
+            const R4 us = s_us[k];
+            const Normal4<Real> z = normals4<Real>((uint32_t)m, (uint32_t)k, s_solve, 0u, key0, key1);
+            R4 u;
+            u.x = clamp_finite(us.x + sig0 * z.z0, tmin, tmax);
+            u.y = clamp_finite(us.y + sig1 * z.z1, tmin, tmax);
+            u.z = clamp_finite(us.z + sig2 * z.z2, tmin, tmax);
+            u.w = clamp_finite(us.w + sig3 * z.z3, tmin, tmax);
+            Real V = Real(0);
+            if (HAS_V) {
+                const Real zv = normal1<Real>((uint32_t)m, (uint32_t)k, s_solve, 1u, key0, key1);
+                V = clamp_finite(s_vs[k] + sigv * zv, Real(0), vmax);
             }
-        } else if (wave == 1 && c >= 2 && c <= nch + 1) {
-            // attitude over chunk c - 2
-            const int kb = (c - 2) * B, ke = min(N, kb + B);
-            auto quat_step = [&](const int k, const int j, const R4 *wst) {
-                R4 (*slot)[64] = s_q[(c - 2) & 1][j];
-                if (OBJ == OBJ_TRACK) {
-                    int r = i0 + k;
-                    if (r > a.R - 1) r = a.R - 1;
-                    const Real *xr = xref + 16 * r;
-                    Real term = Real(0);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const Real e = q[i] - xr[6 + i];
-                        term += (Real)a.Q[6 + i] * e * e;
-                    }
-                    J.add(term);
-                }
-                Real qs[4], kq[4], dq[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) qs[i] = q[i];
-#pragma unroll
-                for (int st = 0; st < 4; ++st) {
-                    const R4 ws = wst[st];
-                    R4 o;
-                    o.x = qs[0]; o.y = qs[1]; o.z = qs[2]; o.w = qs[3];
-                    slot[st][lane] = o;
-                    // kq is twice the quaternion rate; the factor 1/2 is
-                    // carried by the step sizes (exact: a power of two)
-                    kq[0] = -qs[1] * ws.x - qs[2] * ws.y - qs[3] * ws.z;
-                    kq[1] = qs[0] * ws.x + qs[2] * ws.z - qs[3] * ws.y;
-                    kq[2] = qs[0] * ws.y - qs[1] * ws.z + qs[3] * ws.x;
-                    kq[3] = qs[0] * ws.z + qs[1] * ws.y - qs[2] * ws.x;
-                    if (st == 0) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) dq[i] = kq[i];
-                    } else if (st < 3) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) dq[i] += Real(2) * kq[i];
-                    } else {
-                        // the last stage closes the step in one multiply-add
-                        // per component (this wave's recurrence sets the pace)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) q[i] = q[i] + dt12 * (dq[i] + kq[i]);
-                    }
-                    if (st < 3) {
-                        const Real hq = st < 2 ? h4 : h2;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) qs[i] = q[i] + hq * kq[i];
-                    }
-                }
-                renormalize(q);
-            };
-            if (ke - kb == B) {
-                R4 wpre[B][4];
-#pragma unroll
-                for (int j = 0; j < B; ++j)
-#pragma unroll
-                    for (int st = 0; st < 4; ++st) wpre[j][st] = s_w[(c - 2) & 1][j][st][lane];
-#pragma unroll
-                for (int j = 0; j < B; ++j) quat_step(kb + j, j, wpre[j]);
-            } else {
-                for (int k = kb; k < ke; ++k) {
-                    R4 wst[4];
-#pragma unroll
-                    for (int st = 0; st < 4; ++st) wst[st] = s_w[(c - 2) & 1][k - kb][st][lane];
-                    quat_step(k, k - kb, wst);
-                }
+            // store the samples, hand the inputs on
+            if (keep) {
+                const size_t idx = (size_t)k * (size_t)K + (size_t)m;
+                store_nt(&ctrl[idx], u);
+                if (HAS_V) store_nt(&vctrl[idx], V);
             }
-        } else if (wave == 2 && c >= 3 && c <= nch + 2) {
-            // position and velocity over chunk c - 3
-            const int kb = (c - 3) * B, ke = min(N, kb + B);
-            // drag is a launch constant: the branch sits outside the step, so the
-            // stages of a step (independent without drag) schedule together
-            auto trans_step = [&](const int k, const int j, const Real fm, const R4 *qstage, auto drag_tag) {
-                constexpr bool DRAG = decltype(drag_tag)::value;
-                if (OBJ == OBJ_TRACK) {
-                    int r = i0 + k;
-                    if (r > a.R - 1) r = a.R - 1;
-                    const Real *xr = xref + 16 * r;
-                    Real term = Real(0);
+            const StepInput<Real> in = step_input(M, u.x, u.y, u.z, u.w);
+            R4 o;
+            o.x = in.fm; o.y = in.tx; o.z = in.ty; o.w = in.tz;
+            watch.wait<2>(k);
+            s_in[k & (RI - 1)][lane] = o;
+            if (HAS_V) s_v[k & (RI - 1)][lane] = V;
+            if (!GATE) s_u[k & (RI - 1)][lane] = u;
+            pipe_publish(mine, k + kDrawWaves);
+        }
+    } else if (wave == 0) {
+        // body rates
+        const Model<Real> M(a);
+        Real w[3];
+        for (int i = 0; i < 3; ++i) w[i] = (Real)h.x0[10 + i];
+        // inputs drawn; stage slots read by the attitude, the first of them by the rate costs
+        const int reader = TRACK ? PC_TERM : PC_COST;
+        const PipeWatch watch = {&s_cnt[lane < kDrawWaves ? PC_DRAW + lane : (GATE || (lane & 1) ? PC_ATT : reader)],
+                                 lane < kDrawWaves ? 0 : RS};
+        auto omega_step = [&](const int k, const R4 &in, R4 &) {
+            R4 (*slot)[64] = s_w[k & (RS - 1)];
+            Real ws[3], kw[3], dw[3];
 #pragma unroll
-                    for (int i = 0; i < 3; ++i) {
-                        const Real e = p[i] - xr[i];
-                        term += (Real)a.Q[i] * e * e;
-                    }
+            for (int i = 0; i < 3; ++i) ws[i] = w[i];
 #pragma unroll
-                    for (int i = 0; i < 3; ++i) {
-                        const Real e = v[i] - xr[3 + i];
-                        term += (Real)a.Q[3 + i] * e * e;
-                    }
-                    J.add(term);
-                }
-                Real vs[3], kv[3], dpv[3], dvv[3];
+            for (int st = 0; st < 4; ++st) {
+                slot[st][lane].x = ws[0]; slot[st][lane].y = ws[1]; slot[st][lane].z = ws[2];
+                kw[0] = in.y - M.gx * ws[1] * ws[2];
+                kw[1] = in.z - M.gy * ws[2] * ws[0];
+                kw[2] = in.w - M.gz * ws[0] * ws[1];
+                if (st == 0) {
 #pragma unroll
-                for (int i = 0; i < 3; ++i) vs[i] = v[i];
-                // F/m times the thrust direction; the factor 2 of its first
-                // two components rides on F/m (exact: a power of two)
-                const Real fm2 = Real(2) * fm;
+                    for (int i = 0; i < 3; ++i) dw[i] = kw[i];
+                } else if (st < 3) {
 #pragma unroll
-                for (int st = 0; st < 4; ++st) {
-                    const R4 qq = qstage[st];
-                    const Real r3x = Real(2) * (qq.y * qq.w + qq.x * qq.z);
-                    const Real r3y = Real(2) * (qq.z * qq.w - qq.x * qq.y);
-                    const Real r3z = Real(1) - Real(2) * (qq.y * qq.y + qq.z * qq.z);
-                    kv[0] = fm2 * (qq.y * qq.w + qq.x * qq.z);
-                    kv[1] = fm2 * (qq.z * qq.w - qq.x * qq.y);
-                    kv[2] = fm * r3z - M.g;
-                    if (DRAG) {
-                        const Real qw = qq.x, qx = qq.y, qy = qq.z, qz = qq.w;
-                        const Real r11 = Real(1) - Real(2) * (qy * qy + qz * qz), r12 = Real(2) * (qx * qy - qw * qz);
-                        const Real r21 = Real(2) * (qx * qy + qw * qz), r22 = Real(1) - Real(2) * (qx * qx + qz * qz);
-                        const Real r31 = Real(2) * (qx * qz - qw * qy), r32 = Real(2) * (qy * qz + qw * qx);
-                        const Real b0 = M.d0 * (r11 * vs[0] + r21 * vs[1] + r31 * vs[2]);
-                        const Real b1 = M.d1 * (r12 * vs[0] + r22 * vs[1] + r32 * vs[2]);
-                        const Real b2 = M.d2 * (r3x * vs[0] + r3y * vs[1] + r3z * vs[2]);
-                        kv[0] -= r11 * b0 + r12 * b1 + r3x * b2;
-                        kv[1] -= r21 * b0 + r22 * b1 + r3y * b2;
-                        kv[2] -= r31 * b0 + r32 * b1 + r3z * b2;
-                    }
-                    if (st == 0) {
-#pragma unroll
-                        for (int i = 0; i < 3; ++i) { dpv[i] = vs[i]; dvv[i] = kv[i]; }
-                    } else if (st < 3) {
-#pragma unroll
-                        for (int i = 0; i < 3; ++i) { dpv[i] += Real(2) * vs[i]; dvv[i] += Real(2) * kv[i]; }
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < 3; ++i) { dpv[i] = dt6 * (dpv[i] + vs[i]); dvv[i] = dt6 * (dvv[i] + kv[i]); }
-                    }
-                    if (st < 3) {
-                        const Real hh = st < 2 ? h2 : dt;
-#pragma unroll
-                        for (int i = 0; i < 3; ++i) vs[i] = v[i] + hh * kv[i];
-                    }
-                }
-                if (POS) {
-                    R4 (*ps)[64] = s_p[(c - 3) & 1][j];
-                    R4 o;
-                    o.x = p[0]; o.y = p[1]; o.z = p[2]; o.w = Real(0);
-                    ps[0][lane] = o;
-                    o.x = dpv[0]; o.y = dpv[1]; o.z = dpv[2];
-                    ps[1][lane] = o;
-                }
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    p[i] += dpv[i];
-                    v[i] += dvv[i];
-                }
-            };
-            if (ke - kb == B) {
-                Real fpre[B];
-                R4 qpre[B][4];
-#pragma unroll
-                for (int j = 0; j < B; ++j) {
-                    fpre[j] = s_in[(c - 3) % 4][j][lane].x;
-#pragma unroll
-                    for (int st = 0; st < 4; ++st) qpre[j][st] = s_q[(c - 3) & 1][j][st][lane];
-                }
-                if (M.drag) {
-#pragma unroll
-                    for (int j = 0; j < B; ++j) trans_step(kb + j, j, fpre[j], qpre[j], std::true_type{});
+                    for (int i = 0; i < 3; ++i) dw[i] += Real(2) * kw[i];
                 } else {
 #pragma unroll
-                    for (int j = 0; j < B; ++j) trans_step(kb + j, j, fpre[j], qpre[j], std::false_type{});
+                    for (int i = 0; i < 3; ++i) dw[i] = dt6 * (dw[i] + kw[i]);
                 }
-            } else {
-                for (int k = kb; k < ke; ++k) {
-                    R4 qst[4];
+                if (st < 3) {
+                    const Real hh = st < 2 ? h2 : dt;
 #pragma unroll
-                    for (int st = 0; st < 4; ++st) qst[st] = s_q[(c - 3) & 1][k - kb][st][lane];
-                    if (M.drag) trans_step(k, k - kb, s_in[(c - 3) % 4][k - kb][lane].x, qst, std::true_type{});
-                    else trans_step(k, k - kb, s_in[(c - 3) % 4][k - kb][lane].x, qst, std::false_type{});
+                    for (int i = 0; i < 3; ++i) ws[i] = w[i] + hh * kw[i];
                 }
             }
-            if (POS && c == nch + 2) {
-                R4 o;
-                o.x = p[0]; o.y = p[1]; o.z = p[2]; o.w = Real(0);
-                s_pN[lane] = o;
-            }
+#pragma unroll
+            for (int i = 0; i < 3; ++i) w[i] += dw[i];
+            if (GATE) J.add(rate_limit(w[0], w[1], w[2]));
+        };
+        pipe_run<R4>(N, watch, counter(PC_RATE), [&](const int k, R4 &in) { in = s_in[k & (RI - 1)][lane]; }, omega_step);
+        if (GATE) {
+            s_jp[0][lane] = J.value();
+        } else {
+            // w_N, as the first stage of a step N
+            const PipeWatch last = {&s_cnt[lane & 1 ? PC_ATT : reader], RS};
+            last.wait<0>(N);
+            R4 *const o = s_w[N & (RS - 1)][0];
+            o[lane].x = w[0]; o[lane].y = w[1]; o[lane].z = w[2];
+            pipe_publish(counter(PC_RATE), N + 1);
         }
-        if (wave == 3 && c >= 4) {
-            // position costs and input-rate terms of chunk c - 4
-            const int kb = (c - 4) * B, ke = min(N, kb + B);
-            auto cost_step = [&](const int k, const int j, const R4 *pr) {
+    } else if (wave == 1) {
+        // attitude
+        Real q[4];
+        for (int i = 0; i < 4; ++i) q[i] = (Real)h.x0[6 + i];
+        struct In { R4 w[4]; };
+        const PipeWatch watch = {&s_cnt[lane == 0 ? PC_RATE : (TRACK && (lane & 1) ? PC_TERM : PC_POS)], lane == 0 ? 0 : RS};
+        auto quat_step = [&](const int k, const In &wst, In &) {
+            R4 (*slot)[64] = s_q[k & (RS - 1)];
+            Real qs[4], dq[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) qs[i] = q[i];
+#pragma unroll
+            for (int st = 0; st < 4; ++st) {
+                const R4 ws = wst.w[st];
+                // kq is twice the quaternion rate; the factor 1/2 is
+                // carried by the step sizes (exact: a power of two)
+                Real kq[4];
+                level<Real>();
+                kq[0] = -(qs[2] * ws.y);
+                kq[1] = qs[2] * ws.z;
+                kq[2] = -(qs[1] * ws.z);
+                kq[3] = qs[1] * ws.y;
+                level<Real>();
+                kq[0] = fma_t(-qs[1], ws.x, kq[0]);
+                kq[1] = fma_t(qs[0], ws.x, kq[1]);
+                kq[2] = fma_t(qs[0], ws.y, kq[2]);
+                kq[3] = fma_t(qs[0], ws.z, kq[3]);
+                level<Real>();
+                kq[0] = fma_t(-qs[3], ws.z, kq[0]);
+                kq[1] = fma_t(-qs[3], ws.y, kq[1]);
+                kq[2] = fma_t(qs[3], ws.x, kq[2]);
+                kq[3] = fma_t(-qs[2], ws.x, kq[3]);
+                level<Real>();
+                R4 o;
+                o.x = qs[0]; o.y = qs[1]; o.z = qs[2]; o.w = qs[3];
+                slot[st][lane] = o;
+                if (st < 3) {
+                    const Real hq = st < 2 ? h4 : h2;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) qs[i] = fma_t(hq, kq[i], q[i]);
+                }
+                level<Real>();
+                if (st == 0) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) dq[i] = kq[i];
+                } else if (st < 3) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) dq[i] = fma_t(Real(2), kq[i], dq[i]);
+                } else {
+                    // the last stage closes the step in one multiply-add
+                    // per component (this wave's recurrence sets the pace)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) dq[i] = dq[i] + kq[i];
+                    level<Real>();
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) q[i] = fma_t(dt12, dq[i], q[i]);
+                }
+            }
+            level<Real>();
+            renormalize(q);
+        };
+        pipe_run<In>(N, watch, counter(PC_ATT),
+                     [&](const int k, In &in) {
+#pragma unroll
+                         for (int st = 0; st < 4; ++st) in.w[st] = s_w[k & (RS - 1)][st][lane];
+                     },
+                     quat_step);
+        if (TRACK) {
+            R4 o;
+            o.x = q[0]; o.y = q[1]; o.z = q[2]; o.w = q[3];
+            s_pN[lane] = o;     // q_N, for the terminal term
+        }
+    } else if (wave == 2) {
+        // position and velocity
+        const Model<Real> M(a);
+        Real p[3], v[3];
+        for (int i = 0; i < 3; ++i) {
+            p[i] = (Real)h.x0[i];
+            v[i] = (Real)h.x0[3 + i];
+        }
+        struct In { Real fm; R4 q[4]; };
+        const PipeWatch watch = {&s_cnt[lane == 0 ? PC_ATT : PC_COST], lane == 0 ? 0 : RS};
+        // drag is a launch constant: the branch sits outside the step, so the
+        // stages of a step (independent without drag) schedule together
+        auto trans_step = [&](const int k, const In &in, auto drag_tag) {
+            constexpr bool DRAG = decltype(drag_tag)::value;
+            const Real fm = in.fm;
+            Real vs[3], kv[3], dpv[3], dvv[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) vs[i] = v[i];
+            // F/m times the thrust direction; the factor 2 of its first
+            // two components rides on F/m (exact: a power of two)
+            const Real fm2 = Real(2) * fm;
+#pragma unroll
+            for (int st = 0; st < 4; ++st) {
+                const R4 qq = in.q[st];
+                const Real r3z = Real(1) - Real(2) * (qq.y * qq.y + qq.z * qq.z);
+                kv[0] = fm2 * (qq.y * qq.w + qq.x * qq.z);
+                kv[1] = fm2 * (qq.z * qq.w - qq.x * qq.y);
+                kv[2] = fm * r3z - M.g;
+                if (DRAG) {
+                    const Real qw = qq.x, qx = qq.y, qy = qq.z, qz = qq.w;
+                    const Real r3x = Real(2) * (qq.y * qq.w + qq.x * qq.z);
+                    const Real r3y = Real(2) * (qq.z * qq.w - qq.x * qq.y);
+                    const Real r11 = Real(1) - Real(2) * (qy * qy + qz * qz), r12 = Real(2) * (qx * qy - qw * qz);
+                    const Real r21 = Real(2) * (qx * qy + qw * qz), r22 = Real(1) - Real(2) * (qx * qx + qz * qz);
+                    const Real r31 = Real(2) * (qx * qz - qw * qy), r32 = Real(2) * (qy * qz + qw * qx);
+                    const Real b0 = M.d0 * (r11 * vs[0] + r21 * vs[1] + r31 * vs[2]);
+                    const Real b1 = M.d1 * (r12 * vs[0] + r22 * vs[1] + r32 * vs[2]);
+                    const Real b2 = M.d2 * (r3x * vs[0] + r3y * vs[1] + r3z * vs[2]);
+                    kv[0] -= r11 * b0 + r12 * b1 + r3x * b2;
+                    kv[1] -= r21 * b0 + r22 * b1 + r3y * b2;
+                    kv[2] -= r31 * b0 + r32 * b1 + r3z * b2;
+                }
+                if (st == 0) {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) { dpv[i] = vs[i]; dvv[i] = kv[i]; }
+                } else if (st < 3) {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) { dpv[i] += Real(2) * vs[i]; dvv[i] += Real(2) * kv[i]; }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) { dpv[i] = dt6 * (dpv[i] + vs[i]); dvv[i] = dt6 * (dvv[i] + kv[i]); }
+                }
+                if (st < 3) {
+                    const Real hh = st < 2 ? h2 : dt;
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) vs[i] = v[i] + hh * kv[i];
+                }
+            }
+            R4 (*ps)[64] = s_p[k & (RS - 1)];
+            ps[0][lane].x = p[0]; ps[0][lane].y = p[1]; ps[0][lane].z = p[2];
+            const Real *const o2 = TRACK ? v : dpv;
+            ps[1][lane].x = o2[0]; ps[1][lane].y = o2[1]; ps[1][lane].z = o2[2];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                p[i] += dpv[i];
+                v[i] += dvv[i];
+            }
+        };
+        auto load = [&](const int k, In &in) {
+            in.fm = s_in[k & (RI - 1)][lane].x;
+#pragma unroll
+            for (int st = 0; st < 4; ++st) in.q[st] = s_q[k & (RS - 1)][st][lane];
+        };
+        if (M.drag)
+            pipe_run<In>(N, watch, counter(PC_POS), load,
+                         [&](const int k, const In &in, In &) { trans_step(k, in, std::true_type{}); });
+        else
+            pipe_run<In>(N, watch, counter(PC_POS), load,
+                         [&](const int k, const In &in, In &) { trans_step(k, in, std::false_type{}); });
+        if (GATE) {
+            R4 o;
+            o.x = p[0]; o.y = p[1]; o.z = p[2]; o.w = Real(0);
+            s_pN[lane] = o;
+        }
+        if (TRACK) {
+            // the terminal term of position and velocity closes the sum of its
+            // stage terms, which the cost wave keeps
+            s_t[0][0][lane].x = p[0]; s_t[0][0][lane].y = p[1]; s_t[0][0][lane].z = p[2];
+            s_t[0][1][lane].x = v[0]; s_t[0][1][lane].y = v[1]; s_t[0][1][lane].z = v[2];
+        }
+    } else if (wave == 3 && TRACK) {
+        // input-rate terms (J) and the tracking terms of position and velocity (J2)
+        KSum<Real> J2;
+        Real up[4];
+        for (int i = 0; i < 4; ++i) up[i] = (Real)h.u_prev[i];
+        Real rdt[4];
+        for (int i = 0; i < 4; ++i) rdt[i] = (Real)(a.R_dT[i] / (a.dt * a.dt));
+        struct In { R4 p, v, u; Real x[6]; };
+        const PipeWatch watch = {&s_cnt[PC_POS], 0};
+        pipe_run<In>(
+            N, watch, counter(PC_COST),
+            [&](const int k, In &in) {
+                in.p = s_p[k & (RS - 1)][0][lane];
+                in.v = s_p[k & (RS - 1)][1][lane];
+                in.u = s_u[k & (RI - 1)][lane];
+                const Real *xr = ref_row(k);
+#pragma unroll
+                for (int i = 0; i < 6; ++i) in.x[i] = xr[i];
+            },
+            [&](const int, const In &in, In &) {
+                const Real *xr = in.x;
+                const Real p[3] = {in.p.x, in.p.y, in.p.z}, v[3] = {in.v.x, in.v.y, in.v.z};
                 Real term = Real(0);
-                if (RATE) {
-                    const R4 u = s_u[(c - 4) % 5][j][lane];
-                    const Real d0 = u.x - up[0], d1 = u.y - up[1], d2 = u.z - up[2], d3 = u.w - up[3];
-                    term += rdt[0] * d0 * d0 + rdt[1] * d1 * d1 + rdt[2] * d2 * d2 + rdt[3] * d3 * d3;
-                    up[0] = u.x; up[1] = u.y; up[2] = u.z; up[3] = u.w;
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    const Real e = p[i] - xr[i];
+                    term += (Real)a.Q[i] * e * e;
                 }
-                if (HAS_V) {
-                    const Real V = s_v[(c - 4) % 5][j][lane];
-                    const Real dv = V - vp;
-                    term += r_dv * dv * dv;
-                    term -= (Real)a.mu * V;
-                    vp = V;
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    const Real e = v[i] - xr[3 + i];
+                    term += (Real)a.Q[3 + i] * e * e;
                 }
-                if (POS) {
-                    const R4 ph = pr[0];
-                    const Real pk[3] = {ph.x, ph.y, ph.z};
-                    if (OBJ == OBJ_GATE) {
-                        const R4 dp4 = pr[1];
-                        const Real dpv[3] = {dp4.x, dp4.y, dp4.z};
-                        const Real ax = pk[0] - gt.cx;
-                        const Real ay = pk[1] - gt.cy;
-                        const Real az = pk[2] - gt.cz;
-                        const Real bx = pk[0] - g0r.cx;
-                        const Real by = pk[1] - g0r.cy;
-                        const Real bz = pk[2] - g0r.cz;
-                        const Real d2 = bx * bx + by * by + bz * bz;
-                        if (d2 < r_near2) term += q_near * d2;
-                        if (nominal) s_f8[k] = (bx * g0r.nx + by * g0r.ny) < Real(0);
-                        term += dpv[0] * (Real(2) * ax + dpv[0]) + dpv[1] * (Real(2) * ay + dpv[1]) +
-                                dpv[2] * (Real(2) * az + dpv[2]);
-                        const Real sa = ax * gt.nx + ay * gt.ny;
-                        const Real sb = (ax + dpv[0]) * gt.nx + (ay + dpv[1]) * gt.ny;
-                        if (sa < Real(0) && sb >= Real(0)) {
-                            const Real t = sa / (sa - sb);
-                            const Real yx = ax + t * dpv[0], yy = ay + t * dpv[1], yz = az + t * dpv[2];
-                            const Real lat = yx * gt.hx + yy * gt.hy;
-                            const bool inside = fabs(lat) <= half && fabs(yz) <= half;
-                            const int jj = k + 1;
-                            const bool allowed = passes > 0 || ((h.allow[jj >> 5] >> (jj & 31)) & 1u);
-                            if (inside && allowed) {
-                                g = (g + 1 == a.G) ? 0 : g + 1;
-                                ++passes;
-                                gt.load(s_gtab, g);
-                            }
-                        }
-                    } else {
-                        const Real fl = floor(th_hi * inv_ds);
-                        const Real f = ((th_hi - fl * ds) + th_lo) * inv_ds;
-                        const int i = (fl >= Real(0) && fl < Real(1 << 30)) ? ((int)fl % a.P) : 0;
-                        const int i1 = (i + 1 == a.P) ? 0 : i + 1;
-                        const Real *A = path + 8 * i, *Bp = path + 8 * i1;
-                        const Real g1 = Real(1) - f;
-                        const Real px = g1 * A[0] + f * Bp[0], py = g1 * A[1] + f * Bp[1], pz = g1 * A[2] + f * Bp[2];
-                        Real tx = g1 * A[3] + f * Bp[3], ty = g1 * A[4] + f * Bp[4], tz = g1 * A[5] + f * Bp[5];
-                        const Real tn = inv_sqrt(tx * tx + ty * ty + tz * tz);
-                        tx *= tn; ty *= tn; tz *= tn;
-                        const Real ex = pk[0] - px;
-                        const Real ey = pk[1] - py;
-                        const Real ez = pk[2] - pz;
-                        const Real et = ex * tx + ey * ty + ez * tz;
-                        const Real lx = et * tx, ly = et * ty, lz = et * tz;
-                        const Real cxe = ex - lx, cye = ey - ly, cze = ez - lz;
-                        term += (Real)a.q_l * (lx * lx + ly * ly + lz * lz);
-                        term += (Real)a.q_c * (cxe * cxe + cye * cye + cze * cze);
-                        const Real vk = s_v[(c - 4) % 5][j][lane];
-                        const Real y = vk * dt + th_lo;
-                        const Real t = th_hi + y;
-                        th_lo = (sizeof(Real) == 4) ? y - (t - th_hi) : Real(0);
-                        th_hi = t;
-                        if (th_hi >= L) th_hi -= L;
+                J2.add(term);
+                const R4 u = in.u;
+                const Real d0 = u.x - up[0], d1 = u.y - up[1], d2 = u.z - up[2], d3 = u.w - up[3];
+                term = Real(0);
+                term += rdt[0] * d0 * d0 + rdt[1] * d1 * d1 + rdt[2] * d2 * d2 + rdt[3] * d3 * d3;
+                up[0] = u.x; up[1] = u.y; up[2] = u.z; up[3] = u.w;
+                J.add(term);
+            });
+        __syncthreads();
+        const Real *xr = ref_row(N);
+        const R4 pN = s_t[0][0][lane], vN = s_t[0][1][lane];
+        const Real p[3] = {pN.x, pN.y, pN.z}, v[3] = {vN.x, vN.y, vN.z};
+        Real term = 0;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const Real e = p[i] - xr[i];
+            term += (Real)a.QN[i] * e * e;
+            const Real f = v[i] - xr[3 + i];
+            term += (Real)a.QN[3 + i] * f * f;
+        }
+        J2.add(term);
+        s_jp[2][lane] = J2.value();
+    } else if (wave == 4 && TRACK) {
+        // tracking terms of the body rates with the rate limit (J), and of the attitude (J1)
+        KSum<Real> J1;
+        R4 w;
+        w.x = (Real)h.x0[10]; w.y = (Real)h.x0[11]; w.z = (Real)h.x0[12];
+        struct In { R4 q, w; Real x[7]; };
+        const PipeWatch watch = {&s_cnt[lane == 0 ? PC_RATE : PC_ATT], lane == 0 ? -1 : 0};
+        pipe_run<In>(
+            N, watch, counter(PC_TERM),
+            [&](const int k, In &in) {
+                in.q = s_q[k & (RS - 1)][0][lane];
+                in.w = s_w[(k + 1) & (RS - 1)][0][lane];
+                const Real *xr = ref_row(k);
+#pragma unroll
+                for (int i = 0; i < 7; ++i) in.x[i] = xr[6 + i];
+            },
+            [&](const int, const In &in, In &) {
+                const Real *xr = in.x;
+                const Real q[4] = {in.q.x, in.q.y, in.q.z, in.q.w}, ww[3] = {w.x, w.y, w.z};
+                Real term = Real(0);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    const Real e = ww[i] - xr[4 + i];
+                    term += (Real)a.Q[10 + i] * e * e;
+                }
+                J.add(term);
+                J.add(rate_limit(in.w.x, in.w.y, in.w.z));
+                term = Real(0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const Real e = q[i] - xr[i];
+                    term += (Real)a.Q[6 + i] * e * e;
+                }
+                J1.add(term);
+                w = in.w;
+            });
+        __syncthreads();
+        const Real *xr = ref_row(N);
+        const R4 qN = s_pN[lane];
+        const Real q[4] = {qN.x, qN.y, qN.z, qN.w}, ww[3] = {w.x, w.y, w.z};
+        Real term = 0;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const Real e = ww[i] - xr[10 + i];
+            term += (Real)a.QN[10 + i] * e * e;
+        }
+        J.add(term);
+        term = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const Real e = q[i] - xr[6 + i];
+            term += (Real)a.QN[6 + i] * e * e;
+        }
+        J1.add(term);
+        s_jp[0][lane] = J.value();
+        s_jp[1][lane] = J1.value();
+    } else if (wave == 4 && CONT) {
+        // path point and tangent of every step, and the terms of the inputs
+        Real up[4], vp = (Real)h.v_prev;
+        for (int i = 0; i < 4; ++i) up[i] = (Real)h.u_prev[i];
+        Real rdt[4];
+        for (int i = 0; i < 4; ++i) rdt[i] = (Real)(a.R_dT[i] / (a.dt * a.dt));
+        const Real r_dv = (Real)(a.r_dv / (a.dt * a.dt)), mu = (Real)a.mu;
+        const Real *path = (const Real *)a.path_r;
+        Real th_hi = (Real)h.theta0, th_lo = 0;
+        if (sizeof(Real) == 4) th_lo = (Real)(h.theta0 - (double)th_hi);
+        const Real L = (Real)a.path_len;
+        const Real ds = (Real)(a.path_len / (double)a.P), inv_ds = (Real)((double)a.P / a.path_len);
+        // u, V and the table rows around theta_k with its place between them
+        struct In { R4 u; Real V, f; R4 A0, A1, B0, B1; };
+        auto rows = [&](In &in) {
+            const Real fl = floor(th_hi * inv_ds);
+            in.f = ((th_hi - fl * ds) + th_lo) * inv_ds;
+            const int i = (fl >= Real(0) && fl < Real(1 << 30)) ? ((int)fl % a.P) : 0;
+            const int i1 = (i + 1 == a.P) ? 0 : i + 1;
+            const R4 *A = (const R4 *)(path + 8 * i), *B = (const R4 *)(path + 8 * i1);
+            in.A0 = A[0]; in.A1 = A[1]; in.B0 = B[0]; in.B1 = B[1];
+        };
+        const PipeWatch watch = {&s_cnt[lane < kDrawWaves ? PC_DRAW + lane : PC_COST], lane < kDrawWaves ? 0 : RS};
+        pipe_run<In>(
+            N, watch, counter(PC_TERM),
+            [&](const int k, In &in) {
+                in.u = s_u[k & (RI - 1)][lane];
+                in.V = s_v[k & (RI - 1)][lane];
+            },
+            [&](const int k, const In &in, In &nxt) {
+                const Real V = in.V;
+                {   // theta_{k+1}; its table rows are in flight while this step computes
+                    const Real y = V * dt + th_lo;
+                    const Real t = th_hi + y;
+                    th_lo = (sizeof(Real) == 4) ? y - (t - th_hi) : Real(0);
+                    th_hi = t;
+                    if (th_hi >= L) th_hi -= L;
+                    rows(nxt);
+                }
+                Real term = Real(0);
+                const R4 u = in.u;
+                const Real d0 = u.x - up[0], d1 = u.y - up[1], d2 = u.z - up[2], d3 = u.w - up[3];
+                term += rdt[0] * d0 * d0 + rdt[1] * d1 * d1 + rdt[2] * d2 * d2 + rdt[3] * d3 * d3;
+                up[0] = u.x; up[1] = u.y; up[2] = u.z; up[3] = u.w;
+                const Real dv = V - vp;
+                term += r_dv * dv * dv;
+                term -= mu * V;
+                vp = V;
+                const Real f = in.f, g1 = Real(1) - f;
+                const Real A[6] = {in.A0.x, in.A0.y, in.A0.z, in.A0.w, in.A1.x, in.A1.y};
+                const Real Bp[6] = {in.B0.x, in.B0.y, in.B0.z, in.B0.w, in.B1.x, in.B1.y};
+                const Real px = g1 * A[0] + f * Bp[0], py = g1 * A[1] + f * Bp[1], pz = g1 * A[2] + f * Bp[2];
+                Real tx = g1 * A[3] + f * Bp[3], ty = g1 * A[4] + f * Bp[4], tz = g1 * A[5] + f * Bp[5];
+                const Real tn = inv_sqrt(tx * tx + ty * ty + tz * tz);
+                tx *= tn; ty *= tn; tz *= tn;
+                R4 (*o)[64] = s_t[k & (RS - 1)];
+                R4 c;
+                c.x = px; c.y = py; c.z = pz; c.w = term;
+                o[0][lane] = c;
+                o[1][lane].x = tx; o[1][lane].y = ty; o[1][lane].z = tz;
+            },
+            rows);
+    } else if (CONT) {
+        // contouring errors (J), body-rate terms (J0)
+        KSum<Real> J0;
+        const Real q_l = (Real)a.q_l, q_c = (Real)a.q_c;
+        const Real qw0 = (Real)a.Q_w[0], qw1 = (Real)a.Q_w[1], qw2 = (Real)a.Q_w[2];
+        R4 w;
+        w.x = (Real)h.x0[10]; w.y = (Real)h.x0[11]; w.z = (Real)h.x0[12];
+        struct In { R4 p, c, t, w; };
+        const PipeWatch watch = {&s_cnt[lane == 0 ? PC_RATE : (lane & 1 ? PC_POS : PC_TERM)], lane == 0 ? -1 : 0};
+        pipe_run<In>(
+            N, watch, counter(PC_COST),
+            [&](const int k, In &in) {
+                in.p = s_p[k & (RS - 1)][0][lane];
+                in.c = s_t[k & (RS - 1)][0][lane];
+                in.t = s_t[k & (RS - 1)][1][lane];
+                in.w = s_w[(k + 1) & (RS - 1)][0][lane];
+            },
+            [&](const int, const In &in, In &) {
+                Real term = Real(0);
+                term += qw0 * w.x * w.x + qw1 * w.y * w.y + qw2 * w.z * w.z;
+                J0.add(term);
+                J0.add(rate_limit(in.w.x, in.w.y, in.w.z));
+                w = in.w;
+                term = in.c.w;
+                const Real tx = in.t.x, ty = in.t.y, tz = in.t.z;
+                const Real ex = in.p.x - in.c.x;
+                const Real ey = in.p.y - in.c.y;
+                const Real ez = in.p.z - in.c.z;
+                const Real et = ex * tx + ey * ty + ez * tz;
+                const Real lx = et * tx, ly = et * ty, lz = et * tz;
+                const Real cxe = ex - lx, cye = ey - ly, cze = ez - lz;
+                term += q_l * (lx * lx + ly * ly + lz * lz);
+                term += q_c * (cxe * cxe + cye * cye + cze * cze);
+                J.add(term);
+            });
+        __syncthreads();
+        s_jp[0][lane] = J0.value();
+        s_jp[1][lane] = Real(0);
+        s_jp[2][lane] = Real(0);
+    } else if (GATE) {
+        // gate progress, near-gate term, crossing and switch
+        const Real q_near = (Real)a.q_near, r_near2 = (Real)(a.r_near * a.r_near), half = (Real)a.gate_half;
+        GateRegs<Real> gt, g0r;
+        int g = h.g0, passes = 0;
+        gt.load(s_gtab, g);
+        g0r = gt;
+        struct In { R4 p, d; };
+        const PipeWatch watch = {&s_cnt[PC_POS], 0};
+        pipe_run<In>(
+            N, watch, counter(PC_COST),
+            [&](const int k, In &in) {
+                in.p = s_p[k & (RS - 1)][0][lane];
+                in.d = s_p[k & (RS - 1)][1][lane];
+            },
+            [&](const int k, const In &in, In &) {
+                Real term = Real(0);
+                const Real pk[3] = {in.p.x, in.p.y, in.p.z};
+                const Real dpv[3] = {in.d.x, in.d.y, in.d.z};
+                const Real ax = pk[0] - gt.cx;
+                const Real ay = pk[1] - gt.cy;
+                const Real az = pk[2] - gt.cz;
+                const Real bx = pk[0] - g0r.cx;
+                const Real by = pk[1] - g0r.cy;
+                const Real bz = pk[2] - g0r.cz;
+                const Real d2 = bx * bx + by * by + bz * bz;
+                if (d2 < r_near2) term += q_near * d2;
+                if (nominal) s_f8[k] = (bx * g0r.nx + by * g0r.ny) < Real(0);
+                term += dpv[0] * (Real(2) * ax + dpv[0]) + dpv[1] * (Real(2) * ay + dpv[1]) +
+                        dpv[2] * (Real(2) * az + dpv[2]);
+                const Real sa = ax * gt.nx + ay * gt.ny;
+                const Real sb = (ax + dpv[0]) * gt.nx + (ay + dpv[1]) * gt.ny;
+                if (sa < Real(0) && sb >= Real(0)) {
+                    const Real t = sa / (sa - sb);
+                    const Real yx = ax + t * dpv[0], yy = ay + t * dpv[1], yz = az + t * dpv[2];
+                    const Real lat = yx * gt.hx + yy * gt.hy;
+                    const bool inside = fabs(lat) <= half && fabs(yz) <= half;
+                    const int jj = k + 1;
+                    const bool allowed = passes > 0 || ((h.allow[jj >> 5] >> (jj & 31)) & 1u);
+                    if (inside && allowed) {
+                        g = (g + 1 == a.G) ? 0 : g + 1;
+                        ++passes;
+                        gt.load(s_gtab, g);
                     }
                 }
                 J.add(term);
-            };
-            if (ke - kb == B) {
-                R4 ppre[B][2];
-#pragma unroll
-                for (int j = 0; j < B; ++j)
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) ppre[j][i] = POS ? s_p[(c - 4) & 1][j][i][lane] : R4{};
-#pragma unroll
-                for (int j = 0; j < B; ++j) cost_step(kb + j, j, ppre[j]);
-            } else {
-                for (int k = kb; k < ke; ++k) {
-                    R4 pr[2];
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) pr[i] = POS ? s_p[(c - 4) & 1][k - kb][i][lane] : R4{};
-                    cost_step(k, k - kb, pr);
-                }
-            }
-        }
+            });
         __syncthreads();
-    }
-
-    // terminal tracking terms, on the wave that holds each part of x_N
-    if (OBJ == OBJ_TRACK && wave < 3) {
-        int r = i0 + N;
-        if (r > a.R - 1) r = a.R - 1;
-        const Real *xr = xref + 16 * r;
-        Real term = 0;
-        if (wave == 0) {
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const Real e = w[i] - xr[10 + i];
-                term += (Real)a.QN[10 + i] * e * e;
-            }
-        } else if (wave == 1) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const Real e = q[i] - xr[6 + i];
-                term += (Real)a.QN[6 + i] * e * e;
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const Real e = p[i] - xr[i];
-                term += (Real)a.QN[i] * e * e;
-                const Real f = v[i] - xr[3 + i];
-                term += (Real)a.QN[3 + i] * f * f;
-            }
+        if (nominal) {
+            const R4 ph = s_pN[lane];
+            const Real bx = ph.x - g0r.cx;
+            const Real by = ph.y - g0r.cy;
+            a.front8[N] = (bx * g0r.nx + by * g0r.ny) < Real(0);
         }
-        J.add(term);
+        // the tile of the nominal writes its front flags of steps 0..N-1
+        if (blk == (K >> 6))
+            for (int i = lane; i < N; i += 64) a.front8[i] = s_f8[i];
+        s_jp[1][lane] = Real(0);
+        s_jp[2][lane] = Real(0);
     }
-    if (wave < 3) s_jp[wave][lane] = J.value();
+    // (the cost waves meet the others at their own first barrier above)
+    if (!((wave == 3) || (wave == 4 && TRACK))) __syncthreads();
     __syncthreads();
     if (wave == 3) {
         Real Jfinal = Real(0);
         if (active) {
             Jfinal = ((s_jp[0][lane] + s_jp[1][lane]) + s_jp[2][lane]) + J.value();
-            if (OBJ == OBJ_GATE && nominal) {
-                const R4 ph = s_pN[lane];
-                const Real bx = ph.x - g0r.cx;
-                const Real by = ph.y - g0r.cy;
-                a.front8[N] = (bx * g0r.nx + by * g0r.ny) < Real(0);
-            }
             if (nominal) a.cur->J_nom = (double)Jfinal;
             else ((Real *)a.J)[m] = Jfinal;
         }
-        // the tile of the nominal writes its front flags of steps 0..N-1
-        if (OBJ == OBJ_GATE && blk == (K >> 6))
-            for (int i = lane; i < N; i += 64) a.front8[i] = s_f8[i];
         store_tile_min(Jfinal, active && !nominal && isfinite(Jfinal), a.tmin, blk);
     }
     __syncthreads();
 }
 
-template <int OBJ, typename Real, int B> __global__ __launch_bounds__(512) void k_rollout4(KArgs a)
+template <int OBJ, typename Real, int R>
+__global__ __launch_bounds__(64 * pipe_waves(OBJ, sizeof(Real))) void k_rollout4(KArgs a)
 {
     __shared__ HeadVals h;
     compute_head<OBJ == OBJ_CONTOUR>(a, h);
     if (blockIdx.x == 0 && threadIdx.x == 0) publish_head(a, h);
-    rollout4_body<OBJ, Real, B>(a, blockIdx.x, h);
+    rollout4_body<OBJ, Real, R>(a, blockIdx.x, h);
 }
 
 template <int OBJ, typename Real> __global__ __launch_bounds__(192) void k_rollout3(KArgs a)
@@ -2902,7 +3060,8 @@ template <int OBJ, typename Real> __global__ __launch_bounds__(192) void kb_roll
     }
 }
 
-template <int OBJ, typename Real, int B> __global__ __launch_bounds__(256) void kb_rollout4(BArgs b)
+template <int OBJ, typename Real, int R>
+__global__ __launch_bounds__(64 * pipe_waves(OBJ, sizeof(Real))) void kb_rollout4(BArgs b)
 {
     __shared__ KArgs s_a;
     __shared__ HeadVals h;
@@ -2921,7 +3080,7 @@ template <int OBJ, typename Real, int B> __global__ __launch_bounds__(256) void 
         const int blk = u - b.tile_prefix[item];
         compute_head<OBJ == OBJ_CONTOUR>(s_a, h);
         if (blk == 0 && threadIdx.x == 0) publish_head(s_a, h);
-        rollout4_body<OBJ, Real, B>(s_a, blk, h);
+        rollout4_body<OBJ, Real, R>(s_a, blk, h);
     }
 }
 
@@ -3015,12 +3174,12 @@ static hipError_t launch_batch_t(const BArgs &b, const BatchLaunch &L, hipStream
     if (L.draw) {
     } else if (L.rollout_waves == 4) {
         if constexpr (sizeof(Real) == 4) {
-            if (L.ring4_b == 4)
-                hipLaunchKernelGGL((kb_rollout4<OBJ, Real, 4>), dim3(L.rollout_groups), dim3(256), 0, st, b);
+            if (L.ring_steps == 8)
+                hipLaunchKernelGGL((kb_rollout4<OBJ, Real, 8>), dim3(L.rollout_groups), dim3(64 * pipe_waves(OBJ, sizeof(Real))), 0, st, b);
             else
-                hipLaunchKernelGGL((kb_rollout4<OBJ, Real, 2>), dim3(L.rollout_groups), dim3(256), 0, st, b);
+                hipLaunchKernelGGL((kb_rollout4<OBJ, Real, 4>), dim3(L.rollout_groups), dim3(64 * pipe_waves(OBJ, sizeof(Real))), 0, st, b);
         } else {
-            hipLaunchKernelGGL((kb_rollout4<OBJ, Real, 2>), dim3(L.rollout_groups), dim3(256), 0, st, b);
+            hipLaunchKernelGGL((kb_rollout4<OBJ, Real, 4>), dim3(L.rollout_groups), dim3(64 * pipe_waves(OBJ, sizeof(Real))), 0, st, b);
         }
     } else if (L.rollout_waves == 3)
         hipLaunchKernelGGL((kb_rollout3<OBJ, Real>), dim3(L.rollout_groups), dim3(192), 0, st, b);
@@ -3108,12 +3267,12 @@ static hipError_t launch_solve_t(const KArgs &a, bool acc64, hipStream_t st, hip
     const dim3 gt((a.K + 1 + 63) / 64);
     if (a.rollout_waves == 4) {
         if constexpr (sizeof(Real) == 4) {
-            if (a.ring4_b == 4)
-                hipLaunchKernelGGL((k_rollout4<OBJ, Real, 4>), gt, dim3(512), 0, st, a);
+            if (a.ring_steps == 8)
+                hipLaunchKernelGGL((k_rollout4<OBJ, Real, 8>), gt, dim3(64 * pipe_waves(OBJ, sizeof(Real))), 0, st, a);
             else
-                hipLaunchKernelGGL((k_rollout4<OBJ, Real, 2>), gt, dim3(256), 0, st, a);
+                hipLaunchKernelGGL((k_rollout4<OBJ, Real, 4>), gt, dim3(64 * pipe_waves(OBJ, sizeof(Real))), 0, st, a);
         } else {
-            hipLaunchKernelGGL((k_rollout4<OBJ, Real, 2>), gt, dim3(256), 0, st, a);
+            hipLaunchKernelGGL((k_rollout4<OBJ, Real, 4>), gt, dim3(64 * pipe_waves(OBJ, sizeof(Real))), 0, st, a);
         }
     } else if (a.rollout_waves == 3) {
         hipLaunchKernelGGL((k_rollout3<OBJ, Real>), gt, dim3(192), 0, st, a);

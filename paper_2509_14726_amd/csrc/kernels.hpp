@@ -26,7 +26,7 @@ struct BatchLaunch {
     int objective;
     bool fp64, acc64;
     int rollout_waves;    // 1..4 (see mppi_batch_cfg)
-    int ring4_b;          // four-wave chunk (binary32): 4, one workgroup per CU; 2, two
+    int ring_steps;       // rings of the pipeline (binary32): 8 steps, one workgroup per CU; 4, two
     bool draw;            // one-wave rollouts that draw their samples (binary32); with rollout_waves 4
                           // in the pipeline's arithmetic
     int rollout_groups;   // persistent rollout workgroups

@@ -289,13 +289,12 @@ static void plan_layout(mppi_ctx *c)
     const int K = c->K;
     a.n_tiles = (K + 1 + 63) / 64;
     // Rollout layout: with few 64-sample tiles the chip is latency bound and
-    // splitting each tile's step over four pipelined waves (sampling with body
-    // rates, attitude, translation, sampling with position costs), one per
-    // SIMD, shortens each step.  With chunks of 4 steps its LDS rings hold one
-    // such workgroup per CU; with chunks of 2 (binary32) two share a CU, which
-    // takes up to two tiles per CU in one round.  Beyond that one wave per 64
+    // splitting each tile's step over pipelined waves (draws, body rates,
+    // attitude, position, costs) shortens each step.  With rings of 8 steps
+    // the LDS holds one such workgroup per CU; with rings of 4 (binary32) two
+    // share a CU, which takes up to two tiles per CU in one round.  Beyond that one wave per 64
     // samples, which issues the fewest instructions, keeps the whole chip
-    // busy.  Binary64 rings (chunks of 2) fit one workgroup per CU, so from
+    // busy.  Binary64 rings (of 4) fit one workgroup per CU, so from
     // one to two tiles per CU the two-wave split (attitude | translation, two
     // workgroups per CU) takes over there.  Measured on 256 CUs for N = 50,
     // 100 and 200 at 129 to 1016 tiles.  The environment variable
@@ -311,7 +310,7 @@ static void plan_layout(mppi_ctx *c)
     if (const char *e = getenv("MPPI_ROLLOUT_WAVES")) {
         if (e[0] >= '1' && e[0] <= '4') a.rollout_waves = e[0] - '0';
     }
-    a.ring4_b = (!c->fp64 && a.n_tiles <= n_cu) ? 4 : 2;
+    a.ring_steps = (!c->fp64 && a.n_tiles <= n_cu) ? 8 : 4;
     // The one-wave rollout draws its samples itself (binary32) when the
     // sample tensor exceeds the 256 MiB last-level cache: the separate
     // sample pass then costs more than the draw adds to the rollout.  Below
@@ -1060,17 +1059,17 @@ static hipError_t resolve_cfg(mppi_batch *b)
                                        hipMemcpyHostToDevice);
         if (e != hipSuccess) return e;
     }
-    // four-wave chunk: the contexts' own when they all agree (a served solve
+    // ring size of the pipeline: the contexts' own when they all agree (a served solve
     // then runs exactly its stand-alone kernel), else by the batch's tiles
-    int ring = b->ctxs[0]->args.ring4_b;
+    int ring = b->ctxs[0]->args.ring_steps;
     for (const mppi_ctx *x : b->ctxs)
-        if (x->args.ring4_b != ring) ring = 0;
-    if (ring == 0) ring = (!b->fp64 && tiles <= cu) ? 4 : 2;
+        if (x->args.ring_steps != ring) ring = 0;
+    if (ring == 0) ring = (!b->fp64 && tiles <= cu) ? 8 : 4;
     // persistent rollout workgroups: what fits one CU times the CUs (one
-    // four-wave workgroup with 4-step chunks or in binary64, two with 2-step
-    // chunks in binary32, one three-wave, two two-wave, eight one-wave)
+    // pipelined workgroup with rings of 8 steps or in binary64, two with rings
+    // of 4 in binary32, one three-wave, two two-wave, eight one-wave)
     int per_cu = 8;
-    if (waves == 4) per_cu = (!b->fp64 && ring == 2) ? 2 : 1;
+    if (waves == 4) per_cu = (!b->fp64 && ring == 4) ? 2 : 1;
     else if (waves == 3) per_cu = 1;
     else if (waves == 2) per_cu = 2;
     int rg = c.rollout_groups > 0 ? c.rollout_groups : per_cu * cu;
@@ -1080,7 +1079,7 @@ static hipError_t resolve_cfg(mppi_batch *b)
         g.launch.fp64 = b->fp64;
         g.launch.acc64 = g.acc64;
         g.launch.rollout_waves = waves;
-        g.launch.ring4_b = ring;
+        g.launch.ring_steps = ring;
         // one-wave rollouts of thrust contexts draw their samples themselves
         // in binary32 (no sample pass); where a context takes rates, the
         // sample kernel draws for all
@@ -1553,7 +1552,7 @@ struct Slot {
 
 struct mppi_server {
     std::vector<mppi_ctx *> drones;
-    // Drones are grouped by rollout layout (waves, four-wave chunk) and
+    // Drones are grouped by rollout layout (waves, ring size) and
     // iterations per solve: a launch holds drones of one class only and runs
     // their own layout, so a served solve repeats the stand-alone solve bit
     // for bit and a one-wave class (the rate input) does not slow the others
@@ -1724,7 +1723,7 @@ mppi_status mppi_server_create(mppi_ctx *const *drones, int32_t n, const mppi_se
     s->cls.resize(n);
     s->local.resize(n);
     for (int i = 0; i < n; ++i) {
-        const int key = (8 * drones[i]->args.rollout_waves + drones[i]->args.ring4_b) * 128 + drones[i]->n_iter;
+        const int key = (16 * drones[i]->args.rollout_waves + drones[i]->args.ring_steps) * 128 + drones[i]->n_iter;
         int c = 0;
         while (c < (int)cls_key.size() && cls_key[c] != key) ++c;
         if (c == (int)cls_key.size()) {
