@@ -110,6 +110,10 @@ struct KArgs {
     // per-call
     const double *req;          // x0[13], t_now
     double *u0_out;             // 4 doubles or null
+    // host entry point: the report and the solution also go to pinned host
+    // memory (null: not wanted)
+    DevResult *res_host;
+    double *U_host;             // N x 4
 };
 
 // Per-solve scratch of one context, carved out of one block: the sample

@@ -2894,8 +2894,12 @@ __device__ __forceinline__ void final_body(const KArgs &a, int k)
     const bool ok = isfinite(jmin) && den > Acc(0);
     if (ok && tid < C) {
         const double uk = (double)(s_tot[tid] / den);
-        if (tid < 4) a.wU[4 * k + tid] = uk;
-        else a.wV[k] = uk;
+        if (tid < 4) {
+            a.wU[4 * k + tid] = uk;
+            if (a.U_host) a.U_host[4 * k + tid] = uk;
+        } else {
+            a.wV[k] = uk;
+        }
     }
     if (!HAS_V && ok && tid == 0) a.wV[k] = 0.0;
     if (!head) return;
@@ -2914,24 +2918,28 @@ __device__ __forceinline__ void final_body(const KArgs &a, int k)
         w->allow[tid] = 0xffffffffu;
     }
     // the report and the warm-start hand-over, one group of fields per lane
-    DevResult *r = a.res;
+    auto report = [&](DevResult *r) {
+        if (tid < 4) {
+            r->u0[tid] = ok ? (double)(s_tot[tid] / den) : (double)NAN;
+        } else if (tid == 4) {
+            r->J_min = (double)jmin;
+            r->S = (double)den;
+            r->S2 = (double)den2;
+            r->ess = ok ? (double)den * (double)den / (double)den2 : 0.0;
+        } else if (tid == 5) {
+            r->J_nom = rep_Jnom;
+            r->theta0 = rep_theta0;
+            r->status = ok ? ST_OK : ST_NONFINITE;
+            r->g0 = rep_g0;
+            r->i0 = rep_i0;
+            r->shift = rep_shift;
+            r->s = rep_s;
+        }
+    };
+    report(a.res);
+    if (a.res_host) report(a.res_host);
     if (tid < 4) {
-        const double u0 = ok ? (double)(s_tot[tid] / den) : (double)NAN;
-        r->u0[tid] = u0;
-        if (a.u0_out) a.u0_out[tid] = u0;
-    } else if (tid == 4) {
-        r->J_min = (double)jmin;
-        r->S = (double)den;
-        r->S2 = (double)den2;
-        r->ess = ok ? (double)den * (double)den / (double)den2 : 0.0;
-    } else if (tid == 5) {
-        r->J_nom = rep_Jnom;
-        r->theta0 = rep_theta0;
-        r->status = ok ? ST_OK : ST_NONFINITE;
-        r->g0 = rep_g0;
-        r->i0 = rep_i0;
-        r->shift = rep_shift;
-        r->s = rep_s;
+        if (a.u0_out) a.u0_out[tid] = ok ? (double)(s_tot[tid] / den) : (double)NAN;
     } else if (tid == 6 && ok) {
         w->warm = 1;
         w->g0 = rep_g0;
@@ -3220,6 +3228,21 @@ template <typename Real> static hipError_t launch_setup_t(const KArgs &a, hipStr
     if (a.R > n) n = a.R;
     if (n < 1) n = 1;
     hipLaunchKernelGGL(k_setup<Real>, dim3((n + 255) / 256), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
+struct Request { double v[kReqDoubles]; };
+
+__global__ __launch_bounds__(64) void k_request(Request r, double *d_req)
+{
+    if (threadIdx.x < kReqDoubles) d_req[threadIdx.x] = r.v[threadIdx.x];
+}
+
+hipError_t launch_request(const double *values, double *d_req, hipStream_t st)
+{
+    Request r;
+    for (int i = 0; i < kReqDoubles; ++i) r.v[i] = values[i];
+    hipLaunchKernelGGL(k_request, dim3(1), dim3(64), 0, st, r, d_req);
     return hipGetLastError();
 }
 

@@ -10,6 +10,9 @@ namespace mppi {
 // Convert the problem tables of a context to the device layout.
 hipError_t launch_setup(const KArgs &a, bool fp64, hipStream_t st);
 
+// Write a request record, passed as a kernel argument, to device memory.
+hipError_t launch_request(const double *values, double *d_req, hipStream_t st);
+
 // Enqueue one MPPI step: sample (with the head), rollout, average (+ tail).
 // acc64 selects binary64 accumulation of the weighted average.
 // When ev is non-null, ev[0..3] are recorded before the sample, rollout and
