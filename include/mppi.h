@@ -117,8 +117,11 @@ typedef struct {
      * [t_min, t_max] over the step; the contouring acceleration likewise to
      * dv_lim and to the range that keeps the progress speed within
      * [0, v_max].  The rate model runs the one-wave rollout with a separate
-     * sampling kernel; a batch holding such a context runs all its contexts
-     * with one-wave rollouts (a server launches each layout on its own). */
+     * sampling kernel; a context on its own with at most one 64-sample tile
+     * per CU runs a pipelined rollout whose results are those bit for bit
+     * (its report keeps rollout_waves 1).  A batch holding such a context runs
+     * all its contexts with one-wave rollouts (a server launches each layout
+     * on its own). */
     int32_t input_model;
     int32_t pad_;
     double rate_lim[2];   /* thrust-rate bounds, N/s (lower <= 0 <= upper)    */

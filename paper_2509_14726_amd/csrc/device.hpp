@@ -75,7 +75,7 @@ struct KArgs {
     int32_t inner;              // 1: an inner iteration of a control step (no shift, the first
                                 // iteration's last applied input)
     int32_t input_model;        // INPUT_THRUST (13 states) or INPUT_RATE (thrust rates, 17 states)
-    int32_t pad2_;
+    int32_t rate_pipe;          // 1: a rate solve on its own runs the pipelined rollout (the results of one wave)
     uint32_t seed_lo, seed_hi;
     // model
     double inv_mass, gravity, arm_s, c_tau;
@@ -115,6 +115,9 @@ struct KArgs {
     DevResult *res_host;
     double *U_host;             // N x 4
 };
+
+// Whether the rate input's pipelined rollout fits the LDS.
+constexpr bool rate_pipe_fits(int objective, size_t real) { return real == 4 || objective != OBJ_CONTOUR; }
 
 // Per-solve scratch of one context, carved out of one block: the sample
 // tensor, costs, tile minima and the nominal's front flags.  Offsets are

@@ -7,6 +7,7 @@
 //                    and translation, per-step costs fused in (gate Eq. (6)-(7),
 //                    tracking Eq. (8), contouring Eq. (9)); cost write and the
 //                    smallest cost of the tile
+//   k_rollout_rate   the pipeline for the rate input
 //   k_rollout3       three waves, chunks of steps between barriers
 //   k_sample +       (large K) noise and clipped samples for all (m, k), then
 //   k_rollout /      one sample per lane (k_rollout) or attitude and
@@ -1815,7 +1816,7 @@ __device__ __forceinline__ void rollout3_body(const KArgs &a, int blk, const Hea
 // Progress counters of the pipeline, one set per workgroup in LDS.  The
 // drawing waves publish the next step they will draw, the stages the number
 // of steps they have done.
-enum PipeCounter { PC_DRAW = 0, PC_RATE = 4, PC_ATT = 5, PC_POS = 6, PC_COST = 7, PC_TERM = 8, PC_N = 16 };
+enum PipeCounter { PC_DRAW = 0, PC_RATE = 4, PC_ATT = 5, PC_POS = 6, PC_COST = 7, PC_TERM = 8, PC_CHAIN = 9, PC_N = 16 };
 
 // What a wave waits for before it starts a step: each lane watches one
 // counter; step k may start once every lane's counter plus its offset is
@@ -2552,6 +2553,562 @@ __global__ __launch_bounds__(64 * pipe_waves(OBJ, sizeof(Real))) void k_rollout4
     rollout4_body<OBJ, Real, R>(a, blockIdx.x, h);
 }
 
+// ---------------------------------------------------------------- rollout, pipelined, rate input
+
+// The pipeline for the rate input (17 states), with the order of operations
+// of the one-wave rollout, so that its results are those bit for bit (a batch
+// steps rate contexts with one-wave rollouts).  One stage more than above:
+//   draws        the rates (and contouring's progress acceleration), clipped
+//                to their bounds;
+//   chain        the thrust chain in binary64: the clip to the range that
+//                keeps each thrust in [t_min, t_max], the sample tensor, the
+//                thrusts at the middle and the end of the step;
+//   rates, attitude, position as above, from the stage thrusts;
+//   terms        (contouring) the speed chain and its clip, the path point and
+//                tangent, the input terms;
+//   costs        all cost terms of a step, in the one-wave order.
+// A lone wave took 1.1 us a step (K = 8192, N = 20: 22 us behind a 5.6 us
+// sample pass); the stages overlap to about 0.3 us a step.  Calls through the
+// host entry point at K = 8192, N = 20: gate 49.5 -> 39.5 us, contouring 60.8
+// -> 45.4, tracking 52.7 -> 40.0; binary64 gate, K = 4001, N = 33: 72.8 -> 58.9.
+constexpr int rate_pipe_draws = 3;
+constexpr int rate_pipe_waves(int obj) { return (obj == OBJ_CONTOUR ? 6 : 5) + rate_pipe_draws; }
+
+template <int OBJ, typename Real, int R>
+__device__ __forceinline__ void rollout_rate_body(const KArgs &a, int blk, const HeadVals &h)
+{
+    typedef typename Vec4<Real>::T R4;
+    constexpr bool GATE = OBJ == OBJ_GATE, CONT = OBJ == OBJ_CONTOUR, TRACK = OBJ == OBJ_TRACK;
+    constexpr int RS = R, RI = 2 * R;
+    static_assert((R & (R - 1)) == 0, "slots are taken modulo a power of two");
+    constexpr int kDrawWaves = rate_pipe_draws;
+    constexpr int W_DRAW = CONT ? 6 : 5;
+    __shared__ R4 s_r[RI][64];                     // drawn rates within their bounds
+    __shared__ R4 s_T[RI][2][64];                  // thrusts at the middle and the end of the step
+    __shared__ R4 s_w[RS][4][64];                  // stage body rates
+    __shared__ R4 s_q[RS][4][64];                  // stage quaternions
+    __shared__ R4 s_p[RS][CONT ? 1 : 2][64];       // p_k and (gate) its increment, (tracking) v_k
+    __shared__ R4 s_u[GATE ? 1 : RI][64];          // clipped rates
+    __shared__ Real s_v[CONT ? RI : 1][64];        // drawn progress acceleration
+    __shared__ R4 s_t[CONT ? RS : 1][3][64];       // path point, tangent, input terms; acceleration, speed
+    __shared__ R4 s_us[kNMax];                     // shifted warm-start rates per step
+    __shared__ Real s_vs[CONT ? kNMax : 1];        // shifted warm-start acceleration
+    __shared__ R4 s_end[3][64];                    // p_N, v_N, q_N
+    __shared__ Real s_gtab[GATE ? 8 * kGMax : 1];  // the gate table, staged once
+    __shared__ uint8_t s_f8[GATE ? kNMax : 1];     // front flags of the nominal, steps 0..N-1
+    __shared__ int s_cnt[PC_N + 64];               // progress counters; then a word per lane that nothing reads
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int m = blk * 64 + lane;
+    const int K = a.K, N = a.N;
+    const bool active = m <= K;
+    const bool nominal = m == K;
+    const bool sampled = m < K;
+    const Real dt = (Real)a.dt;
+    const Real h2 = Real(0.5) * dt;
+    const Real dt6 = dt / Real(6);
+    const Real h4 = Real(0.5) * h2, dt12 = Real(0.5) * dt6;
+
+    if (GATE)
+        for (int i = threadIdx.x; i < 8 * a.G; i += blockDim.x) s_gtab[i] = ((const Real *)a.gates_r)[i];
+    for (int k = threadIdx.x; k < N; k += blockDim.x) {
+        int src = k + h.shift;
+        if (src > N - 1) src = N - 1;
+        R4 o;
+        o.x = h.warm ? (Real)a.wU[4 * src + 0] : (Real)a.hover;
+        o.y = h.warm ? (Real)a.wU[4 * src + 1] : (Real)a.hover;
+        o.z = h.warm ? (Real)a.wU[4 * src + 2] : (Real)a.hover;
+        o.w = h.warm ? (Real)a.wU[4 * src + 3] : (Real)a.hover;
+        s_us[k] = o;
+        if (CONT) s_vs[k] = h.warm ? (Real)a.wV[src] : Real(0);
+    }
+    if (threadIdx.x < PC_N) s_cnt[threadIdx.x] = (int)threadIdx.x < kDrawWaves ? (int)threadIdx.x : 0;
+    __syncthreads();
+
+    auto counter = [&](const int c) { return lane == 0 ? &s_cnt[c] : &s_cnt[PC_N + lane]; };
+    if (wave >= W_DRAW) {
+        const Real rlo = (Real)a.rate_lim[0], rhi = (Real)a.rate_lim[1];
+        const Real dlo = (Real)a.dv_lim[0], dhi = (Real)a.dv_lim[1];
+        const Real sig0 = sampled ? (Real)a.sigma[0] : Real(0), sig1 = sampled ? (Real)a.sigma[1] : Real(0);
+        const Real sig2 = sampled ? (Real)a.sigma[2] : Real(0), sig3 = sampled ? (Real)a.sigma[3] : Real(0);
+        const Real sigv = sampled ? (Real)a.sigma_v : Real(0);
+        const uint32_t s_solve = __builtin_amdgcn_readfirstlane(h.s);
+        const PipeWatch watch = {&s_cnt[CONT && (lane & 1) ? PC_TERM : PC_CHAIN], RI};
+        int *const mine = counter(PC_DRAW + wave - W_DRAW);
+        for (int k = wave - W_DRAW; k < N; k += kDrawWaves) {
+            const R4 us = s_us[k];
+            const Normal4<Real> z = normals4<Real>((uint32_t)m, (uint32_t)k, s_solve, 0u, a.seed_lo, a.seed_hi);
+            R4 u;
+            u.x = clamp_finite(us.x + sig0 * z.z0, rlo, rhi);
+            u.y = clamp_finite(us.y + sig1 * z.z1, rlo, rhi);
+            u.z = clamp_finite(us.z + sig2 * z.z2, rlo, rhi);
+            u.w = clamp_finite(us.w + sig3 * z.z3, rlo, rhi);
+            Real V = Real(0);
+            if (CONT) {
+                const Real zv = normal1<Real>((uint32_t)m, (uint32_t)k, s_solve, 1u, a.seed_lo, a.seed_hi);
+                V = clamp_finite(s_vs[k] + sigv * zv, dlo, dhi);
+            }
+            watch.wait<2>(k);
+            s_r[k & (RI - 1)][lane] = u;
+            if (CONT) s_v[k & (RI - 1)][lane] = V;
+            pipe_publish(mine, k + kDrawWaves);
+        }
+    } else if (wave == 4) {
+        // thrust chain, carried in binary64 in every precision (an
+        // integrator: in binary32 its rounding over the horizon reaches the
+        // attitude through the small inertia and the position through the attitude)
+        double T[4];
+        for (int i = 0; i < 4; ++i) T[i] = a.req[kReqThrust + i];
+        const double inv_dt = 1.0 / a.dt, hh = 0.5 * a.dt, ddt = a.dt;
+        const double t_min = a.t_min, t_max = a.t_max;
+        R4 *rec = (R4 *)a.ctrl + m;
+        const int reader = CONT ? PC_TERM : (TRACK ? PC_COST : PC_POS);
+        const PipeWatch watch = {&s_cnt[lane < kDrawWaves ? PC_DRAW + lane : (lane & 1 ? PC_POS : reader)],
+                                 lane < kDrawWaves ? 0 : RI};
+        pipe_run<R4>(
+            N, watch, counter(PC_CHAIN), [&](const int k, R4 &in) { in = s_r[k & (RI - 1)][lane]; },
+            [&](const int k, const R4 &in, R4 &) {
+                Real u[4] = {in.x, in.y, in.z, in.w}, tm[4], te[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    // the clip to the range that keeps the thrust within its
+                    // bounds over the step (multiplied by 1/dt: the bound can
+                    // differ from the quotient in the last binary64 place)
+                    u[i] = (Real)clamp_finite((double)u[i], (t_min - T[i]) * inv_dt, (t_max - T[i]) * inv_dt);
+                    const double ur = (double)u[i];
+                    tm[i] = (Real)(T[i] + hh * ur);
+                    T[i] += ddt * ur;
+                    te[i] = (Real)T[i];
+                }
+                R4 o;
+                o.x = tm[0]; o.y = tm[1]; o.z = tm[2]; o.w = tm[3];
+                s_T[k & (RI - 1)][0][lane] = o;
+                o.x = te[0]; o.y = te[1]; o.z = te[2]; o.w = te[3];
+                s_T[k & (RI - 1)][1][lane] = o;
+                o.x = u[0]; o.y = u[1]; o.z = u[2]; o.w = u[3];
+                if (!GATE) s_u[k & (RI - 1)][lane] = o;
+                if (sampled) store_nt(rec, o);
+                rec += K;
+            });
+    } else if (wave == 0) {
+        // body rates
+        const Model<Real> M(a);
+        Real w[3];
+        for (int i = 0; i < 3; ++i) w[i] = (Real)h.x0[10 + i];
+        const double *const T0 = a.req + kReqThrust;
+        StepInput<Real> in1 = step_input(M, (Real)T0[0], (Real)T0[1], (Real)T0[2], (Real)T0[3]);
+        struct In { R4 tm, te; };
+        const PipeWatch watch = {&s_cnt[lane == 0 ? PC_CHAIN : (lane & 1 ? PC_ATT : PC_COST)], lane == 0 ? 0 : RS};
+        pipe_run<In>(
+            N, watch, counter(PC_RATE),
+            [&](const int k, In &in) {
+                in.tm = s_T[k & (RI - 1)][0][lane];
+                in.te = s_T[k & (RI - 1)][1][lane];
+            },
+            [&](const int k, const In &in, In &) {
+                R4 (*slot)[64] = s_w[k & (RS - 1)];
+                const StepInput<Real> in2 = step_input(M, in.tm.x, in.tm.y, in.tm.z, in.tm.w);
+                const StepInput<Real> in4 = step_input(M, in.te.x, in.te.y, in.te.z, in.te.w);
+                Real ws[3], kw[3], dw[3];
+#pragma unroll
+                for (int i = 0; i < 3; ++i) ws[i] = w[i];
+#pragma unroll
+                for (int st = 0; st < 4; ++st) {
+                    const StepInput<Real> &si = st == 0 ? in1 : (st < 3 ? in2 : in4);
+                    slot[st][lane].x = ws[0]; slot[st][lane].y = ws[1]; slot[st][lane].z = ws[2];
+                    kw[0] = si.tx - M.gx * ws[1] * ws[2];
+                    kw[1] = si.ty - M.gy * ws[2] * ws[0];
+                    kw[2] = si.tz - M.gz * ws[0] * ws[1];
+                    if (st == 0) {
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) dw[i] = kw[i];
+                    } else if (st < 3) {
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) dw[i] += Real(2) * kw[i];
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) dw[i] = dt6 * (dw[i] + kw[i]);
+                    }
+                    if (st < 3) {
+                        const Real hs = st < 2 ? h2 : dt;
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) ws[i] = w[i] + hs * kw[i];
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < 3; ++i) w[i] += dw[i];
+                // the thrusts at the end of a step are those at the start of the next
+                in1 = in4;
+            });
+        // w_N, as the first stage of a step N
+        const PipeWatch last = {&s_cnt[lane & 1 ? PC_ATT : PC_COST], RS};
+        last.wait<0>(N);
+        R4 *const o = s_w[N & (RS - 1)][0];
+        o[lane].x = w[0]; o[lane].y = w[1]; o[lane].z = w[2];
+        pipe_publish(counter(PC_RATE), N + 1);
+    } else if (wave == 1) {
+        // attitude
+        Real q[4];
+        for (int i = 0; i < 4; ++i) q[i] = (Real)h.x0[6 + i];
+        struct In { R4 w[4]; };
+        const PipeWatch watch = {&s_cnt[lane == 0 ? PC_RATE : (TRACK && (lane & 1) ? PC_COST : PC_POS)], lane == 0 ? 0 : RS};
+        pipe_run<In>(
+            N, watch, counter(PC_ATT),
+            [&](const int k, In &in) {
+#pragma unroll
+                for (int st = 0; st < 4; ++st) in.w[st] = s_w[k & (RS - 1)][st][lane];
+            },
+            [&](const int k, const In &wst, In &) {
+                R4 (*slot)[64] = s_q[k & (RS - 1)];
+                Real qs[4], kq[4], dq[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) qs[i] = q[i];
+#pragma unroll
+                for (int st = 0; st < 4; ++st) {
+                    const R4 ws = wst.w[st];
+                    R4 o;
+                    o.x = qs[0]; o.y = qs[1]; o.z = qs[2]; o.w = qs[3];
+                    slot[st][lane] = o;
+                    // kq is twice the quaternion rate; the factor 1/2 is
+                    // carried by the step sizes (exact: a power of two)
+                    kq[0] = -qs[1] * ws.x - qs[2] * ws.y - qs[3] * ws.z;
+                    kq[1] = qs[0] * ws.x + qs[2] * ws.z - qs[3] * ws.y;
+                    kq[2] = qs[0] * ws.y - qs[1] * ws.z + qs[3] * ws.x;
+                    kq[3] = qs[0] * ws.z + qs[1] * ws.y - qs[2] * ws.x;
+                    if (st == 0) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) dq[i] = kq[i];
+                    } else if (st < 3) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) dq[i] += Real(2) * kq[i];
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            dq[i] = dt12 * (dq[i] + kq[i]);
+                            q[i] += dq[i];
+                        }
+                    }
+                    if (st < 3) {
+                        const Real hq = st < 2 ? h4 : h2;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) qs[i] = q[i] + hq * kq[i];
+                    }
+                }
+                renormalize(q);
+            });
+        if (TRACK) {
+            R4 o;
+            o.x = q[0]; o.y = q[1]; o.z = q[2]; o.w = q[3];
+            s_end[2][lane] = o;
+        }
+    } else if (wave == 2) {
+        // position and velocity
+        const Model<Real> M(a);
+        Real p[3], v[3];
+        for (int i = 0; i < 3; ++i) {
+            p[i] = (Real)h.x0[i];
+            v[i] = (Real)h.x0[3 + i];
+        }
+        const double *const T0 = a.req + kReqThrust;
+        Real fm1 = step_input(M, (Real)T0[0], (Real)T0[1], (Real)T0[2], (Real)T0[3]).fm;
+        struct In { R4 tm, te, q[4]; };
+        const PipeWatch watch = {&s_cnt[lane == 0 ? PC_ATT : PC_COST], lane == 0 ? 0 : RS};
+        auto pos_step = [&](const int k, const In &in, auto drag_tag) {
+            constexpr bool DRAG = decltype(drag_tag)::value;
+            const Real fm2 = step_input(M, in.tm.x, in.tm.y, in.tm.z, in.tm.w).fm;
+            const Real fm4 = step_input(M, in.te.x, in.te.y, in.te.z, in.te.w).fm;
+            Real vs[3], kv[3], dpv[3], dvv[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) vs[i] = v[i];
+#pragma unroll
+            for (int st = 0; st < 4; ++st) {
+                const Real q[4] = {in.q[st].x, in.q[st].y, in.q[st].z, in.q[st].w};
+                stage_accel<DRAG>(M, st == 0 ? fm1 : (st < 3 ? fm2 : fm4), q, vs, kv);
+                if (st == 0) {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) { dpv[i] = vs[i]; dvv[i] = kv[i]; }
+                } else if (st < 3) {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) { dpv[i] += Real(2) * vs[i]; dvv[i] += Real(2) * kv[i]; }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) { dpv[i] = dt6 * (dpv[i] + vs[i]); dvv[i] = dt6 * (dvv[i] + kv[i]); }
+                }
+                if (st < 3) {
+                    const Real hs = st < 2 ? h2 : dt;
+#pragma unroll
+                    for (int i = 0; i < 3; ++i) vs[i] = v[i] + hs * kv[i];
+                }
+            }
+            R4 (*ps)[64] = s_p[k & (RS - 1)];
+            ps[0][lane].x = p[0]; ps[0][lane].y = p[1]; ps[0][lane].z = p[2];
+            if (!CONT) {
+                const Real *const o2 = TRACK ? v : dpv;
+                ps[CONT ? 0 : 1][lane].x = o2[0]; ps[CONT ? 0 : 1][lane].y = o2[1]; ps[CONT ? 0 : 1][lane].z = o2[2];
+            }
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                p[i] += dpv[i];
+                v[i] += dvv[i];
+            }
+            fm1 = fm4;
+        };
+        auto load = [&](const int k, In &in) {
+            in.tm = s_T[k & (RI - 1)][0][lane];
+            in.te = s_T[k & (RI - 1)][1][lane];
+#pragma unroll
+            for (int st = 0; st < 4; ++st) in.q[st] = s_q[k & (RS - 1)][st][lane];
+        };
+        if (M.drag)
+            pipe_run<In>(N, watch, counter(PC_POS), load,
+                         [&](const int k, const In &in, In &) { pos_step(k, in, std::true_type{}); });
+        else
+            pipe_run<In>(N, watch, counter(PC_POS), load,
+                         [&](const int k, const In &in, In &) { pos_step(k, in, std::false_type{}); });
+        s_end[0][lane].x = p[0]; s_end[0][lane].y = p[1]; s_end[0][lane].z = p[2];
+        s_end[1][lane].x = v[0]; s_end[1][lane].y = v[1]; s_end[1][lane].z = v[2];
+    } else if (wave == 5 && CONT) {
+        // the speed chain (binary64, as the thrusts), the path point and
+        // tangent of every step, the input terms
+        double vs = h.v_prev;
+        const double inv_dt = 1.0 / a.dt, ddt = a.dt, hdt = 0.5 * a.dt, v_max = a.v_max;
+        const Real rd0 = (Real)a.R_dT[0], rd1 = (Real)a.R_dT[1], rd2 = (Real)a.R_dT[2], rd3 = (Real)a.R_dT[3];
+        const Real *path = (const Real *)a.path_r;
+        Real *vrec = (Real *)a.vctrl + m;
+        Real th_hi = (Real)h.theta0, th_lo = 0;
+        if (sizeof(Real) == 4) th_lo = (Real)(h.theta0 - (double)th_hi);
+        const Real L = (Real)a.path_len;
+        const Real ds = (Real)(a.path_len / (double)a.P), inv_ds = (Real)((double)a.P / a.path_len);
+        struct In { R4 u; Real V, f; R4 A0, A1, B0, B1; };
+        auto rows = [&](In &in) {
+            const Real fl = floor(th_hi * inv_ds);
+            in.f = ((th_hi - fl * ds) + th_lo) * inv_ds;
+            const int i = (fl >= Real(0) && fl < Real(1 << 30)) ? ((int)fl % a.P) : 0;
+            const int i1 = (i + 1 == a.P) ? 0 : i + 1;
+            const R4 *A = (const R4 *)(path + 8 * i), *B = (const R4 *)(path + 8 * i1);
+            in.A0 = A[0]; in.A1 = A[1]; in.B0 = B[0]; in.B1 = B[1];
+        };
+        const PipeWatch watch = {&s_cnt[lane < kDrawWaves ? PC_DRAW + lane : (lane & 1 ? PC_CHAIN : PC_COST)],
+                                 lane < kDrawWaves || (lane & 1) ? 0 : RS};
+        pipe_run<In>(
+            N, watch, counter(PC_TERM),
+            [&](const int k, In &in) {
+                in.u = s_u[k & (RI - 1)][lane];
+                in.V = s_v[k & (RI - 1)][lane];
+            },
+            [&](const int k, const In &in, In &nxt) {
+                const Real V = (Real)clamp_finite((double)in.V, (0.0 - vs) * inv_dt, (v_max - vs) * inv_dt);
+                const Real speed = (Real)vs;
+                {   // theta_{k+1}; its table rows are in flight while this step computes
+                    const double vsn = vs + ddt * (double)V;
+                    const Real adv = (Real)(hdt * (vs + vsn));
+                    vs = vsn;
+                    const Real y = adv + th_lo;
+                    const Real t = th_hi + y;
+                    th_lo = (sizeof(Real) == 4) ? y - (t - th_hi) : Real(0);
+                    th_hi = t;
+                    if (th_hi >= L) th_hi -= L;
+                    rows(nxt);
+                }
+                if (sampled) store_nt(vrec, V);
+                vrec += K;
+                const R4 u = in.u;
+                const Real ut = rd0 * u.x * u.x + rd1 * u.y * u.y + rd2 * u.z * u.z + rd3 * u.w * u.w;
+                const Real f = in.f, g1 = Real(1) - f;
+                const Real A[6] = {in.A0.x, in.A0.y, in.A0.z, in.A0.w, in.A1.x, in.A1.y};
+                const Real B[6] = {in.B0.x, in.B0.y, in.B0.z, in.B0.w, in.B1.x, in.B1.y};
+                const Real px = g1 * A[0] + f * B[0], py = g1 * A[1] + f * B[1], pz = g1 * A[2] + f * B[2];
+                Real tx = g1 * A[3] + f * B[3], ty = g1 * A[4] + f * B[4], tz = g1 * A[5] + f * B[5];
+                const Real tn = inv_sqrt(tx * tx + ty * ty + tz * tz);
+                tx *= tn; ty *= tn; tz *= tn;
+                R4 (*o)[64] = s_t[k & (RS - 1)];
+                R4 c;
+                c.x = px; c.y = py; c.z = pz; c.w = ut;
+                o[0][lane] = c;
+                c.x = tx; c.y = ty; c.z = tz; c.w = V;
+                o[1][lane] = c;
+                o[2][lane].x = speed;
+            },
+            rows);
+    } else {
+        // costs, all terms of a step in one sum
+        KSum<Real> J;
+        const Real w_max = (Real)a.w_max, w_lim = (Real)a.w_lim;
+        R4 w;
+        w.x = (Real)h.x0[10]; w.y = (Real)h.x0[11]; w.z = (Real)h.x0[12];
+        auto rate_limit = [&](Real &term, const R4 &wn) {
+            const Real ww[3] = {wn.x, wn.y, wn.z};
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const Real e = fmax(fabs(ww[i]) - w_max, Real(0));
+                term += w_lim * e * e;
+            }
+        };
+        GateRegs<Real> g0r;
+        if constexpr (GATE) {
+            const Real q_near = (Real)a.q_near, r_near2 = (Real)(a.r_near * a.r_near), half = (Real)a.gate_half;
+            GateRegs<Real> gt;
+            int g = h.g0, passes = 0;
+            gt.load(s_gtab, g);
+            g0r = gt;
+            struct In { R4 p, d, w; };
+            const PipeWatch watch = {&s_cnt[lane == 0 ? PC_RATE : PC_POS], lane == 0 ? -1 : 0};
+            pipe_run<In>(
+                N, watch, counter(PC_COST),
+                [&](const int k, In &in) {
+                    in.p = s_p[k & (RS - 1)][0][lane];
+                    in.d = s_p[k & (RS - 1)][CONT ? 0 : 1][lane];
+                    in.w = s_w[(k + 1) & (RS - 1)][0][lane];
+                },
+                [&](const int k, const In &in, In &) {
+                    Real term = Real(0);
+                    const Real dx[3] = {in.d.x, in.d.y, in.d.z};
+                    const Real ax = in.p.x - gt.cx;
+                    const Real ay = in.p.y - gt.cy;
+                    const Real az = in.p.z - gt.cz;
+                    const Real bx = in.p.x - g0r.cx;
+                    const Real by = in.p.y - g0r.cy;
+                    const Real bz = in.p.z - g0r.cz;
+                    const Real d2 = bx * bx + by * by + bz * bz;
+                    if (d2 < r_near2) term += q_near * d2;  // Eq. (7), current gate
+                    if (nominal) s_f8[k] = (bx * g0r.nx + by * g0r.ny) < Real(0);
+                    // |p_{k+1} - c|^2 - |p_k - c|^2 = dp . (2 (p_k - c) + dp)
+                    term += dx[0] * (Real(2) * ax + dx[0]) + dx[1] * (Real(2) * ay + dx[1]) +
+                            dx[2] * (Real(2) * az + dx[2]);
+                    const Real sa = ax * gt.nx + ay * gt.ny;
+                    const Real sb = (ax + dx[0]) * gt.nx + (ay + dx[1]) * gt.ny;
+                    if (sa < Real(0) && sb >= Real(0)) {
+                        const Real t = sa / (sa - sb);
+                        const Real yx = ax + t * dx[0], yy = ay + t * dx[1], yz = az + t * dx[2];
+                        const Real lat = yx * gt.hx + yy * gt.hy;
+                        const bool inside = fabs(lat) <= half && fabs(yz) <= half;
+                        const int j = k + 1;
+                        const bool allowed = passes > 0 || ((h.allow[j >> 5] >> (j & 31)) & 1u);
+                        if (inside && allowed) {
+                            g = (g + 1 == a.G) ? 0 : g + 1;
+                            ++passes;
+                            gt.load(s_gtab, g);
+                        }
+                    }
+                    rate_limit(term, in.w);
+                    J.add(term);
+                });
+        } else if constexpr (TRACK) {
+            const Real *xref = (const Real *)a.xref_r;
+            const int i0 = h.i0;
+            auto ref_row = [&](const int k) {
+                int r = i0 + k;
+                if (r > a.R - 1) r = a.R - 1;
+                return xref + 16 * r;
+            };
+            struct In { R4 p, v, q, w, u; Real x[13]; };
+            const PipeWatch watch = {&s_cnt[lane == 0 ? PC_RATE : PC_POS], lane == 0 ? -1 : 0};
+            pipe_run<In>(
+                N, watch, counter(PC_COST),
+                [&](const int k, In &in) {
+                    in.p = s_p[k & (RS - 1)][0][lane];
+                    in.v = s_p[k & (RS - 1)][CONT ? 0 : 1][lane];
+                    in.q = s_q[k & (RS - 1)][0][lane];
+                    in.w = s_w[(k + 1) & (RS - 1)][0][lane];
+                    in.u = s_u[k & (RI - 1)][lane];
+                    const Real *xr = ref_row(k);
+#pragma unroll
+                    for (int i = 0; i < 13; ++i) in.x[i] = xr[i];
+                },
+                [&](const int, const In &in, In &) {
+                    const Real x[13] = {in.p.x, in.p.y, in.p.z, in.v.x, in.v.y, in.v.z, in.q.x,
+                                        in.q.y, in.q.z, in.q.w, w.x,    w.y,    w.z};
+                    Real term = Real(0);
+#pragma unroll
+                    for (int i = 0; i < 13; ++i) {
+                        const Real e = x[i] - in.x[i];
+                        term += (Real)a.Q[i] * e * e;
+                    }
+                    const R4 u = in.u;
+                    term += (Real)a.R_dT[0] * u.x * u.x + (Real)a.R_dT[1] * u.y * u.y + (Real)a.R_dT[2] * u.z * u.z +
+                            (Real)a.R_dT[3] * u.w * u.w;
+                    rate_limit(term, in.w);
+                    J.add(term);
+                    w = in.w;
+                });
+        } else {
+            const Real q_l = (Real)a.q_l, q_c = (Real)a.q_c, r_dv = (Real)a.r_dv, mu = (Real)a.mu;
+            const Real qw0 = (Real)a.Q_w[0], qw1 = (Real)a.Q_w[1], qw2 = (Real)a.Q_w[2];
+            struct In { R4 p, c, t, w; Real vs; };
+            const PipeWatch watch = {&s_cnt[lane == 0 ? PC_RATE : (lane & 1 ? PC_POS : PC_TERM)], lane == 0 ? -1 : 0};
+            pipe_run<In>(
+                N, watch, counter(PC_COST),
+                [&](const int k, In &in) {
+                    in.p = s_p[k & (RS - 1)][0][lane];
+                    in.c = s_t[k & (RS - 1)][0][lane];
+                    in.t = s_t[k & (RS - 1)][1][lane];
+                    in.vs = s_t[k & (RS - 1)][2][lane].x;
+                    in.w = s_w[(k + 1) & (RS - 1)][0][lane];
+                },
+                [&](const int, const In &in, In &) {
+                    Real term = Real(0);
+                    const Real tx = in.t.x, ty = in.t.y, tz = in.t.z, V = in.t.w;
+                    const Real ex = in.p.x - in.c.x;
+                    const Real ey = in.p.y - in.c.y;
+                    const Real ez = in.p.z - in.c.z;
+                    const Real et = ex * tx + ey * ty + ez * tz;
+                    const Real lx = et * tx, ly = et * ty, lz = et * tz;
+                    const Real cxe = ex - lx, cye = ey - ly, cze = ez - lz;
+                    term += q_l * (lx * lx + ly * ly + lz * lz);
+                    term += q_c * (cxe * cxe + cye * cye + cze * cze);
+                    term += qw0 * w.x * w.x + qw1 * w.y * w.y + qw2 * w.z * w.z;
+                    term += r_dv * V * V;
+                    term += in.c.w;
+                    term -= mu * in.vs;
+                    rate_limit(term, in.w);
+                    J.add(term);
+                    w = in.w;
+                });
+        }
+        __syncthreads();
+        if (TRACK) {
+            int r = h.i0 + N;
+            if (r > a.R - 1) r = a.R - 1;
+            const Real *xr = (const Real *)a.xref_r + 16 * r;
+            const R4 pN = s_end[0][lane], vN = s_end[1][lane], qN = s_end[2][lane];
+            const Real x[13] = {pN.x, pN.y, pN.z, vN.x, vN.y, vN.z, qN.x, qN.y, qN.z, qN.w, w.x, w.y, w.z};
+            Real term = 0;
+#pragma unroll
+            for (int i = 0; i < 13; ++i) {
+                const Real e = x[i] - xr[i];
+                term += (Real)a.QN[i] * e * e;
+            }
+            J.add(term);
+        }
+        if (GATE && nominal) {
+            const R4 ph = s_end[0][lane];
+            const Real bx = ph.x - g0r.cx;
+            const Real by = ph.y - g0r.cy;
+            a.front8[N] = (bx * g0r.nx + by * g0r.ny) < Real(0);
+        }
+        if (GATE && blk == (K >> 6))
+            for (int i = lane; i < N; i += 64) a.front8[i] = s_f8[i];
+        Real Jfinal = Real(0);
+        if (active) {
+            Jfinal = J.value();
+            if (nominal) a.cur->J_nom = (double)Jfinal;
+            else ((Real *)a.J)[m] = Jfinal;
+        }
+        store_tile_min(Jfinal, active && !nominal && isfinite(Jfinal), a.tmin, blk);
+    }
+    if (wave != 3) __syncthreads();     // (the cost wave meets the others above)
+}
+
+template <int OBJ, typename Real, int R>
+__global__ __launch_bounds__(64 * rate_pipe_waves(OBJ)) void k_rollout_rate(KArgs a)
+{
+    __shared__ HeadVals h;
+    compute_head<OBJ == OBJ_CONTOUR>(a, h);
+    if (blockIdx.x == 0 && threadIdx.x == 0) publish_head(a, h);
+    rollout_rate_body<OBJ, Real, R>(a, blockIdx.x, h);
+}
+
 template <int OBJ, typename Real> __global__ __launch_bounds__(192) void k_rollout3(KArgs a)
 {
     __shared__ HeadVals h;
@@ -3283,12 +3840,17 @@ static hipError_t launch_solve_t(const KArgs &a, bool acc64, hipStream_t st, hip
     const bool draw = sizeof(Real) == 4 && a.rollout_draw;
     if (draw) {
         if constexpr (sizeof(Real) == 4) hipLaunchKernelGGL((k_head<Real, HAS_V>), dim3(1), dim3(256), 0, st, a);
-    } else if (a.rollout_waves < 3) {
+    } else if (a.rollout_waves < 3 && !a.rate_pipe) {
         hipLaunchKernelGGL((k_sample<Real, HAS_V>), gs, dim3(256), 0, st, a);
     }
     if (ev) (void)hipEventRecord(ev[1], st);
     const dim3 gt((a.K + 1 + 63) / 64);
-    if (a.rollout_waves == 4) {
+    if (a.rate_pipe) {
+        // (rings of 4 where 8 would not fit the LDS; binary64 contouring not at all)
+        constexpr int R = sizeof(Real) == 8 || OBJ == OBJ_CONTOUR ? 4 : 8;
+        if constexpr (rate_pipe_fits(OBJ, sizeof(Real)))
+            hipLaunchKernelGGL((k_rollout_rate<OBJ, Real, R>), gt, dim3(64 * rate_pipe_waves(OBJ)), 0, st, a);
+    } else if (a.rollout_waves == 4) {
         if constexpr (sizeof(Real) == 4) {
             if (a.ring_steps == 8)
                 hipLaunchKernelGGL((k_rollout4<OBJ, Real, 8>), gt, dim3(64 * pipe_waves(OBJ, sizeof(Real))), 0, st, a);

@@ -52,6 +52,7 @@ struct mppi_ctx {
     bool external_ws = false;   // per-solve scratch is lent by a server
     size_t ws_bytes = 0;        // size of that scratch
     int device = 0;             // device current at creation
+    int n_cu = 256;             // its compute units
     int n_iter = 1;             // MPPI iterations per solve
     bool no_tensor = false;     // the last solve's average drew the samples again
     std::string err;
@@ -306,6 +307,7 @@ static void plan_layout(mppi_ctx *c)
         (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
     c->device = dev;
     if (n_cu < 1) n_cu = 256;
+    c->n_cu = n_cu;
     if (a.n_tiles <= n_cu) a.rollout_waves = 4;
     else if (a.n_tiles <= 2 * n_cu) a.rollout_waves = c->fp64 ? 2 : 4;
     else a.rollout_waves = 1;
@@ -449,6 +451,13 @@ mppi_status mppi_create(const mppi_params *params, const mppi_quad *quad, const 
         // sampling kernel walks per sample: the one-wave rollout reads it
         a.rollout_waves = 1;
         a.rollout_draw = 0;
+        // With a CU per tile a solve on its own runs the pipelined rollout,
+        // which draws the samples and whose results are those of one wave per
+        // tile bit for bit; MPPI_ROLLOUT_WAVES=1 keeps it to one wave.  More
+        // tiles would queue behind each other (its rings fill a CU's LDS).
+        const char *e = getenv("MPPI_ROLLOUT_WAVES");
+        const bool one = e && e[0] == '1';
+        a.rate_pipe = !one && a.n_tiles <= c->n_cu && rate_pipe_fits(a.objective, c->fp64 ? 8 : 4) ? 1 : 0;
     }
 
     const size_t rs = c->fp64 ? sizeof(double) : sizeof(float);
@@ -654,7 +663,7 @@ mppi_status mppi_solve(mppi_ctx *ctx, const double x0[13], double t_now, double 
     // front of them; the sample and head kernels of the other layouts read it
     // from every block, so there a one-block kernel carries it to the device.
     // (K = 8192, N = 20: copies 42.8 us a call, kernel 39.1, pinned 37.9.)
-    if (a.rollout_waves >= 3) {
+    if (a.rollout_waves >= 3 || a.rate_pipe) {
         a.req = ctx->h_req;
     } else {
         HIP_TRY(ctx, launch_request(ctx->h_req, ctx->req, ctx->stream));

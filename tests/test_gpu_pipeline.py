@@ -45,6 +45,45 @@ def test_ring_sizes_give_the_same_bits(N, objective):
     assert np.array_equal(J[0], J[1][:130])
 
 
+@pytest.mark.parametrize("precision", [M.FP32, M.FP64], ids=["fp32", "fp64"])
+@pytest.mark.parametrize("objective", ["gate", "contour", "track"])
+@pytest.mark.parametrize("N", [1, 2, 3, 4, 7, 8, 9, 16, 17, 40])
+def test_rate_input_pipeline_equals_one_wave(N, objective, precision, monkeypatch):
+    """The rate input's pipelined rollout against its one-wave rollout (which
+    other tests hold against the oracle): costs, clipped samples, solution and
+    handed-on speed bit for bit over three warm solves, horizons around the
+    ring sizes, a ragged last tile, with and without drag."""
+    print("[gpu-case] rate pipeline", objective, "N", N, "fp64" if precision == M.FP64 else "fp32", flush=True)
+    sys.stdout.flush()
+    w = synth.single_solve_workload(K=200, N=N, objective=objective, seed=31 + N, track_seed=4, sigma=(8.0,) * 4,
+                                    sigma_v=5.0, input_model=M.INPUT_RATE, rate_lim=(-10.0, 10.0),
+                                    dv_lim=(-20.0, 20.0), **{"lambda": 20.0})
+    if N % 2:
+        w["quad"] = dict(w["quad"], drag=(0.3, 0.3, 0.15))
+    x0 = np.concatenate([w["x0"], np.full(4, synth.hover_thrust())])
+    out = []
+    for waves in (None, "1"):
+        if waves:
+            monkeypatch.setenv("MPPI_ROLLOUT_WAVES", waves)
+        else:
+            monkeypatch.delenv("MPPI_ROLLOUT_WAVES", raising=False)
+        sv = M.Solver(w["quad"], w["params"], gates=w["gates"], path=w.get("path"), path_len=w.get("path_len", 0.0),
+                      xref=w.get("xref"), ref_dt=w.get("ref_dt", 0.0), precision=precision)
+        x, got = x0.copy(), []
+        for step in range(3):
+            u0, U, info = sv.solve(x, step * 0.02)
+            J, Us = sv.read_samples(want_U=True)
+            wd = sv.get_warm()
+            got.append((u0, U, J, Us, info["J_min"], info["S"], info["J_nom"], info["rollout_waves"], np.array(wd.V),
+                        np.array(wd.allow), wd.vtheta, wd.theta0))
+            x = M.plant_step_rate(w["quad"], x, u0, 0.02, 2)
+        out.append(got)
+        sv.close()
+    for a, b in zip(*out):
+        for xa, xb in zip(a, b):
+            np.testing.assert_array_equal(xa, xb)
+
+
 def _check(K, N, objective, precision, drag):
     print("[gpu-case] pipeline", objective, "K", K, "N", N, "fp64" if precision == M.FP64 else "fp32", flush=True)
     sys.stdout.flush()
