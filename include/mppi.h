@@ -341,7 +341,9 @@ mppi_status mppi_read_profile(mppi_ctx *ctx, double mean_ms[3], int32_t *n_solve
  * context has the term (one unit per context and 64-sample tile), and a
  * grid-stride weighted-average kernel (one unit per context and horizon
  * step), repeated n_iter times (the contexts' shared n_iter), per group
- * of contexts sharing an objective and accumulation type.  Grids are fixed
+ * of contexts sharing an objective, accumulation type and input model.
+ * One-wave rollouts of binary32 contexts draw their samples themselves (no
+ * sample kernel).  Grids are fixed
  * and the work description lives in device memory, so the sequence is
  * captured once in a HIP graph (cfg.use_graph) and replayed for any subset.
  * Each context's result, report and warm-start state are the same as those

@@ -116,6 +116,10 @@ struct KArgs {
     double *U_host;             // N x 4
 };
 
+// Horizon steps of one block of the batched average: what two blocks' LDS
+// holds on a CU (binary32 sums: 72 KB, 68 KB contouring).
+constexpr int final_steps(bool has_v, size_t acc) { return acc == 8 ? 1 : (has_v ? 3 : 4); }
+
 // Whether the rate input's pipelined rollout fits the LDS.
 constexpr bool rate_pipe_fits(int objective, size_t real) { return real == 4 || objective != OBJ_CONTOUR; }
 
@@ -159,7 +163,7 @@ struct BatchDesc {
     int32_t n;                  // items
     int32_t n_sample_units;     // sum over items of ceil((K+1)/256)
     int32_t n_tiles;            // sum over items of ceil((K+1)/64)
-    int32_t n_steps;            // sum over items of N (units of the weighted-average kernel)
+    int32_t n_steps;            // units of the weighted-average kernel: sum over items of ceil(N / final_steps)
     uint32_t queue;             // rollout tile counter, reset by the sample kernel
     uint32_t sample_queue;      // sample unit counter (both also reset by the
                                 // average kernel, for the step's next iteration)

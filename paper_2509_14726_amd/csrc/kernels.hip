@@ -366,7 +366,7 @@ __device__ __forceinline__ void sample_body(const KArgs &a, int bx, int k0, int 
                 z[0] = n4.z0; z[1] = n4.z1; z[2] = n4.z2; z[3] = n4.z3;
             }
             Real u[4];
-            for (int i = 0; i < 4; ++i) u[i] = clampT(noisy ? ust[i] + sg[i] * z[i] : ust[i], rlo, rhi);
+            for (int i = 0; i < 4; ++i) u[i] = clamp_finite(noisy ? ust[i] + sg[i] * z[i] : ust[i], rlo, rhi);
             R4 o;
             o.x = u[0]; o.y = u[1]; o.z = u[2]; o.w = u[3];
             if (noisy) ((R4 *)a.ctrl)[(size_t)k * (size_t)K + (size_t)m] = o;
@@ -374,7 +374,7 @@ __device__ __forceinline__ void sample_body(const KArgs &a, int bx, int k0, int 
             if (HAS_V) {
                 Real zv = Real(0);
                 if (noisy) zv = normal1<Real>((uint32_t)m, (uint32_t)k, s, 1u, a.seed_lo, a.seed_hi);
-                const Real acc = clampT(noisy ? s_vs[k] + (Real)a.sigma_v * zv : s_vs[k], dlo, dhi);
+                const Real acc = clamp_finite(noisy ? s_vs[k] + (Real)a.sigma_v * zv : s_vs[k], dlo, dhi);
                 if (noisy) ((Real *)a.vctrl)[(size_t)k * (size_t)K + (size_t)m] = acc;
                 else ((Real *)a.nomV)[k] = acc;
             }
@@ -484,6 +484,11 @@ template <typename Real> __device__ __forceinline__ void in_vgpr(Model<Real> &M)
     M.gx = in_vgpr(M.gx); M.gy = in_vgpr(M.gy); M.gz = in_vgpr(M.gz);
 }
 
+template <int OBJ, typename Real, bool DRAW> struct DrawLds {
+    typename Vec4<Real>::T us[DRAW ? kNMax : 1];    // shifted warm-start inputs per step
+    Real vs[DRAW && OBJ == OBJ_CONTOUR ? kNMax : 1];
+};
+
 // One wave: samples 64*blk .. 64*blk+63 (sample K is the noise-free nominal).
 // DRAW: the wave draws its samples itself (the noise, perturbation and clip
 // of the sample kernel, same operations) and stores them for the weighted
@@ -493,14 +498,14 @@ template <typename Real> __device__ __forceinline__ void in_vgpr(Model<Real> &M)
 // the pipelined rollout, so that the results are those of k_rollout4 bit for
 // bit (for launches with more tiles than the pipeline holds at once).
 template <int OBJ, typename Real, bool DRAW, bool PIPE, bool RATE, bool DRAG, typename Head>
-__device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const Head &h)
+__device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const Head &h, DrawLds<OBJ, Real, DRAW> &lds)
 {
     typedef typename Vec4<Real>::T R4;
     constexpr bool GATE = OBJ == OBJ_GATE, CONT = OBJ == OBJ_CONTOUR, TRACK = OBJ == OBJ_TRACK;
     constexpr bool HAS_V = CONT;
-    static_assert(!(DRAW && RATE) && !(PIPE && RATE), "the rate input reads the sample kernel's rates");
-    __shared__ R4 s_us[DRAW ? kNMax : 1];
-    __shared__ Real s_vs[DRAW && HAS_V ? kNMax : 1];
+    static_assert(!(PIPE && RATE), "the rate input's order is the one-wave order");
+    auto &s_us = lds.us;
+    auto &s_vs = lds.vs;
     const int m = blk * 64 + (int)(threadIdx.x & 63);
     const int K = a.K, N = a.N;
     const bool active = m <= K;
@@ -550,30 +555,39 @@ __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const He
         if (HAS_V) vrow = nominal ? (const Real *)a.nomV : (const Real *)a.vctrl + m;
         const bool keep = DRAW && !a.regen && !nominal;
         const uint32_t s_solve = h.s, key0 = a.seed_lo, key1 = a.seed_hi;
-        const Real tmin = (Real)a.t_min, tmax = (Real)a.t_max, vmax = (Real)a.v_max;
+        const Real lo = (Real)(RATE ? a.rate_lim[0] : a.t_min), hi = (Real)(RATE ? a.rate_lim[1] : a.t_max);
+        const Real vlo = (Real)(RATE ? a.dv_lim[0] : 0.0), vhi = (Real)(RATE ? a.dv_lim[1] : a.v_max);
         // the nominal draws with zero noise, so that no step selects
         const Real sig0 = in_vgpr(nominal ? Real(0) : (Real)a.sigma[0]), sig1 = in_vgpr(nominal ? Real(0) : (Real)a.sigma[1]);
         const Real sig2 = in_vgpr(nominal ? Real(0) : (Real)a.sigma[2]), sig3 = in_vgpr(nominal ? Real(0) : (Real)a.sigma[3]);
         const Real sigv = in_vgpr(nominal ? Real(0) : (Real)a.sigma_v);
-        R4 *urec = (R4 *)a.ctrl + m;                // of the step's record, advanced step by step
+        R4 *rec = (R4 *)a.ctrl + m;                 // the sample's record, advanced step by step
         Real *vrec = HAS_V ? (Real *)a.vctrl + m : nullptr;
+        auto put = [&](const R4 &uo, const Real vo) {
+            if (DRAW) {
+                if (keep) {
+                    store_nt(rec, uo);
+                    if (HAS_V) store_nt(vrec, vo);
+                }
+            } else if (!nominal) {
+                *rec = uo;
+                if (HAS_V) *vrec = vo;
+            }
+            rec += K;
+            if (HAS_V) vrec += K;
+        };
         auto draw = [&](const int k, R4 &uo, Real &vo) {
             const R4 us = s_us[k];
             const Normal4<Real> z = normals4<Real>((uint32_t)m, (uint32_t)k, s_solve, 0u, key0, key1);
-            uo.x = clamp_finite(us.x + sig0 * z.z0, tmin, tmax);
-            uo.y = clamp_finite(us.y + sig1 * z.z1, tmin, tmax);
-            uo.z = clamp_finite(us.z + sig2 * z.z2, tmin, tmax);
-            uo.w = clamp_finite(us.w + sig3 * z.z3, tmin, tmax);
+            uo.x = clamp_finite(us.x + sig0 * z.z0, lo, hi);
+            uo.y = clamp_finite(us.y + sig1 * z.z1, lo, hi);
+            uo.z = clamp_finite(us.z + sig2 * z.z2, lo, hi);
+            uo.w = clamp_finite(us.w + sig3 * z.z3, lo, hi);
             if (HAS_V) {
                 const Real zv = normal1<Real>((uint32_t)m, (uint32_t)k, s_solve, 1u, key0, key1);
-                vo = clamp_finite(s_vs[k] + sigv * zv, Real(0), vmax);
+                vo = clamp_finite(s_vs[k] + sigv * zv, vlo, vhi);
             }
-            if (keep) {
-                store_nt(urec, uo);
-                if (HAS_V) store_nt(vrec, vo);
-            }
-            urec += K;
-            if (HAS_V) vrec += K;
+            if (!RATE) put(uo, vo);
         };
 
         // gate objective state
@@ -622,7 +636,7 @@ __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const He
         double vs = RATE ? h.v_prev : 0.0;
         // the rate input's range clips (multiplied by 1/dt: the bound can
         // differ from the quotient in the last binary64 place)
-        const double inv_dt = 1.0 / a.dt;
+        const double inv_dt = 1.0 / a.dt, t_min = a.t_min, t_max = a.t_max, v_max = a.v_max;
         R4 un;
         Real vn = Real(0);
         if (!DRAW) {
@@ -647,20 +661,15 @@ __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const He
                 // clip the drawn rates to the range that keeps each thrust of
                 // this sample's chain within [t_min, t_max] over the step (the
                 // progress acceleration: the speed within [0, v_max]); the
-                // clipped inputs replace the drawn ones for the average
-                u.x = (Real)clampT((double)u.x, (a.t_min - T[0]) * inv_dt, (a.t_max - T[0]) * inv_dt);
-                u.y = (Real)clampT((double)u.y, (a.t_min - T[1]) * inv_dt, (a.t_max - T[1]) * inv_dt);
-                u.z = (Real)clampT((double)u.z, (a.t_min - T[2]) * inv_dt, (a.t_max - T[2]) * inv_dt);
-                u.w = (Real)clampT((double)u.w, (a.t_min - T[3]) * inv_dt, (a.t_max - T[3]) * inv_dt);
-                if (HAS_V) V = (Real)clampT((double)V, (0.0 - vs) * inv_dt, (a.v_max - vs) * inv_dt);
-                if (nominal) {
-                    ((R4 *)a.nomU)[k] = u;
-                    if (HAS_V) ((Real *)a.nomV)[k] = V;
-                } else {
-                    ((R4 *)a.ctrl)[(size_t)k * (size_t)K + (size_t)m] = u;
-                    if (HAS_V) ((Real *)a.vctrl)[(size_t)k * (size_t)K + (size_t)m] = V;
-                }
+                // clipped inputs are what the average weighs.  (Minimum and
+                // maximum, not selects: those issue several times as slowly.)
+                u.x = (Real)clamp_finite((double)u.x, (t_min - T[0]) * inv_dt, (t_max - T[0]) * inv_dt);
+                u.y = (Real)clamp_finite((double)u.y, (t_min - T[1]) * inv_dt, (t_max - T[1]) * inv_dt);
+                u.z = (Real)clamp_finite((double)u.z, (t_min - T[2]) * inv_dt, (t_max - T[2]) * inv_dt);
+                u.w = (Real)clamp_finite((double)u.w, (t_min - T[3]) * inv_dt, (t_max - T[3]) * inv_dt);
+                if (HAS_V) V = (Real)clamp_finite((double)V, (0.0 - vs) * inv_dt, (v_max - vs) * inv_dt);
             }
+            if (RATE) put(u, V);
             Real term = Real(0);
 
             // ---- stage terms at state k
@@ -959,22 +968,25 @@ __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const He
     store_tile_min(Jfinal, active && !nominal && isfinite(Jfinal), a.tmin, blk);
 }
 
-// The variant of a launch: input model and drag are launch constants.
-template <int OBJ, typename Real, bool DRAW, bool PIPE = false, typename Head>
-__device__ __forceinline__ void rollout1_body(const KArgs &a, int blk, const Head &h)
+// Drag is a launch constant: the variant is chosen once.
+template <int OBJ, typename Real, bool DRAW, bool PIPE, bool RATE, typename Head>
+__device__ __forceinline__ void rollout1_body(const KArgs &a, int blk, const Head &h, DrawLds<OBJ, Real, DRAW> &lds)
 {
-    if (!DRAW && !PIPE && a.input_model == INPUT_RATE) {
-        if (a.has_drag) rollout1_steps<OBJ, Real, false, false, !DRAW && !PIPE, true>(a, blk, h);
-        else rollout1_steps<OBJ, Real, false, false, !DRAW && !PIPE, false>(a, blk, h);
-    } else {
-        if (a.has_drag) rollout1_steps<OBJ, Real, DRAW, PIPE, false, true>(a, blk, h);
-        else rollout1_steps<OBJ, Real, DRAW, PIPE, false, false>(a, blk, h);
-    }
+    if (a.has_drag) rollout1_steps<OBJ, Real, DRAW, PIPE, RATE, true>(a, blk, h, lds);
+    else rollout1_steps<OBJ, Real, DRAW, PIPE, RATE, false>(a, blk, h, lds);
 }
 
 template <int OBJ, typename Real, bool DRAW> __global__ __launch_bounds__(64) void k_rollout(KArgs a)
 {
-    rollout1_body<OBJ, Real, DRAW>(a, blockIdx.x, *(const DevCur *)a.cur);
+    __shared__ DrawLds<OBJ, Real, DRAW> lds;
+    const DevCur &h = *(const DevCur *)a.cur;
+    // (on its own a rate context reads the sample kernel's rates)
+    if constexpr (DRAW) {
+        rollout1_body<OBJ, Real, true, false, false>(a, blockIdx.x, h, lds);
+    } else {
+        if (a.input_model == INPUT_RATE) rollout1_body<OBJ, Real, false, false, true>(a, blockIdx.x, h, lds);
+        else rollout1_body<OBJ, Real, false, false, false>(a, blockIdx.x, h, lds);
+    }
 }
 
 // ---------------------------------------------------------------- rollout, two waves
@@ -3220,22 +3232,31 @@ __device__ __forceinline__ double wave_sum(double v)
 // above J_min) is neither read nor drawn: it adds nothing to any sum, so the
 // result is the same bit for bit.  With sharp weights (lambda = 1 at the
 // benchmark's noise) almost no sample is read: K = 262144, N = 200, binary64
-// sums: 157 -> 22 us; with all weights alive the samples of a round are
+// sums: 157 -> 48 us; with all weights alive the samples of a round are
 // still in flight while the previous round is summed.  Used wherever a thread
 // has several rounds of samples; with one round the samples are loaded at
 // once with the costs, which saves a round trip to memory.
 template <typename Real> constexpr Real kWeightCut = sizeof(Real) == 4 ? Real(105) : Real(750);
 
-template <typename Real, typename Acc, bool HAS_V, bool REGEN, int UR = 4, bool SKIP = false>
-__device__ __forceinline__ void final_body(const KArgs &a, int k)
+// S: horizon steps k .. k + S - 1 in one block.  The weights depend on the
+// costs only, so a block of several steps forms them once: batches, whose
+// average otherwise spends itself on them (256 uneven instances, lambda = 1:
+// 457 -> 218 us), give each block final_steps() of them.
+template <typename Acc, bool HAS_V, int S> struct FinalLds {
+    static constexpr int NV = S * (HAS_V ? 5 : 4) + 2;  // step s: values s C ..; then the two weight sums
+    Acc part[NV][kFinalThreads], tot[NV];
+};
+
+template <typename Real, typename Acc, bool HAS_V, bool REGEN, int UR = 4, bool SKIP = false, int S = 1>
+__device__ __forceinline__ void final_body(const KArgs &a, int k, FinalLds<Acc, HAS_V, S> &lds)
 {
     constexpr int C = HAS_V ? 5 : 4;
-    constexpr int NV = C + 2;
+    constexpr int NV = FinalLds<Acc, HAS_V, S>::NV;
     constexpr int NT = kFinalThreads, NWV = NT / 64;
     typedef typename Vec4<Real>::T R4;
-    static_assert(NV <= NWV, "one wave per reduced value");
-    __shared__ Acc s_part[NV][NT];
-    __shared__ Acc s_tot[NV];
+    static_assert(SKIP || S == 1, "several steps share the weights of a round");
+    auto &s_part = lds.part;
+    auto &s_tot = lds.tot;
 
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int K = a.K, N = a.N;
@@ -3248,26 +3269,30 @@ __device__ __forceinline__ void final_body(const KArgs &a, int k)
     const bool head = k == 0;
     const bool gate = a.objective == OBJ_GATE;
     // regenerated draws: the shifted warm start of step k and the noise key
-    R4 us{};
-    Real vs = Real(0);
+    const int ns = S == 1 ? 1 : min(S, N - k);
+    R4 us[S] = {};
+    Real vs[S] = {};
     uint32_t s_solve = 0;
     if (REGEN) {
-        us = ((const R4 *)a.nomU)[k];
-        if (HAS_V) vs = ((const Real *)a.nomV)[k];
+        for (int s = 0; s < S; ++s) {
+            if (s >= ns) break;
+            us[s] = ((const R4 *)a.nomU)[k + s];
+            if (HAS_V) vs[s] = ((const Real *)a.nomV)[k + s];
+        }
         s_solve = cur->s;
     }
     const Real tmin = (Real)a.t_min, tmax = (Real)a.t_max, vmax = (Real)a.v_max;
     const Real sig0 = (Real)a.sigma[0], sig1 = (Real)a.sigma[1], sig2 = (Real)a.sigma[2], sig3 = (Real)a.sigma[3];
     const Real sigv = (Real)a.sigma_v;
-    auto redraw = [&](const int m, R4 &u, Real &V) {
-        const Normal4<Real> z = normals4<Real>((uint32_t)m, (uint32_t)k, s_solve, 0u, a.seed_lo, a.seed_hi);
-        u.x = clamp_finite(us.x + sig0 * z.z0, tmin, tmax);
-        u.y = clamp_finite(us.y + sig1 * z.z1, tmin, tmax);
-        u.z = clamp_finite(us.z + sig2 * z.z2, tmin, tmax);
-        u.w = clamp_finite(us.w + sig3 * z.z3, tmin, tmax);
+    auto redraw = [&](const int m, const int st, R4 &u, Real &V) {
+        const Normal4<Real> z = normals4<Real>((uint32_t)m, (uint32_t)(k + st), s_solve, 0u, a.seed_lo, a.seed_hi);
+        u.x = clamp_finite(us[st].x + sig0 * z.z0, tmin, tmax);
+        u.y = clamp_finite(us[st].y + sig1 * z.z1, tmin, tmax);
+        u.z = clamp_finite(us[st].z + sig2 * z.z2, tmin, tmax);
+        u.w = clamp_finite(us[st].w + sig3 * z.z3, tmin, tmax);
         if (HAS_V) {
-            const Real zv = normal1<Real>((uint32_t)m, (uint32_t)k, s_solve, 1u, a.seed_lo, a.seed_hi);
-            V = clamp_finite(vs + sigv * zv, Real(0), vmax);
+            const Real zv = normal1<Real>((uint32_t)m, (uint32_t)(k + st), s_solve, 1u, a.seed_lo, a.seed_hi);
+            V = clamp_finite(vs[st] + sigv * zv, Real(0), vmax);
         }
     };
 
@@ -3328,32 +3353,10 @@ __device__ __forceinline__ void final_body(const KArgs &a, int k)
 #pragma unroll
     for (int i = 0; i < NV; ++i) v[i] = Acc(0);
     if constexpr (SKIP) {
-        // weights and samples of a round: the samples of the lanes that weigh
-        // something, the others 0
-        struct Round { Real w[UR], v[UR]; R4 u[UR]; bool any[UR]; };
-        auto fetch = [&](const int m0, const Real *Jr, Round &r) {
-#pragma unroll
-            for (int i = 0; i < UR; ++i) {
-                const int m = m0 + NT * i;
-                const Real arg = -(Jr[i] - jmin) * inv_lambda;
-                const bool live = isfinite(Jr[i]) && arg > -kWeightCut<Real>;
-                r.any[i] = __builtin_amdgcn_ballot_w64(live) != 0;
-                r.w[i] = Real(0);
-                r.u[i] = R4{};
-                r.v[i] = Real(0);
-                if (r.any[i]) {
-                    if (live) {
-                        if (REGEN) {
-                            redraw(m, r.u[i], r.v[i]);
-                        } else {
-                            r.u[i] = ctrl[m];
-                            if (HAS_V) r.v[i] = vctrl[m];
-                        }
-                        r.w[i] = exp(arg);
-                    }
-                }
-            }
-        };
+        // the weights of a round of samples; the samples of one step of it,
+        // of the lanes that weigh something (the others 0)
+        struct Weights { Real w[UR]; bool any[UR], live[UR]; };
+        struct Samples { R4 u[UR]; Real v[UR]; };
         auto costs = [&](const int m0, Real *Jr) {
 #pragma unroll
             for (int i = 0; i < UR; ++i) {
@@ -3362,35 +3365,81 @@ __device__ __forceinline__ void final_body(const KArgs &a, int k)
                 if (m < K) Jr[i] = J[m];
             }
         };
-        auto sum = [&](const Round &r) {
+        // which samples of a round weigh something; their weights are formed
+        // with the fetch of the first step, while its samples are on their way
+        auto sort_out = [&](const Real *Jr, Weights &r) {
+#pragma unroll
+            for (int i = 0; i < UR; ++i) {
+                r.w[i] = -(Jr[i] - jmin) * inv_lambda;
+                r.live[i] = isfinite(Jr[i]) && r.w[i] > -kWeightCut<Real>;
+                r.any[i] = __builtin_amdgcn_ballot_w64(r.live[i]) != 0;
+            }
+        };
+        auto fetch = [&](const int m0, const int st, Weights &r, Samples &x) {
+#pragma unroll
+            for (int i = 0; i < UR; ++i) {
+                const int m = m0 + NT * i;
+                const Real arg = r.w[i];
+                if (st == 0) r.w[i] = Real(0);
+                x.u[i] = R4{};
+                x.v[i] = Real(0);
+                if (r.any[i] && st < ns) {
+                    if (r.live[i]) {
+                        if (REGEN) {
+                            redraw(m, st, x.u[i], x.v[i]);
+                        } else {
+                            x.u[i] = ctrl[(size_t)st * (size_t)K + (size_t)m];
+                            if (HAS_V) x.v[i] = vctrl[(size_t)st * (size_t)K + (size_t)m];
+                        }
+                        if (st == 0) r.w[i] = exp(arg);
+                    }
+                }
+            }
+        };
+        auto sum = [&](const int st, const Weights &r, const Samples &x) {
 #pragma unroll
             for (int i = 0; i < UR; ++i) {
                 if (r.any[i]) {
                     const Acc wa = (Acc)r.w[i];
-                    v[0] += wa * (Acc)r.u[i].x;
-                    v[1] += wa * (Acc)r.u[i].y;
-                    v[2] += wa * (Acc)r.u[i].z;
-                    v[3] += wa * (Acc)r.u[i].w;
-                    if (HAS_V) v[4] += wa * (Acc)r.v[i];
-                    v[C] += wa;
-                    v[C + 1] += wa * wa;
+                    Acc *const vv = v + st * C;
+                    vv[0] += wa * (Acc)x.u[i].x;
+                    vv[1] += wa * (Acc)x.u[i].y;
+                    vv[2] += wa * (Acc)x.u[i].z;
+                    vv[3] += wa * (Acc)x.u[i].w;
+                    if (HAS_V) vv[C - 1] += wa * (Acc)x.v[i];
+                    if (st == 0) {
+                        v[S * C] += wa;
+                        v[S * C + 1] += wa * wa;
+                    }
                 }
             }
         };
-        // the costs two rounds ahead, the samples one round ahead of the sums
-        Round ra, rb;
+        // the costs two rounds ahead, the samples one step or round ahead of
+        // the sums; two rounds unrolled so that both buffers stay in registers
+        Weights wa, wb;
+        Samples x[2];
         Real Jb[UR];
         const int step = NT * UR;
         const int rounds = (K + step - 1) / step;   // the same for every thread
         costs(tid + step, Jb);
-        fetch(tid, Jm, ra);
+        sort_out(Jm, wa);
+        fetch(tid, 0, wa, x[0]);
         for (int r = 0; r < rounds; r += 2) {
-            costs(tid + (r + 2) * step, Jm);
-            fetch(tid + (r + 1) * step, Jb, rb);
-            sum(ra);
-            costs(tid + (r + 3) * step, Jb);
-            fetch(tid + (r + 2) * step, Jm, ra);
-            sum(rb);
+            const int m0 = tid + r * step, m1 = m0 + step, m2 = m1 + step;
+            costs(m2, Jm);
+#pragma unroll
+            for (int st = 0; st < S; ++st) {
+                if (st + 1 < S) fetch(m0, st + 1, wa, x[(st + 1) & 1]);
+                else { sort_out(Jb, wb); fetch(m1, 0, wb, x[S & 1]); }
+                sum(st, wa, x[st & 1]);
+            }
+            costs(m2 + step, Jb);
+#pragma unroll
+            for (int st = 0; st < S; ++st) {
+                if (st + 1 < S) fetch(m1, st + 1, wb, x[(S + st + 1) & 1]);
+                else { sort_out(Jm, wa); fetch(m2, 0, wa, x[0]); }
+                sum(st, wb, x[(S + st) & 1]);
+            }
         }
     } else
     for (int m0 = tid; m0 < K; m0 += NT * UR) {
@@ -3413,7 +3462,7 @@ __device__ __forceinline__ void final_body(const KArgs &a, int k)
 #pragma unroll
         for (int i = 0; i < UR; ++i) {
             if (m0 + NT * i < K) {
-                if (REGEN) redraw(m0 + NT * i, u[i], vm[i]);
+                if (REGEN) redraw(m0 + NT * i, 0, u[i], vm[i]);
                 const Real wr = isfinite(Jm[i]) ? exp(-(Jm[i] - jmin) * inv_lambda) : Real(0);
                 const Acc wa = (Acc)wr;
                 v[0] += wa * (Acc)u[i].x;
@@ -3439,26 +3488,27 @@ __device__ __forceinline__ void final_body(const KArgs &a, int k)
 #pragma unroll
     for (int i = 0; i < NV; ++i) s_part[i][tid] = v[i];
     __syncthreads();
-    if (wv < NV) {
-        Acc t = s_part[wv][lane];
+    for (int i = wv; i < NV; i += NWV) {
+        Acc t = s_part[i][lane];
 #pragma unroll
-        for (int j = 1; j < NWV; ++j) t += s_part[wv][64 * j + lane];
+        for (int j = 1; j < NWV; ++j) t += s_part[i][64 * j + lane];
         t = wave_sum(t);
-        if (lane == 0) s_tot[wv] = t;
+        if (lane == 0) s_tot[i] = t;
     }
     __syncthreads();
-    const Acc den = s_tot[C], den2 = s_tot[C + 1];
+    const Acc den = s_tot[S * C], den2 = s_tot[S * C + 1];
     const bool ok = isfinite(jmin) && den > Acc(0);
-    if (ok && tid < C) {
+    if (ok && tid < C * ns) {
         const double uk = (double)(s_tot[tid] / den);
-        if (tid < 4) {
-            a.wU[4 * k + tid] = uk;
-            if (a.U_host) a.U_host[4 * k + tid] = uk;
+        const int st = tid / C, c = tid % C;
+        if (c < 4) {
+            a.wU[4 * (k + st) + c] = uk;
+            if (a.U_host) a.U_host[4 * (k + st) + c] = uk;
         } else {
-            a.wV[k] = uk;
+            a.wV[k + st] = uk;
         }
     }
-    if (!HAS_V && ok && tid == 0) a.wV[k] = 0.0;
+    if (!HAS_V && ok && tid < ns) a.wV[k + tid] = 0.0;
     if (!head) return;
 
     // pass mask of the next solve: bit j = front flag of the nominal at step j
@@ -3514,7 +3564,8 @@ __device__ __forceinline__ void final_body(const KArgs &a, int k)
 template <typename Real, typename Acc, bool HAS_V, bool REGEN, int UR, bool SKIP>
 __global__ __launch_bounds__(kFinalThreads) void k_final(KArgs a)
 {
-    final_body<Real, Acc, HAS_V, REGEN, UR, SKIP>(a, blockIdx.x);
+    __shared__ FinalLds<Acc, HAS_V, 1> lds;
+    final_body<Real, Acc, HAS_V, REGEN, UR, SKIP>(a, blockIdx.x, lds);
 }
 
 // ---------------------------------------------------------------- batched (persistent)
@@ -3583,6 +3634,7 @@ template <typename Real, bool HAS_V> __global__ __launch_bounds__(256) void kb_s
 
 template <int OBJ, typename Real, int WAVES> __global__ __launch_bounds__(64 * WAVES) void kb_rollout(BArgs b)
 {
+    __shared__ DrawLds<OBJ, Real, false> lds;
     __shared__ KArgs s_a;
     __shared__ int s_ctx, s_unit;
     if (threadIdx.x == 0) s_ctx = -1;
@@ -3598,7 +3650,10 @@ template <int OBJ, typename Real, int WAVES> __global__ __launch_bounds__(64 * W
         stage_args(s_a, s_ctx, b, item);
         const int blk = u - b.tile_prefix[item];
         if (WAVES == 2) rollout2_body<OBJ, Real>(s_a, blk);
-        else rollout1_body<OBJ, Real, false>(s_a, blk, *(const DevCur *)s_a.cur);
+        else if (s_a.input_model == INPUT_RATE)
+            rollout1_body<OBJ, Real, false, false, true>(s_a, blk, *(const DevCur *)s_a.cur, lds);
+        else
+            rollout1_body<OBJ, Real, false, false, false>(s_a, blk, *(const DevCur *)s_a.cur, lds);
     }
 }
 
@@ -3649,12 +3704,19 @@ __global__ __launch_bounds__(64 * pipe_waves(OBJ, sizeof(Real))) void kb_rollout
     }
 }
 
-// One-wave rollouts that draw their samples (binary32, thrust input): no
+// One-wave rollouts that draw their samples (binary32): no
 // sample kernel.  PIPE: with the pipelined rollout's arithmetic, for launches
 // whose tiles fill the chip several times over: a tile then costs the issue
 // of one wave's operations instead of the pipeline's latency and handoffs.
-template <int OBJ, typename Real, bool PIPE> __global__ __launch_bounds__(64, 4) void kb_rollout_draw(BArgs b)
+// The contexts of a launch share the input model.
+// Two waves per SIMD with all their registers where the pipeline's sums or
+// the thrust chain need them (four waves spill: 64 served drones, half of them
+// on thrust rates, 694 -> 614 us), else four (half as many workgroups: 256
+// uneven instances 1281 -> 1427 us).
+template <int OBJ, typename Real, bool PIPE, bool RATE>
+__global__ __launch_bounds__(64, RATE || PIPE ? 2 : 4) void kb_rollout_draw(BArgs b)
 {
+    __shared__ DrawLds<OBJ, Real, true> lds;
     __shared__ KArgs s_a;
     __shared__ HeadVals h;
     __shared__ int s_ctx, s_unit;
@@ -3672,7 +3734,7 @@ template <int OBJ, typename Real, bool PIPE> __global__ __launch_bounds__(64, 4)
         const int blk = u - b.tile_prefix[item];
         compute_head<OBJ == OBJ_CONTOUR>(s_a, h);
         if (blk == 0 && threadIdx.x == 0) publish_head(s_a, h);
-        rollout1_body<OBJ, Real, true, PIPE>(s_a, blk, h);
+        rollout1_body<OBJ, Real, true, PIPE, RATE>(s_a, blk, h, lds);
     }
 }
 
@@ -3694,11 +3756,14 @@ template <typename Real, bool HAS_V> __global__ __launch_bounds__(64) void kb_ct
     }
 }
 
-// One unit per (item, step) of the weighted average.  The sample and rollout
+// One unit per (item, final_steps() steps) of the weighted average.  The sample and rollout
 // kernels of this step have finished, so their work queues are reset here
 // for the next iteration of the step.
 template <typename Real, typename Acc, bool HAS_V> __global__ __launch_bounds__(kFinalThreads) void kb_final(BArgs b)
 {
+    constexpr int S = final_steps(HAS_V, sizeof(Acc));
+    constexpr int UR = S > 1 ? 2 : 4;     // (four loads of four steps would not fit the registers)
+    __shared__ FinalLds<Acc, HAS_V, S> lds;
     __shared__ KArgs s_a;
     __shared__ int s_ctx;
     if (threadIdx.x == 0) s_ctx = -1;
@@ -3714,8 +3779,9 @@ template <typename Real, typename Acc, bool HAS_V> __global__ __launch_bounds__(
         item = advance_item(b.step_prefix, n, u, item);
         stage_args(s_a, s_ctx, b, item);
         // a context whose rollout left no sample tensor: draw the samples again
-        if (s_a.regen) final_body<Real, Acc, HAS_V, true, 4, true>(s_a, u - b.step_prefix[item]);
-        else final_body<Real, Acc, HAS_V, false, 4, true>(s_a, u - b.step_prefix[item]);
+        const int k = S * (u - b.step_prefix[item]);
+        if (s_a.regen) final_body<Real, Acc, HAS_V, true, UR, true, S>(s_a, k, lds);
+        else final_body<Real, Acc, HAS_V, false, UR, true, S>(s_a, k, lds);
         __syncthreads();
     }
 }
@@ -3727,9 +3793,11 @@ static hipError_t launch_batch_t(const BArgs &b, const BatchLaunch &L, hipStream
     if constexpr (sizeof(Real) == 4) {
         if (L.draw) {
             if (L.rollout_waves == 4)
-                hipLaunchKernelGGL((kb_rollout_draw<OBJ, Real, true>), dim3(L.draw_groups), dim3(64), 0, st, b);
+                hipLaunchKernelGGL((kb_rollout_draw<OBJ, Real, true, false>), dim3(L.draw_groups), dim3(64), 0, st, b);
+            else if (L.rate)
+                hipLaunchKernelGGL((kb_rollout_draw<OBJ, Real, false, true>), dim3(L.draw_groups), dim3(64), 0, st, b);
             else
-                hipLaunchKernelGGL((kb_rollout_draw<OBJ, Real, false>), dim3(L.draw_groups), dim3(64), 0, st, b);
+                hipLaunchKernelGGL((kb_rollout_draw<OBJ, Real, false, false>), dim3(L.draw_groups), dim3(64), 0, st, b);
         }
     }
     if (L.draw) {

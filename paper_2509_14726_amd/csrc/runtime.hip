@@ -988,7 +988,7 @@ namespace {
 
 struct BatchGroup {
     int objective = 0;
-    bool acc64 = false;
+    bool acc64 = false, rate = false;
     std::vector<int> regs;       // registered contexts of this group
     int cap = 0;                 // = regs.size()
     size_t bytes = 0;
@@ -1096,15 +1096,16 @@ static hipError_t resolve_cfg(mppi_batch *b)
         g.launch.objective = g.objective;
         g.launch.fp64 = b->fp64;
         g.launch.acc64 = g.acc64;
+        g.launch.rate = g.rate;
         g.launch.rollout_waves = waves;
         g.launch.ring_steps = ring;
-        // one-wave rollouts of thrust contexts draw their samples themselves
-        // in binary32 (no sample pass); where a context takes rates, the
-        // sample kernel draws for all
-        g.launch.draw = waves == 1 && !b->fp64 && !b->has_rate;
+        // one-wave rollouts draw their samples themselves in binary32 (no
+        // sample pass)
+        g.launch.draw = waves == 1 && !b->fp64;
         g.launch.rollout_groups = rg;
-        // one-wave workgroups, four per SIMD
-        g.launch.draw_groups = c.rollout_groups > 0 && waves == 1 ? c.rollout_groups : 16 * cu;
+        // one-wave workgroups: four per SIMD; two where the kernel is built for two
+        g.launch.draw_groups = c.rollout_groups > 0 && waves == 1 ? c.rollout_groups
+                                                                  : (waves == 4 || g.rate ? 8 : 16) * cu;
         g.launch.sample_groups = sg;
         // kFinalThreads-thread workgroups, two per CU
         g.launch.final_groups = 2 * b->n_cu;
@@ -1176,18 +1177,21 @@ mppi_status mppi_batch_create(mppi_ctx *const *ctxs, int32_t n, void *stream, co
         release_batch(b);
         return bfail(nullptr, MPPI_E_DEVICE, "hipEventCreate failed");
     }
-    // groups by (objective, accumulation type)
+    // groups by (objective, accumulation type, input model)
     b->group_of.resize(n);
     b->tiles_of.resize(n);
     for (int i = 0; i < n; ++i) {
         const mppi_ctx *c = ctxs[i];
         int gi = -1;
         for (size_t g = 0; g < b->groups.size(); ++g)
-            if (b->groups[g].objective == c->objective && b->groups[g].acc64 == c->acc64) gi = (int)g;
+            if (b->groups[g].objective == c->objective && b->groups[g].acc64 == c->acc64 &&
+                b->groups[g].rate == (c->args.input_model == INPUT_RATE))
+                gi = (int)g;
         if (gi < 0) {
             b->groups.emplace_back();
             b->groups.back().objective = c->objective;
             b->groups.back().acc64 = c->acc64;
+            b->groups.back().rate = c->args.input_model == INPUT_RATE;
             gi = (int)b->groups.size() - 1;
         }
         b->groups[gi].regs.push_back(i);
@@ -1331,6 +1335,7 @@ static mppi_status batch_solve(mppi_batch *b, const int32_t *active, int32_t n_a
         int32_t *tp = (int32_t *)(h + ((const char *)g.bargs.tile_prefix - d));
         int32_t *ap = (int32_t *)(h + ((const char *)g.bargs.step_prefix - d));
         int64_t s_units = 0, t_units = 0, a_units = 0;
+        const int per_block = final_steps(g.objective == OBJ_CONTOUR, g.acc64 || b->fp64 ? 8 : 4);
         sp[0] = tp[0] = ap[0] = 0;
         for (size_t j = 0; j < lst.size(); ++j) {
             const mppi_ctx *c = b->ctxs[lst[j].first];
@@ -1341,7 +1346,7 @@ static mppi_status batch_solve(mppi_batch *b, const int32_t *active, int32_t n_a
             items[j].ws = ws ? ws[lst[j].second] : nullptr;
             s_units += (c->K + 1 + 255) / 256;
             t_units += (c->K + 1 + 63) / 64;
-            a_units += c->N;
+            a_units += (c->N + per_block - 1) / per_block;
             if (s_units > INT32_MAX || a_units > INT32_MAX) return bfail(b, MPPI_E_INVAL, "batch too large");
             sp[j + 1] = (int32_t)s_units;
             tp[j + 1] = (int32_t)t_units;
