@@ -497,7 +497,8 @@ template <int OBJ, typename Real, bool DRAW> struct DrawLds {
 // stored.  PIPE: the costs are summed and the attitude step is closed as in
 // the pipelined rollout, so that the results are those of k_rollout4 bit for
 // bit (for launches with more tiles than the pipeline holds at once).
-template <int OBJ, typename Real, bool DRAW, bool PIPE, bool RATE, bool DRAG, typename Head>
+// NOM: the tile holds the nominal alone (K a multiple of 64) and draws nothing.
+template <int OBJ, typename Real, bool DRAW, bool PIPE, bool RATE, bool DRAG, bool NOM, typename Head>
 __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const Head &h, DrawLds<OBJ, Real, DRAW> &lds)
 {
     typedef typename Vec4<Real>::T R4;
@@ -578,13 +579,14 @@ __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const He
         };
         auto draw = [&](const int k, R4 &uo, Real &vo) {
             const R4 us = s_us[k];
-            const Normal4<Real> z = normals4<Real>((uint32_t)m, (uint32_t)k, s_solve, 0u, key0, key1);
+            Normal4<Real> z = {};
+            if (!NOM) z = normals4<Real>((uint32_t)m, (uint32_t)k, s_solve, 0u, key0, key1);
             uo.x = clamp_finite(us.x + sig0 * z.z0, lo, hi);
             uo.y = clamp_finite(us.y + sig1 * z.z1, lo, hi);
             uo.z = clamp_finite(us.z + sig2 * z.z2, lo, hi);
             uo.w = clamp_finite(us.w + sig3 * z.z3, lo, hi);
             if (HAS_V) {
-                const Real zv = normal1<Real>((uint32_t)m, (uint32_t)k, s_solve, 1u, key0, key1);
+                const Real zv = NOM ? Real(0) : normal1<Real>((uint32_t)m, (uint32_t)k, s_solve, 1u, key0, key1);
                 vo = clamp_finite(s_vs[k] + sigv * zv, vlo, vhi);
             }
             if (!RATE) put(uo, vo);
@@ -968,12 +970,22 @@ __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const He
     store_tile_min(Jfinal, active && !nominal && isfinite(Jfinal), a.tmin, blk);
 }
 
-// Drag is a launch constant: the variant is chosen once.
+// Drag is a launch constant: the variant is chosen once.  A last tile that
+// holds the nominal alone skips the draws: where K fills the chip's waves to
+// the last lane it runs after them, alone (K = 262144, N = 200: 523 -> 454 us
+// a solve).
 template <int OBJ, typename Real, bool DRAW, bool PIPE, bool RATE, typename Head>
 __device__ __forceinline__ void rollout1_body(const KArgs &a, int blk, const Head &h, DrawLds<OBJ, Real, DRAW> &lds)
 {
-    if (a.has_drag) rollout1_steps<OBJ, Real, DRAW, PIPE, RATE, true>(a, blk, h, lds);
-    else rollout1_steps<OBJ, Real, DRAW, PIPE, RATE, false>(a, blk, h, lds);
+    const bool nom = DRAW && !RATE && blk * 64 == a.K;
+    constexpr bool NOM = DRAW && !RATE;
+    if (a.has_drag) {
+        if (nom) rollout1_steps<OBJ, Real, DRAW, PIPE, RATE, true, NOM>(a, blk, h, lds);
+        else rollout1_steps<OBJ, Real, DRAW, PIPE, RATE, true, false>(a, blk, h, lds);
+    } else {
+        if (nom) rollout1_steps<OBJ, Real, DRAW, PIPE, RATE, false, NOM>(a, blk, h, lds);
+        else rollout1_steps<OBJ, Real, DRAW, PIPE, RATE, false, false>(a, blk, h, lds);
+    }
 }
 
 template <int OBJ, typename Real, bool DRAW> __global__ __launch_bounds__(64) void k_rollout(KArgs a)

@@ -7,6 +7,7 @@ for bit, since every layout keeps its arithmetic and its order of additions.
   rounds of its threads, sharp weights (most samples are skipped) and spread;
 * a step with more tiles than two pipelines per CU, whose pipelined contexts
   run one-wave rollouts in the pipeline's arithmetic;
+* a last tile that holds the nominal alone (K a multiple of 64);
 * rate-input contexts, which draw their samples in the rollout.
 """
 import sys
@@ -108,3 +109,28 @@ def test_rate_contexts(mixed, precision, monkeypatch):
     ws = [workload(i, K, N, ("gate", "contour", "track")[i % 3], not (mixed and i % 2), 20.0,
                    ctrl_cost=0.1 if i == 2 else 0.0) for i, (K, N) in enumerate(SHAPES)]
     check_batch(ws, precision, 1, not mixed, "rate mixed %d" % mixed)
+
+
+@pytest.mark.parametrize("objective", ["gate", "contour", "track"])
+@pytest.mark.parametrize("K,N", [(64, 1), (128, 7), (1024, 50)])
+def test_nominal_alone_in_its_tile(K, N, objective, monkeypatch):
+    """One-wave rollouts that draw against those that read the sample kernel's
+    samples."""
+    monkeypatch.setenv("MPPI_ROLLOUT_WAVES", "1")
+    print("[gpu-case] nominal tile", objective, "K", K, "N", N, flush=True)
+    sys.stdout.flush()
+    out = []
+    for draw in ("1", "0"):
+        monkeypatch.setenv("MPPI_ROLLOUT_DRAW", draw)
+        w = workload(N, K, N, objective, False, 20.0)
+        sv = solver_for(w, M.FP32)
+        x, got = np.array(w["x0"]), []
+        for step in range(3):
+            u0, _, _ = sv.solve(x, step * 0.02)
+            got.append(outcome(sv))
+            x = M.plant_step(w["quad"], x, u0, 0.02, 2)
+        sv.close()
+        out.append(got)
+    for a, b in zip(*out):
+        for xa, xb in zip(a, b):
+            np.testing.assert_array_equal(xa, xb)
