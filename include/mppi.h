@@ -227,7 +227,9 @@ typedef struct {
  * in mppi_info (rollout_waves, rollout_draw).  Two environment variables,
  * read at creation, override the choice for testing and measurement:
  * MPPI_ROLLOUT_WAVES (1..4: waves per 64-sample tile) and MPPI_ROLLOUT_DRAW
- * (0 or 1: whether a binary32 one-wave rollout draws its own samples).  The
+ * (0 or 1: whether a binary32 one-wave rollout draws its own samples).  Some
+ * sizes of the one-wave layout run as a pair of waves per tile, with its
+ * results bit for bit, unless one of the two variables is set.  The
  * results do not depend on the layout beyond rounding; rollout_draw changes
  * no bit. */
 mppi_status mppi_create(const mppi_params *params, const mppi_quad *quad,

@@ -75,6 +75,7 @@ struct KArgs {
     int32_t inner;              // 1: an inner iteration of a control step (no shift, the first
                                 // iteration's last applied input)
     int32_t input_model;        // INPUT_THRUST (13 states) or INPUT_RATE (thrust rates, 17 states)
+    int32_t rollout_pair;       // 1: two waves per tile where the layout is one wave (the results of one wave)
     int32_t rate_pipe;          // 1: a rate solve on its own runs the pipelined rollout (the results of one wave)
     uint32_t seed_lo, seed_hi;
     // model

@@ -484,10 +484,104 @@ template <typename Real> __device__ __forceinline__ void in_vgpr(Model<Real> &M)
     M.gx = in_vgpr(M.gx); M.gy = in_vgpr(M.gy); M.gz = in_vgpr(M.gz);
 }
 
+// What a wave waits for before it starts a step: each lane watches one
+// counter; step k may start once every lane's counter plus its offset is
+// above k (offset 0: the producer has done step k; a ring's size: the slot of
+// step k has been read).  LDS operations of one wave execute in order, so a
+// data read issued after the counter read sees what was written before the
+// counter was, and a counter written after the data never overtakes it: the
+// compiler is held to that order, the hardware needs no wait for it.
+struct PipeWatch {
+    const int *c;
+    int off;
+    __device__ __forceinline__ int peek() const
+    {
+        return __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) + off;
+    }
+    static __device__ __forceinline__ bool may_start(int seen, int k)
+    {
+        const bool r = __builtin_amdgcn_ballot_w64(seen > k) == ~0ull;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "singlethread");
+        return r;
+    }
+    template <int SLEEP> __device__ __forceinline__ void wait(int k) const
+    {
+        while (!may_start(peek(), k)) __builtin_amdgcn_s_sleep(SLEEP);
+    }
+};
+// Lane 0 writes the counter, the other lanes a word that nothing reads: no
+// change of the execution mask, so the steps around it stay one block.
+__device__ __forceinline__ void pipe_publish(int *c, int v)
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "singlethread");
+    __hip_atomic_store(c, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "singlethread");
+}
+
+// One tile on two waves: one wave draws the samples and sums the costs, the
+// other moves the state (all in the arithmetic and order of the one-wave
+// rollout, so the results are the same bit for bit).  The draws run kPairAhead
+// steps ahead of the costs, the motion in between.
+//
+// Where the one-wave rollout leaves a single wave per SIMD (two to four tiles
+// per CU), its operations issue at half the rate that two waves reach, so the
+// two parts run beside each other, and no sample kernel writes what this one
+// reads: K = 65000, N = 100 120 -> 98 us a solve, tracking K = 50011, N = 33
+// 60 -> 42.
+enum RolloutPart { PART_ALL = 0, PART_COSTS = 1, PART_MOTION = 2 };
+constexpr int kPairRing = 4, kPairAhead = 3;
+// Slot k mod kPairRing of a ring is written again by step k + kPairRing.  The
+// costs publish the input of step i once they have read the motion of step
+// i - 1 - kPairAhead, and the motion of step i is written after its input was
+// published: with kPairAhead < kPairRing neither overtakes its reader, and a
+// wave waits for the other's counter only to read.
+template <int OBJ, typename Real> struct PairLds {
+    typedef typename Vec4<Real>::T R4;
+    static constexpr bool CONT = OBJ == OBJ_CONTOUR, TRACK = OBJ == OBJ_TRACK;
+    R4 u[kPairRing][64];
+    Real V[CONT ? kPairRing : 1][64];
+    R4 dpw[kPairRing][64];              // the step's displacement and the new state's first body rate
+    Real wy[kPairRing][64], wz[kPairRing][64];
+    R4 q[TRACK ? kPairRing : 1][64];
+    Real v[TRACK ? 3 : 1][TRACK ? kPairRing : 1][64];
+    int cnt[2 + 64];                    // inputs drawn, steps moved; then words that nothing reads
+};
+struct NoPair {};
+
 template <int OBJ, typename Real, bool DRAW> struct DrawLds {
     typename Vec4<Real>::T us[DRAW ? kNMax : 1];    // shifted warm-start inputs per step
     Real vs[DRAW && OBJ == OBJ_CONTOUR ? kNMax : 1];
 };
+
+// The shifted warm start of every step, staged once by the NT threads.
+template <int NT, int OBJ, typename Real, bool DRAW, typename Head>
+__device__ __forceinline__ void stage_warm_start(const KArgs &a, int blk, const Head &h, DrawLds<OBJ, Real, DRAW> &lds)
+{
+    typedef typename Vec4<Real>::T R4;
+    constexpr bool HAS_V = OBJ == OBJ_CONTOUR;
+    auto &s_us = lds.us;
+    auto &s_vs = lds.vs;
+    const int K = a.K, N = a.N;
+    const int shift = h.shift, warm = h.warm;
+    const bool rows = a.regen && blk == (K >> 6);
+    for (int k = (int)threadIdx.x; k < N; k += NT) {
+        int src = k + shift;
+        if (src > N - 1) src = N - 1;
+        R4 o;
+        o.x = warm ? (Real)a.wU[4 * src + 0] : (Real)a.hover;
+        o.y = warm ? (Real)a.wU[4 * src + 1] : (Real)a.hover;
+        o.z = warm ? (Real)a.wU[4 * src + 2] : (Real)a.hover;
+        o.w = warm ? (Real)a.wU[4 * src + 3] : (Real)a.hover;
+        s_us[k] = o;
+        if (HAS_V) s_vs[k] = warm ? (Real)a.wV[src] : Real(0);
+        // the weighted average draws the samples again from these rows
+        if (rows) {
+            ((R4 *)a.nomU)[k] = o;
+            if (HAS_V) ((Real *)a.nomV)[k] = s_vs[k];
+        }
+    }
+    __syncthreads();
+}
 
 // One wave: samples 64*blk .. 64*blk+63 (sample K is the noise-free nominal).
 // DRAW: the wave draws its samples itself (the noise, perturbation and clip
@@ -498,8 +592,11 @@ template <int OBJ, typename Real, bool DRAW> struct DrawLds {
 // the pipelined rollout, so that the results are those of k_rollout4 bit for
 // bit (for launches with more tiles than the pipeline holds at once).
 // NOM: the tile holds the nominal alone (K a multiple of 64) and draws nothing.
-template <int OBJ, typename Real, bool DRAW, bool PIPE, bool RATE, bool DRAG, bool NOM, typename Head>
-__device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const Head &h, DrawLds<OBJ, Real, DRAW> &lds)
+// PART: the whole rollout or one wave's part of a pair.
+template <int OBJ, typename Real, bool DRAW, bool PIPE, bool RATE, bool DRAG, bool NOM, int PART = PART_ALL,
+          typename Head, typename Pair = NoPair>
+__device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const Head &h, DrawLds<OBJ, Real, DRAW> &lds,
+                                               Pair &&pr = Pair())
 {
     typedef typename Vec4<Real>::T R4;
     constexpr bool GATE = OBJ == OBJ_GATE, CONT = OBJ == OBJ_CONTOUR, TRACK = OBJ == OBJ_TRACK;
@@ -512,29 +609,9 @@ __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const He
     const bool active = m <= K;
     const bool nominal = m == K;
     Real Jfinal = Real(0);
-    if (DRAW) {
-        const int shift = h.shift, warm = h.warm;
-        const bool rows = a.regen && blk == (K >> 6);
-        for (int k = (int)threadIdx.x; k < N; k += 64) {
-            int src = k + shift;
-            if (src > N - 1) src = N - 1;
-            R4 o;
-            o.x = warm ? (Real)a.wU[4 * src + 0] : (Real)a.hover;
-            o.y = warm ? (Real)a.wU[4 * src + 1] : (Real)a.hover;
-            o.z = warm ? (Real)a.wU[4 * src + 2] : (Real)a.hover;
-            o.w = warm ? (Real)a.wU[4 * src + 3] : (Real)a.hover;
-            s_us[k] = o;
-            if (HAS_V) s_vs[k] = warm ? (Real)a.wV[src] : Real(0);
-            // the weighted average draws the samples again from these rows
-            if (rows) {
-                ((R4 *)a.nomU)[k] = o;
-                if (HAS_V) ((Real *)a.nomV)[k] = s_vs[k];
-            }
-        }
-        __syncthreads();
-    }
+    if (DRAW && PART == PART_ALL) stage_warm_start<64>(a, blk, h, lds);
 
-    if (active) {
+    if (PART != PART_ALL || active) {
         Model<Real> M(a);
         in_vgpr(M);
         const Real dt = in_vgpr((Real)a.dt);
@@ -554,18 +631,24 @@ __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const He
         const size_t ustride = nominal ? 1 : (size_t)K;
         const Real *vrow = nullptr;
         if (HAS_V) vrow = nominal ? (const Real *)a.nomV : (const Real *)a.vctrl + m;
-        const bool keep = DRAW && !a.regen && !nominal;
+        const bool keep = DRAW && !a.regen && (PART == PART_ALL ? !nominal : m < K);
+        const bool quiet = PART == PART_ALL ? nominal : m >= K;
         const uint32_t s_solve = h.s, key0 = a.seed_lo, key1 = a.seed_hi;
         const Real lo = (Real)(RATE ? a.rate_lim[0] : a.t_min), hi = (Real)(RATE ? a.rate_lim[1] : a.t_max);
         const Real vlo = (Real)(RATE ? a.dv_lim[0] : 0.0), vhi = (Real)(RATE ? a.dv_lim[1] : a.v_max);
         // the nominal draws with zero noise, so that no step selects
-        const Real sig0 = in_vgpr(nominal ? Real(0) : (Real)a.sigma[0]), sig1 = in_vgpr(nominal ? Real(0) : (Real)a.sigma[1]);
-        const Real sig2 = in_vgpr(nominal ? Real(0) : (Real)a.sigma[2]), sig3 = in_vgpr(nominal ? Real(0) : (Real)a.sigma[3]);
-        const Real sigv = in_vgpr(nominal ? Real(0) : (Real)a.sigma_v);
+        const Real sig0 = in_vgpr(quiet ? Real(0) : (Real)a.sigma[0]), sig1 = in_vgpr(quiet ? Real(0) : (Real)a.sigma[1]);
+        const Real sig2 = in_vgpr(quiet ? Real(0) : (Real)a.sigma[2]), sig3 = in_vgpr(quiet ? Real(0) : (Real)a.sigma[3]);
+        const Real sigv = in_vgpr(quiet ? Real(0) : (Real)a.sigma_v);
         R4 *rec = (R4 *)a.ctrl + m;                 // the sample's record, advanced step by step
         Real *vrec = HAS_V ? (Real *)a.vctrl + m : nullptr;
         auto put = [&](const R4 &uo, const Real vo) {
-            if (DRAW) {
+            if (PART == PART_COSTS) {
+                if (keep) {
+                    *rec = uo;
+                    if (HAS_V) *vrec = vo;
+                }
+            } else if (DRAW) {
                 if (keep) {
                     store_nt(rec, uo);
                     if (HAS_V) store_nt(vrec, vo);
@@ -641,14 +724,67 @@ __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const He
         const double inv_dt = 1.0 / a.dt, t_min = a.t_min, t_max = a.t_max, v_max = a.v_max;
         R4 un;
         Real vn = Real(0);
-        if (!DRAW) {
+        if (PART == PART_ALL && !DRAW) {
             un = urow[0];
             if (HAS_V) vn = vrow[0];
         }
-        for (int k = 0; k < N; ++k) {
+        const int lane = (int)(threadIdx.x & 63);
+        PipeWatch watch = {};
+        int *mine = nullptr;
+        int seen = 0;
+        if constexpr (PART != PART_ALL) {
+            watch.c = &pr.cnt[PART == PART_COSTS ? 1 : 0];
+            mine = &pr.cnt[lane == 0 ? (PART == PART_COSTS ? 0 : 1) : 2 + lane];
+        }
+        for (int k = PART == PART_COSTS ? -kPairAhead : 0; k < N; ++k) {
             R4 u;
             Real V = Real(0);
-            if (DRAW) {
+            Real dp[3], wn[3], qn[4], vnew[3];
+            if constexpr (PART == PART_COSTS) {
+                // draw step k + kPairAhead while the motion of step k arrives
+                const int sl = k & (kPairRing - 1);
+                auto load = [&] {
+                    const R4 d = pr.dpw[sl][lane];
+                    dp[0] = d.x; dp[1] = d.y; dp[2] = d.z; wn[0] = d.w;
+                    wn[1] = pr.wy[sl][lane];
+                    wn[2] = pr.wz[sl][lane];
+                    if (TRACK) {
+                        const R4 t = pr.q[sl][lane];
+                        qn[0] = t.x; qn[1] = t.y; qn[2] = t.z; qn[3] = t.w;
+                        for (int i = 0; i < 3; ++i) vnew[i] = pr.v[i][sl][lane];
+                    }
+                };
+                seen = watch.peek();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "singlethread");
+                load();
+                if (!GATE) u = pr.u[sl][lane];
+                if (CONT) V = pr.V[sl][lane];
+                if (k + kPairAhead < N) {
+                    const int dl = (k + kPairAhead) & (kPairRing - 1);
+                    R4 ud;
+                    Real vd = Real(0);
+                    draw(k + kPairAhead, ud, vd);
+                    pr.u[dl][lane] = ud;
+                    if (CONT) pr.V[dl][lane] = vd;
+                    pipe_publish(mine, k + kPairAhead + 1);
+                }
+                if (k < 0) continue;
+                if (!PipeWatch::may_start(seen, k)) {
+                    watch.wait<0>(k);
+                    load();
+                }
+            } else if constexpr (PART == PART_MOTION) {
+                // the inputs of the next step are read while this one computes
+                const int sl = k & (kPairRing - 1);
+                if (k == 0 || !PipeWatch::may_start(seen, k)) {
+                    watch.wait<0>(k);
+                    un = pr.u[sl][lane];
+                }
+                u = un;
+                seen = watch.peek();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "singlethread");
+                un = pr.u[(k + 1) & (kPairRing - 1)][lane];
+            } else if (DRAW) {
                 draw(k, u, V);
             } else {
                 // the inputs of the next step are in flight while this one computes
@@ -676,7 +812,8 @@ __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const He
 
             // ---- stage terms at state k
             Real ax = 0, ay = 0, az = 0;  // p_k - c_g (gate)
-            if (GATE) {
+            if (PART == PART_MOTION) {
+            } else if (GATE) {
                 ax = p[0] - gt.cx;
                 ay = p[1] - gt.cy;
                 az = p[2] - gt.cz;
@@ -799,85 +936,106 @@ __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const He
             // ---- dynamics: RK4 of Eq. (2).  The rate model's thrusts move
             // linearly over the step: its stages see them at the start, middle
             // and end of it.
-            StepInput<Real> in[3];
-            if (RATE) {
-                const double h = 0.5 * a.dt, ur[4] = {(double)u.x, (double)u.y, (double)u.z, (double)u.w};
-                in[0] = step_input(M, (Real)T[0], (Real)T[1], (Real)T[2], (Real)T[3]);
-                in[1] = step_input(M, (Real)(T[0] + h * ur[0]), (Real)(T[1] + h * ur[1]), (Real)(T[2] + h * ur[2]),
-                                   (Real)(T[3] + h * ur[3]));
-                in[2] = step_input(M, (Real)(T[0] + a.dt * ur[0]), (Real)(T[1] + a.dt * ur[1]),
-                                   (Real)(T[2] + a.dt * ur[2]), (Real)(T[3] + a.dt * ur[3]));
-                for (int i = 0; i < 4; ++i) T[i] += a.dt * ur[i];
-            } else {
-                in[0] = step_input(M, u.x, u.y, u.z, u.w);
-            }
-            Real dp[3], dv[3], dq[4], dw[3];
-            {
-                Real vst[3], qs[4], ws[3];
+            if (PART != PART_COSTS) {
+                StepInput<Real> in[3];
+                if (RATE) {
+                    const double h = 0.5 * a.dt, ur[4] = {(double)u.x, (double)u.y, (double)u.z, (double)u.w};
+                    in[0] = step_input(M, (Real)T[0], (Real)T[1], (Real)T[2], (Real)T[3]);
+                    in[1] = step_input(M, (Real)(T[0] + h * ur[0]), (Real)(T[1] + h * ur[1]), (Real)(T[2] + h * ur[2]),
+                                       (Real)(T[3] + h * ur[3]));
+                    in[2] = step_input(M, (Real)(T[0] + a.dt * ur[0]), (Real)(T[1] + a.dt * ur[1]),
+                                       (Real)(T[2] + a.dt * ur[2]), (Real)(T[3] + a.dt * ur[3]));
+                    for (int i = 0; i < 4; ++i) T[i] += a.dt * ur[i];
+                } else {
+                    in[0] = step_input(M, u.x, u.y, u.z, u.w);
+                }
+                Real dv[3], dq[4], dw[3];
+                {
+                    Real vst[3], qs[4], ws[3];
 #pragma unroll
-                for (int i = 0; i < 3; ++i) { vst[i] = v[i]; ws[i] = w[i]; }
+                    for (int i = 0; i < 3; ++i) { vst[i] = v[i]; ws[i] = w[i]; }
 #pragma unroll
-                for (int i = 0; i < 4; ++i) qs[i] = q[i];
+                    for (int i = 0; i < 4; ++i) qs[i] = q[i];
 #pragma unroll
-                for (int st = 0; st < 4; ++st) {
-                    const StepInput<Real> &si = in[RATE ? (st == 0 ? 0 : (st < 3 ? 1 : 2)) : 0];
-                    Real kv[3], kw[3], kq[4];
-                    stage_accel<DRAG>(M, si.fm, qs, vst, kv);
-                    kw[0] = si.tx - M.gx * ws[1] * ws[2];
-                    kw[1] = si.ty - M.gy * ws[2] * ws[0];
-                    kw[2] = si.tz - M.gz * ws[0] * ws[1];
-                    // kq is twice the quaternion rate; the factor 1/2 is
-                    // carried by the step sizes (exact: a power of two)
-                    kq[0] = -qs[1] * ws[0] - qs[2] * ws[1] - qs[3] * ws[2];
-                    kq[1] = qs[0] * ws[0] + qs[2] * ws[2] - qs[3] * ws[1];
-                    kq[2] = qs[0] * ws[1] - qs[1] * ws[2] + qs[3] * ws[0];
-                    kq[3] = qs[0] * ws[2] + qs[1] * ws[1] - qs[2] * ws[0];
-                    if (st == 0) {
+                    for (int st = 0; st < 4; ++st) {
+                        const StepInput<Real> &si = in[RATE ? (st == 0 ? 0 : (st < 3 ? 1 : 2)) : 0];
+                        Real kv[3], kw[3], kq[4];
+                        stage_accel<DRAG>(M, si.fm, qs, vst, kv);
+                        kw[0] = si.tx - M.gx * ws[1] * ws[2];
+                        kw[1] = si.ty - M.gy * ws[2] * ws[0];
+                        kw[2] = si.tz - M.gz * ws[0] * ws[1];
+                        // kq is twice the quaternion rate; the factor 1/2 is
+                        // carried by the step sizes (exact: a power of two)
+                        kq[0] = -qs[1] * ws[0] - qs[2] * ws[1] - qs[3] * ws[2];
+                        kq[1] = qs[0] * ws[0] + qs[2] * ws[2] - qs[3] * ws[1];
+                        kq[2] = qs[0] * ws[1] - qs[1] * ws[2] + qs[3] * ws[0];
+                        kq[3] = qs[0] * ws[2] + qs[1] * ws[1] - qs[2] * ws[0];
+                        if (st == 0) {
 #pragma unroll
-                        for (int i = 0; i < 3; ++i) { dp[i] = vst[i]; dv[i] = kv[i]; dw[i] = kw[i]; }
+                            for (int i = 0; i < 3; ++i) { dp[i] = vst[i]; dv[i] = kv[i]; dw[i] = kw[i]; }
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) dq[i] = kq[i];
-                    } else if (st < 3) {
+                            for (int i = 0; i < 4; ++i) dq[i] = kq[i];
+                        } else if (st < 3) {
 #pragma unroll
-                        for (int i = 0; i < 3; ++i) {
-                            dp[i] += Real(2) * vst[i];
-                            dv[i] += Real(2) * kv[i];
-                            dw[i] += Real(2) * kw[i];
-                        }
+                            for (int i = 0; i < 3; ++i) {
+                                dp[i] += Real(2) * vst[i];
+                                dv[i] += Real(2) * kv[i];
+                                dw[i] += Real(2) * kw[i];
+                            }
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) dq[i] += Real(2) * kq[i];
-                    } else {
+                            for (int i = 0; i < 4; ++i) dq[i] += Real(2) * kq[i];
+                        } else {
 #pragma unroll
-                        for (int i = 0; i < 3; ++i) {
-                            dp[i] = dt6 * (dp[i] + vst[i]);
-                            dv[i] = dt6 * (dv[i] + kv[i]);
-                            dw[i] = dt6 * (dw[i] + kw[i]);
-                        }
+                            for (int i = 0; i < 3; ++i) {
+                                dp[i] = dt6 * (dp[i] + vst[i]);
+                                dv[i] = dt6 * (dv[i] + kv[i]);
+                                dw[i] = dt6 * (dw[i] + kw[i]);
+                            }
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            if (PIPE) {
-                                q[i] = q[i] + dt12 * (dq[i] + kq[i]);
-                            } else {
-                                dq[i] = dt12 * (dq[i] + kq[i]);
-                                q[i] += dq[i];
+                            for (int i = 0; i < 4; ++i) {
+                                if (PIPE) {
+                                    q[i] = q[i] + dt12 * (dq[i] + kq[i]);
+                                } else {
+                                    dq[i] = dt12 * (dq[i] + kq[i]);
+                                    q[i] += dq[i];
+                                }
                             }
                         }
-                    }
-                    if (st < 3) {
-                        const Real hh = st < 2 ? h2 : dt, hq = st < 2 ? h4 : h2;
+                        if (st < 3) {
+                            const Real hh = st < 2 ? h2 : dt, hq = st < 2 ? h4 : h2;
 #pragma unroll
-                        for (int i = 0; i < 3; ++i) {
-                            vst[i] = v[i] + hh * kv[i];
-                            ws[i] = w[i] + hh * kw[i];
+                            for (int i = 0; i < 3; ++i) {
+                                vst[i] = v[i] + hh * kv[i];
+                                ws[i] = w[i] + hh * kw[i];
+                            }
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) qs[i] = q[i] + hq * kq[i];
                         }
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) qs[i] = q[i] + hq * kq[i];
                     }
                 }
-            }
 #pragma unroll
-            for (int i = 0; i < 3; ++i) { p[i] += dp[i]; v[i] += dv[i]; w[i] += dw[i]; }
-            renormalize(q);
+                for (int i = 0; i < 3; ++i) { p[i] += dp[i]; v[i] += dv[i]; w[i] += dw[i]; }
+                renormalize(q);
+                if constexpr (PART == PART_MOTION) {
+                    const int sl = k & (kPairRing - 1);
+                    R4 d;
+                    d.x = dp[0]; d.y = dp[1]; d.z = dp[2]; d.w = w[0];
+                    pr.dpw[sl][lane] = d;
+                    pr.wy[sl][lane] = w[1];
+                    pr.wz[sl][lane] = w[2];
+                    if (TRACK) {
+                        R4 t;
+                        t.x = q[0]; t.y = q[1]; t.z = q[2]; t.w = q[3];
+                        pr.q[sl][lane] = t;
+                        for (int i = 0; i < 3; ++i) pr.v[i][sl][lane] = v[i];
+                    }
+                    pipe_publish(mine, k + 1);
+                    continue;
+                }
+            } else {
+                for (int i = 0; i < 3; ++i) { p[i] += dp[i]; w[i] = wn[i]; if (TRACK) v[i] = vnew[i]; }
+                if (TRACK) for (int i = 0; i < 4; ++i) q[i] = qn[i];
+            }
 
             // ---- progress and switching (gate)
             if (GATE) {
@@ -919,6 +1077,7 @@ __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const He
             J.add(term);
             if (!GATE && !RATE) { up[0] = u.x; up[1] = u.y; up[2] = u.z; up[3] = u.w; }
         }
+        if (PART == PART_MOTION) return;
         if (TRACK) {
             int r = i0 + N;
             if (r > R - 1) r = R - 1;
@@ -964,7 +1123,7 @@ __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const He
         }
         Jfinal = PIPE ? ((J0.value() + J1.value()) + J2.value()) + J.value() : J.value();
         if (nominal) a.cur->J_nom = (double)Jfinal;
-        else ((Real *)a.J)[m] = Jfinal;
+        else if (PART == PART_ALL || m < K) ((Real *)a.J)[m] = Jfinal;
     }
     // smallest finite sample cost of the tile
     store_tile_min(Jfinal, active && !nominal && isfinite(Jfinal), a.tmin, blk);
@@ -985,6 +1144,25 @@ __device__ __forceinline__ void rollout1_body(const KArgs &a, int blk, const Hea
     } else {
         if (nom) rollout1_steps<OBJ, Real, DRAW, PIPE, RATE, false, NOM>(a, blk, h, lds);
         else rollout1_steps<OBJ, Real, DRAW, PIPE, RATE, false, false>(a, blk, h, lds);
+    }
+}
+
+// A pair of waves per tile (binary32, thrust input).
+template <int OBJ, typename Real> __global__ __launch_bounds__(128) void k_rollout_pair(KArgs a)
+{
+    __shared__ HeadVals h;
+    __shared__ DrawLds<OBJ, Real, true> lds;
+    __shared__ PairLds<OBJ, Real> pr;
+    compute_head<OBJ == OBJ_CONTOUR>(a, h);
+    if (blockIdx.x == 0 && threadIdx.x == 0) publish_head(a, h);
+    if (threadIdx.x < 2) pr.cnt[threadIdx.x] = 0;
+    stage_warm_start<128>(a, blockIdx.x, h, lds);
+    if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) == 0) {
+        rollout1_steps<OBJ, Real, true, false, false, false, false, PART_COSTS>(a, blockIdx.x, h, lds, pr);
+    } else if (a.has_drag) {
+        rollout1_steps<OBJ, Real, true, false, false, true, false, PART_MOTION>(a, blockIdx.x, h, lds, pr);
+    } else {
+        rollout1_steps<OBJ, Real, true, false, false, false, false, PART_MOTION>(a, blockIdx.x, h, lds, pr);
     }
 }
 
@@ -1841,40 +2019,6 @@ __device__ __forceinline__ void rollout3_body(const KArgs &a, int blk, const Hea
 // drawing waves publish the next step they will draw, the stages the number
 // of steps they have done.
 enum PipeCounter { PC_DRAW = 0, PC_RATE = 4, PC_ATT = 5, PC_POS = 6, PC_COST = 7, PC_TERM = 8, PC_CHAIN = 9, PC_N = 16 };
-
-// What a wave waits for before it starts a step: each lane watches one
-// counter; step k may start once every lane's counter plus its offset is
-// above k (offset 0: the producer has done step k; a ring's size: the slot of
-// step k has been read).  LDS operations of one wave execute in order, so a
-// data read issued after the counter read sees what was written before the
-// counter was, and a counter written after the data never overtakes it: the
-// compiler is held to that order, the hardware needs no wait for it.
-struct PipeWatch {
-    const int *c;
-    int off;
-    __device__ __forceinline__ int peek() const
-    {
-        return __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) + off;
-    }
-    static __device__ __forceinline__ bool may_start(int seen, int k)
-    {
-        const bool r = __builtin_amdgcn_ballot_w64(seen > k) == ~0ull;
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "singlethread");
-        return r;
-    }
-    template <int SLEEP> __device__ __forceinline__ void wait(int k) const
-    {
-        while (!may_start(peek(), k)) __builtin_amdgcn_s_sleep(SLEEP);
-    }
-};
-// Lane 0 writes the counter, the other lanes a word that nothing reads: no
-// change of the execution mask, so the steps around it stay one block.
-__device__ __forceinline__ void pipe_publish(int *c, int v)
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "singlethread");
-    __hip_atomic_store(c, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "singlethread");
-}
 
 // One stage of the pipeline over the steps 0..N-1: load(k, in) reads the
 // inputs of step k from the rings, step(k, in) computes it and writes its
@@ -3922,10 +4066,10 @@ static hipError_t launch_solve_t(const KArgs &a, bool acc64, hipStream_t st, hip
     const dim3 gs((a.K + 1 + 255) / 256, (a.N + kSampleSteps - 1) / kSampleSteps);
     if (ev) (void)hipEventRecord(ev[0], st);
     // a one-wave rollout that draws its samples (binary32) needs only the head first
-    const bool draw = sizeof(Real) == 4 && a.rollout_draw;
+    const bool draw = sizeof(Real) == 4 && a.rollout_draw && !a.rollout_pair;
     if (draw) {
         if constexpr (sizeof(Real) == 4) hipLaunchKernelGGL((k_head<Real, HAS_V>), dim3(1), dim3(256), 0, st, a);
-    } else if (a.rollout_waves < 3 && !a.rate_pipe) {
+    } else if (a.rollout_waves < 3 && !a.rate_pipe && !a.rollout_pair) {
         hipLaunchKernelGGL((k_sample<Real, HAS_V>), gs, dim3(256), 0, st, a);
     }
     if (ev) (void)hipEventRecord(ev[1], st);
@@ -3948,6 +4092,8 @@ static hipError_t launch_solve_t(const KArgs &a, bool acc64, hipStream_t st, hip
         hipLaunchKernelGGL((k_rollout3<OBJ, Real>), gt, dim3(192), 0, st, a);
     } else if (a.rollout_waves == 2) {
         hipLaunchKernelGGL((k_rollout_split<OBJ, Real>), gt, dim3(128), 0, st, a);
+    } else if (a.rollout_pair) {
+        if constexpr (sizeof(Real) == 4) hipLaunchKernelGGL((k_rollout_pair<OBJ, Real>), gt, dim3(128), 0, st, a);
     } else if (draw) {
         if constexpr (sizeof(Real) == 4) hipLaunchKernelGGL((k_rollout<OBJ, Real, true>), gt, dim3(64), 0, st, a);
     } else {

@@ -326,6 +326,17 @@ static void plan_layout(mppi_ctx *c)
     if (const char *e = getenv("MPPI_ROLLOUT_DRAW")) {
         if (e[0] == '0' || e[0] == '1') a.rollout_draw = (!c->fp64 && a.rollout_waves == 1) ? e[0] - '0' : 0;
     }
+    // A pair of waves per tile in place of one (binary32, the same results):
+    // against one wave that reads a sample kernel's samples it pays up to
+    // twelve tiles per CU (contouring, whose costs outweigh the motion: eight),
+    // against one that draws them up to five.  One wave -> pair, us a solve:
+    // gate N = 50 4 tiles per CU 77 -> 63, 8: 109 -> 87, 12: 148 -> 133, 16:
+    // 166 -> 161 (tracking 131 -> 134); contouring N = 30 8: 101 -> 86, 12:
+    // 122 -> 130; drawing gate N = 220 5: 246 -> 197, N = 200 6: 230 -> 242.
+    // Either environment variable keeps one wave.
+    const int pair_tiles = a.rollout_draw ? 5 : (c->objective == MPPI_OBJ_CONTOUR ? 8 : 12);
+    a.rollout_pair = (!c->fp64 && a.rollout_waves == 1 && a.n_tiles <= pair_tiles * n_cu &&
+                      !getenv("MPPI_ROLLOUT_WAVES") && !getenv("MPPI_ROLLOUT_DRAW")) ? 1 : 0;
 }
 
 // The average can draw the samples again only where the rollout draws them
@@ -451,6 +462,7 @@ mppi_status mppi_create(const mppi_params *params, const mppi_quad *quad, const 
         // sampling kernel walks per sample: the one-wave rollout reads it
         a.rollout_waves = 1;
         a.rollout_draw = 0;
+        a.rollout_pair = 0;
         // With a CU per tile a solve on its own runs the pipelined rollout,
         // which draws the samples and whose results are those of one wave per
         // tile bit for bit; MPPI_ROLLOUT_WAVES=1 keeps it to one wave.  More
