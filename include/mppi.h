@@ -345,16 +345,18 @@ mppi_status mppi_read_profile(mppi_ctx *ctx, double mean_ms[3], int32_t *n_solve
  * step), repeated n_iter times (the contexts' shared n_iter), per group
  * of contexts sharing an objective, accumulation type and input model.
  * One-wave rollouts of binary32 contexts draw their samples themselves (no
- * sample kernel).  Grids are fixed
- * and the work description lives in device memory, so the sequence is
- * captured once in a HIP graph (cfg.use_graph) and replayed for any subset.
+ * sample kernel), and one block of the average takes several horizon steps;
+ * pipelined binary32 contexts run one-wave rollouts of the same results in a
+ * step whose tiles exceed what the chip holds.  Grids are fixed and the work
+ * description lives in device memory, so the sequence is captured once in a
+ * HIP graph (cfg.use_graph) and replayed for any subset.
  * Each context's result, report and warm-start state are the same as those
  * of mppi_solve_device on that context alone with the same rollout layout. */
 typedef struct mppi_batch mppi_batch;
 
 typedef struct {
-    int32_t rollout_waves;     /* waves per 64-sample tile: 1 (separate sampling
-                                  kernel), 2 (attitude / translation split), 3
+    int32_t rollout_waves;     /* waves per 64-sample tile: 1 (in binary64 with a
+                                  separate sampling kernel), 2 (attitude / translation split), 3
                                   (sampling joins the rollout) or 4 (pipeline:
                                   body rates, attitude, translation, costs and
                                   the draws on waves of their own, coupled by

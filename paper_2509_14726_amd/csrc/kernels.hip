@@ -9,9 +9,12 @@
 //                    smallest cost of the tile
 //   k_rollout_rate   the pipeline for the rate input
 //   k_rollout3       three waves, chunks of steps between barriers
+//   k_rollout_pair   (binary32, medium K) the one-wave rollout's arithmetic on
+//                    two waves: draws and costs | motion
 //   k_sample +       (large K) noise and clipped samples for all (m, k), then
-//   k_rollout /      one sample per lane (k_rollout) or attitude and
-//   k_rollout_split  translation on two waves (k_rollout_split)
+//   k_rollout /      one sample per lane (k_rollout; drawing itself after k_head
+//   k_rollout_split  where the sample tensor is large) or attitude and
+//                    translation on two waves (k_rollout_split)
 //   k_final          one block per horizon step: J_min from the tile minima,
 //                    softmax weights (Eq. (4)), the weighted average (Eq. (5)),
 //                    the first input, the report and the warm-start hand-over

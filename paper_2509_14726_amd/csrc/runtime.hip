@@ -295,9 +295,9 @@ static void plan_layout(mppi_ctx *c)
     // splitting each tile's step over pipelined waves (draws, body rates,
     // attitude, position, costs) shortens each step.  With rings of 8 steps
     // the LDS holds one such workgroup per CU; with rings of 4 (binary32) two
-    // share a CU, which takes up to two tiles per CU in one round.  Beyond that one wave per 64
-    // samples, which issues the fewest instructions, keeps the whole chip
-    // busy.  Binary64 rings (of 4) fit one workgroup per CU, so from
+    // share a CU, which takes up to two tiles per CU in one round.  Beyond that
+    // one wave per 64 samples, which issues the fewest instructions, keeps the
+    // whole chip busy (or a pair of waves, below).  Binary64 rings (of 4) fit one workgroup per CU, so from
     // one to two tiles per CU the two-wave split (attitude | translation, two
     // workgroups per CU) takes over there.  Measured on 256 CUs for N = 50,
     // 100 and 200 at 129 to 1016 tiles.  The environment variable
@@ -1097,8 +1097,9 @@ static hipError_t resolve_cfg(mppi_batch *b)
     if (ring == 0) ring = (!b->fp64 && tiles <= cu) ? 8 : 4;
     // persistent rollout workgroups: what fits one CU times the CUs (one
     // pipelined workgroup with rings of 8 steps or in binary64, two with rings
-    // of 4 in binary32, one three-wave, two two-wave, eight one-wave)
-    int per_cu = 8;
+    // of 4 in binary32, one three-wave, two two-wave, eight one-wave that read
+    // their samples, sixteen that draw them)
+    int per_cu = b->fp64 ? 8 : 16;
     if (waves == 4) per_cu = (!b->fp64 && ring == 4) ? 2 : 1;
     else if (waves == 3) per_cu = 1;
     else if (waves == 2) per_cu = 2;
@@ -1445,7 +1446,7 @@ mppi_status mppi_batch_autotune(mppi_batch *b, const double *d_reqs, double *d_u
     std::vector<mppi_batch_cfg> cand;
     const int cu = b->n_cu;
     for (int waves = 1; waves <= (b->has_rate ? 1 : 4); ++waves) {
-        const int rg_mult[] = {1, 2, 4, 8};
+        const int rg_mult[] = {1, 2, 4, 8, 16};
         for (int rm : rg_mult) {
             if (waves >= 2 && rm > 2) continue;  // one or two LDS rings fit one CU
             for (int sm : {1, 4})
