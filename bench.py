@@ -39,17 +39,17 @@ PEAK_HBM_GBPS = 8000.0
 # HBM bytes per launch measured with rocprofv3 --pmc FETCH_SIZE and, in a run
 # of its own, WRITE_SIZE (KiB per dispatch, mean of 12 dispatches of the
 # benchmark workload), scaled by what the same counters read for a plain
-# 256 MiB device copy (FETCH_SIZE 131085.2 KiB -> x 2.0, WRITE_SIZE
+# 256 MiB device copy (FETCH_SIZE 131085.3 KiB -> x 2.0, WRITE_SIZE
 # 262144.0 KiB -> x 1.0); see profiles/k_rollout4_gate_k8192_n100_traffic.md.
 # They hold only for the workload (K = 8192, N = 100, gate, binary32, the
-# four-wave layout with 4-step chunks; the average reading the sample tensor
+# pipelined layout; the average reading the sample tensor
 # or drawing the samples again) and the device sources they were taken on
 # (sha256 of kernels.hip, device.hpp, rollout.hpp, noise.hpp in that order);
 # otherwise the traffic is reported as null.
-TRAFFIC_SOURCES = "fb4b8f90baacc8aedb9d869f966968959d580ebad4ea0565a29b5417ce29b7b9"
-FETCH_SCALE, WRITE_SCALE = 262144.0 / 131085.2, 262144.0 / 262144.0
-TRAFFIC_KIB = {("k_rollout4", 0): (185.7, 12836.4), ("k_final", 0): (6575.5, 6.6),
-               ("k_rollout4", 1): (185.6, 38.0), ("k_final", 1): (211.5, 6.6)}
+TRAFFIC_SOURCES = "7d57694adeb42afa68574a26f737637a26e4302400b20af45ae08a3c0670a44b"
+FETCH_SCALE, WRITE_SCALE = 262144.0 / 131085.3, 262144.0 / 262144.0
+TRAFFIC_KIB = {("k_rollout4", 0): (135.0, 12836.4), ("k_final", 0): (6571.8, 6.8),
+               ("k_rollout4", 1): (134.8, 38.0), ("k_final", 1): (213.3, 6.8)}
 TRAFFIC_WORKLOADS = {(8192, 100, "fp32", 0), (8192, 100, "fp32", 1)}
 ROLLOUT_KERNELS = {1: "k_rollout", 2: "k_rollout_split", 3: "k_rollout3", 4: "k_rollout4"}
 
@@ -415,9 +415,10 @@ def large_bench(steps: int = 5):
     tune = sv.autotune(req[0].data_ptr(), reps=3, force=True)
     sv.close()
     K, N = 262144, 200
-    # algorithmic bytes of the average: the sample tensor, the costs and the
-    # tile minima, each read once (the blocks of later steps find the costs
-    # in L2)
+    # algorithmic bytes of an average whose weights are all alive: the sample
+    # tensor, the costs and the tile minima, each read once (the blocks of
+    # later steps find the costs in L2).  Samples of weight exactly 0 are not
+    # read, so no rate is formed from it.
     avg_bytes = K * N * 16 + K * 4 + ((K + 64) // 64) * 4
     # with the rollout drawing its samples the first slot times the head kernel
     return {"K": K, "N": N, "ms_per_solve": ms, "rollout_steps_per_s": K * N / (ms * 1e-3),
@@ -425,7 +426,6 @@ def large_bench(steps: int = 5):
             "kernels_ms": {"head" if info["rollout_draw"] else "sample": float(kern[0]),
                            "rollout": float(kern[1]), "average": float(kern[2])},
             "average_bytes_per_launch": avg_bytes,
-            "average_GBps": avg_bytes / (float(kern[2]) * 1e-3) / 1e9,
             "solve_ms_stored_average": tune["ms_stored"], "solve_ms_regenerating_average": tune["ms_regen"],
             "autotuner_choice": "regenerating" if tune["regen_average"] else "stored"}, w, rec
 
