@@ -3964,10 +3964,8 @@ static hipError_t launch_batch_t(const BArgs &b, const BatchLaunch &L, hipStream
                 hipLaunchKernelGGL((kb_rollout_draw<OBJ, Real, false, false>), dim3(L.draw_groups), dim3(64), 0, st, b);
         }
     }
-    if (L.draw) {
-    } else if (L.rollout_waves < 3) {
+    if (!L.draw && L.rollout_waves < 3)
         hipLaunchKernelGGL((kb_sample<Real, HAS_V>), dim3(L.sample_groups), dim3(256), 0, st, b);
-    }
     if (L.draw) {
     } else if (L.rollout_waves == 4) {
         if constexpr (sizeof(Real) == 4) {
@@ -3982,7 +3980,7 @@ static hipError_t launch_batch_t(const BArgs &b, const BatchLaunch &L, hipStream
         hipLaunchKernelGGL((kb_rollout3<OBJ, Real>), dim3(L.rollout_groups), dim3(192), 0, st, b);
     else if (L.rollout_waves == 2)
         hipLaunchKernelGGL((kb_rollout<OBJ, Real, 2>), dim3(L.rollout_groups), dim3(128), 0, st, b);
-    else
+    else if constexpr (sizeof(Real) == 8)   // (binary32 draws)
         hipLaunchKernelGGL((kb_rollout<OBJ, Real, 1>), dim3(L.rollout_groups), dim3(64), 0, st, b);
     if (L.ctrl_groups > 0)
         hipLaunchKernelGGL((kb_ctrl_cost<Real, HAS_V>), dim3(L.ctrl_groups), dim3(64), 0, st, b);
