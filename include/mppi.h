@@ -289,6 +289,16 @@ mppi_status mppi_solve_device(mppi_ctx *ctx, const double *d_req, double *d_u0);
 #define MPPI_SCRATCH_BYTES ((size_t)32 << 20)
 mppi_status mppi_solve_device_noalloc(mppi_ctx *ctx, const double *d_req, double *d_u0);
 
+/* Which of the rollouts that stand in for a reported layout, with its results,
+ * a solve ran (tests and measurement): an OR of the bits below.
+ * mppi_layout_ran: the context's latest solve of its own.
+ * mppi_batch_layout_ran: the batch's latest step.  0: none of them, or nothing
+ * solved yet, or NULL. */
+#define MPPI_RAN_PAIR 1       /* rollout_waves 1 as a pair of waves per tile        */
+#define MPPI_RAN_RATE_PIPE 2  /* the rate input's one wave as a pipeline            */
+#define MPPI_RAN_WIDE 4       /* a batch's pipelines as drawing one-wave rollouts   */
+int32_t mppi_layout_ran(const mppi_ctx *ctx);
+
 /* Wait for the context stream and copy the report of the latest solve. */
 mppi_status mppi_read_info(mppi_ctx *ctx, mppi_info *info);
 
@@ -391,6 +401,8 @@ mppi_status mppi_batch_create(mppi_ctx *const *ctxs, int32_t n, void *stream, co
  * stay valid until the stream reaches the end of the step.  Asynchronous. */
 mppi_status mppi_batch_solve_device(mppi_batch *b, const int32_t *active, int32_t n_active,
                                     const double *d_reqs, double *d_u0s);
+
+int32_t mppi_batch_layout_ran(const mppi_batch *b);   /* see mppi_layout_ran */
 
 /* Change the launch shape (drops a captured graph). */
 mppi_status mppi_batch_set_cfg(mppi_batch *b, const mppi_batch_cfg *cfg);

@@ -25,6 +25,8 @@
 #include <mutex>
 #include <type_traits>
 
+#include "../../include/mppi.h"
+
 #include "device.hpp"
 #include "kernels.hpp"
 #include "noise.hpp"
@@ -3951,14 +3953,15 @@ template <typename Real, typename Acc, bool HAS_V> __global__ __launch_bounds__(
 }
 
 template <typename Real, int OBJ>
-static hipError_t launch_batch_t(const BArgs &b, const BatchLaunch &L, hipStream_t st)
+static hipError_t launch_batch_t(const BArgs &b, const BatchLaunch &L, hipStream_t st, int32_t *ran)
 {
     constexpr bool HAS_V = OBJ == OBJ_CONTOUR;
     if constexpr (sizeof(Real) == 4) {
         if (L.draw) {
-            if (L.rollout_waves == 4)
+            if (L.rollout_waves == 4) {
+                *ran |= MPPI_RAN_WIDE;
                 hipLaunchKernelGGL((kb_rollout_draw<OBJ, Real, true, false>), dim3(L.draw_groups), dim3(64), 0, st, b);
-            else if (L.rate)
+            } else if (L.rate)
                 hipLaunchKernelGGL((kb_rollout_draw<OBJ, Real, false, true>), dim3(L.draw_groups), dim3(64), 0, st, b);
             else
                 hipLaunchKernelGGL((kb_rollout_draw<OBJ, Real, false, false>), dim3(L.draw_groups), dim3(64), 0, st, b);
@@ -3991,19 +3994,19 @@ static hipError_t launch_batch_t(const BArgs &b, const BatchLaunch &L, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_batch(const BArgs &b, const BatchLaunch &L, hipStream_t st)
+hipError_t launch_batch(const BArgs &b, const BatchLaunch &L, hipStream_t st, int32_t *ran)
 {
     if (L.fp64) {
         switch (L.objective) {
-        case OBJ_CONTOUR: return launch_batch_t<double, OBJ_CONTOUR>(b, L, st);
-        case OBJ_TRACK: return launch_batch_t<double, OBJ_TRACK>(b, L, st);
-        default: return launch_batch_t<double, OBJ_GATE>(b, L, st);
+        case OBJ_CONTOUR: return launch_batch_t<double, OBJ_CONTOUR>(b, L, st, ran);
+        case OBJ_TRACK: return launch_batch_t<double, OBJ_TRACK>(b, L, st, ran);
+        default: return launch_batch_t<double, OBJ_GATE>(b, L, st, ran);
         }
     }
     switch (L.objective) {
-    case OBJ_CONTOUR: return launch_batch_t<float, OBJ_CONTOUR>(b, L, st);
-    case OBJ_TRACK: return launch_batch_t<float, OBJ_TRACK>(b, L, st);
-    default: return launch_batch_t<float, OBJ_GATE>(b, L, st);
+    case OBJ_CONTOUR: return launch_batch_t<float, OBJ_CONTOUR>(b, L, st, ran);
+    case OBJ_TRACK: return launch_batch_t<float, OBJ_TRACK>(b, L, st, ran);
+    default: return launch_batch_t<float, OBJ_GATE>(b, L, st, ran);
     }
 }
 
@@ -4061,7 +4064,7 @@ static hipError_t launch_average_t(const KArgs &a, hipStream_t st)
 }
 
 template <typename Real, int OBJ>
-static hipError_t launch_solve_t(const KArgs &a, bool acc64, hipStream_t st, hipEvent_t *ev)
+static hipError_t launch_solve_t(const KArgs &a, bool acc64, hipStream_t st, hipEvent_t *ev, int32_t *ran)
 {
     constexpr bool HAS_V = OBJ == OBJ_CONTOUR;
     const dim3 gs((a.K + 1 + 255) / 256, (a.N + kSampleSteps - 1) / kSampleSteps);
@@ -4075,11 +4078,14 @@ static hipError_t launch_solve_t(const KArgs &a, bool acc64, hipStream_t st, hip
     }
     if (ev) (void)hipEventRecord(ev[1], st);
     const dim3 gt((a.K + 1 + 63) / 64);
+    *ran = 0;
     if (a.rate_pipe) {
         // (rings of 4 where 8 would not fit the LDS; binary64 contouring not at all)
         constexpr int R = sizeof(Real) == 8 || OBJ == OBJ_CONTOUR ? 4 : 8;
-        if constexpr (rate_pipe_fits(OBJ, sizeof(Real)))
+        if constexpr (rate_pipe_fits(OBJ, sizeof(Real))) {
+            *ran = MPPI_RAN_RATE_PIPE;
             hipLaunchKernelGGL((k_rollout_rate<OBJ, Real, R>), gt, dim3(64 * rate_pipe_waves(OBJ)), 0, st, a);
+        }
     } else if (a.rollout_waves == 4) {
         if constexpr (sizeof(Real) == 4) {
             if (a.ring_steps == 8)
@@ -4094,7 +4100,10 @@ static hipError_t launch_solve_t(const KArgs &a, bool acc64, hipStream_t st, hip
     } else if (a.rollout_waves == 2) {
         hipLaunchKernelGGL((k_rollout_split<OBJ, Real>), gt, dim3(128), 0, st, a);
     } else if (a.rollout_pair) {
-        if constexpr (sizeof(Real) == 4) hipLaunchKernelGGL((k_rollout_pair<OBJ, Real>), gt, dim3(128), 0, st, a);
+        if constexpr (sizeof(Real) == 4) {
+            *ran = MPPI_RAN_PAIR;
+            hipLaunchKernelGGL((k_rollout_pair<OBJ, Real>), gt, dim3(128), 0, st, a);
+        }
     } else if (draw) {
         if constexpr (sizeof(Real) == 4) hipLaunchKernelGGL((k_rollout<OBJ, Real, true>), gt, dim3(64), 0, st, a);
     } else {
@@ -4109,19 +4118,19 @@ static hipError_t launch_solve_t(const KArgs &a, bool acc64, hipStream_t st, hip
     return e;
 }
 
-hipError_t launch_solve(const KArgs &a, bool fp64, bool acc64, hipStream_t st, hipEvent_t *ev)
+hipError_t launch_solve(const KArgs &a, bool fp64, bool acc64, hipStream_t st, hipEvent_t *ev, int32_t *ran)
 {
     if (fp64) {
         switch (a.objective) {
-        case OBJ_CONTOUR: return launch_solve_t<double, OBJ_CONTOUR>(a, true, st, ev);
-        case OBJ_TRACK: return launch_solve_t<double, OBJ_TRACK>(a, true, st, ev);
-        default: return launch_solve_t<double, OBJ_GATE>(a, true, st, ev);
+        case OBJ_CONTOUR: return launch_solve_t<double, OBJ_CONTOUR>(a, true, st, ev, ran);
+        case OBJ_TRACK: return launch_solve_t<double, OBJ_TRACK>(a, true, st, ev, ran);
+        default: return launch_solve_t<double, OBJ_GATE>(a, true, st, ev, ran);
         }
     }
     switch (a.objective) {
-    case OBJ_CONTOUR: return launch_solve_t<float, OBJ_CONTOUR>(a, acc64, st, ev);
-    case OBJ_TRACK: return launch_solve_t<float, OBJ_TRACK>(a, acc64, st, ev);
-    default: return launch_solve_t<float, OBJ_GATE>(a, acc64, st, ev);
+    case OBJ_CONTOUR: return launch_solve_t<float, OBJ_CONTOUR>(a, acc64, st, ev, ran);
+    case OBJ_TRACK: return launch_solve_t<float, OBJ_TRACK>(a, acc64, st, ev, ran);
+    default: return launch_solve_t<float, OBJ_GATE>(a, acc64, st, ev, ran);
     }
 }
 

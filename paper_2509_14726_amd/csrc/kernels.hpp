@@ -16,8 +16,9 @@ hipError_t launch_request(const double *values, double *d_req, hipStream_t st);
 // Enqueue one MPPI step: sample (with the head), rollout, average (+ tail).
 // acc64 selects binary64 accumulation of the weighted average.
 // When ev is non-null, ev[0..3] are recorded before the sample, rollout and
-// average kernels and after the average kernel.
-hipError_t launch_solve(const KArgs &a, bool fp64, bool acc64, hipStream_t st, hipEvent_t *ev = nullptr);
+// average kernels and after the average kernel.  *ran becomes the MPPI_RAN_*
+// bits of the rollout that was launched.
+hipError_t launch_solve(const KArgs &a, bool fp64, bool acc64, hipStream_t st, hipEvent_t *ev, int32_t *ran);
 
 // Device address of the fixed solve workspace (kScratchBytes, 256-byte
 // aligned) on the current device.  The first call on a device resolves it
@@ -40,7 +41,8 @@ struct BatchLaunch {
     int ctrl_groups;      // grid-stride workgroups of the control-cost kernel (0: no item has the term)
 };
 
-// Enqueue one batched MPPI step over the items described in device memory.
-hipError_t launch_batch(const BArgs &b, const BatchLaunch &L, hipStream_t st);
+// Enqueue one batched MPPI step over the items described in device memory;
+// the MPPI_RAN_* bits of its rollout are added to *ran.
+hipError_t launch_batch(const BArgs &b, const BatchLaunch &L, hipStream_t st, int32_t *ran);
 
 }  // namespace mppi

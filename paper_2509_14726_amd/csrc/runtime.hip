@@ -55,6 +55,7 @@ struct mppi_ctx {
     int n_cu = 256;             // its compute units
     int n_iter = 1;             // MPPI iterations per solve
     bool no_tensor = false;     // the last solve's average drew the samples again
+    int32_t ran = 0;            // MPPI_RAN_* bits of the last solve
     std::string err;
 };
 
@@ -369,7 +370,7 @@ static mppi_status launch_iterations(mppi_ctx *ctx, KArgs a)
     ctx->no_tensor = a.regen != 0;
     for (int it = 0; it < ctx->n_iter; ++it) {
         a.inner = it > 0 ? 1 : 0;
-        HIP_TRY(ctx, launch_solve(a, ctx->fp64, ctx->acc64, ctx->stream, next_events(ctx)));
+        HIP_TRY(ctx, launch_solve(a, ctx->fp64, ctx->acc64, ctx->stream, next_events(ctx), &ctx->ran));
     }
     return MPPI_OK;
 }
@@ -695,6 +696,8 @@ mppi_status mppi_solve(mppi_ctx *ctx, const double x0[13], double t_now, double 
     if (U_out) memcpy(U_out, ctx->h_U, sizeof(double) * 4 * ctx->N);
     return MPPI_OK;
 }
+
+int32_t mppi_layout_ran(const mppi_ctx *ctx) { return ctx ? ctx->ran : 0; }
 
 mppi_status mppi_read_info(mppi_ctx *ctx, mppi_info *info)
 {
@@ -1028,6 +1031,8 @@ struct mppi_batch {
     mppi_batch_cfg cfg{};
     hipGraphExec_t exec[2] = {};  // captured launch sequences: [1] for steps with wide groups
     hipGraph_t graph[2] = {};
+    int32_t graph_ran[2] = {};   // MPPI_RAN_* bits of what they launch
+    int32_t ran = 0;             // and of the last step
     hipEvent_t copy_done = nullptr;
     bool copy_pending = false;
     int n_cu = 256;
@@ -1261,6 +1266,8 @@ mppi_status mppi_batch_create(mppi_ctx *const *ctxs, int32_t n, void *stream, co
     return MPPI_OK;
 }
 
+int32_t mppi_batch_layout_ran(const mppi_batch *b) { return b ? b->ran : 0; }
+
 mppi_status mppi_batch_set_cfg(mppi_batch *b, const mppi_batch_cfg *cfg)
 {
     if (!b || !cfg) return bfail(b, MPPI_E_INVAL, "batch and cfg are required");
@@ -1298,7 +1305,7 @@ static mppi_status enqueue_groups(mppi_batch *b, bool skip_empty, bool wide)
             if (it > 0) ba.table = b->d_table + b->ctxs.size();
             BatchLaunch l = g.launch;
             if (wide) l.draw = true;
-            BHIP_TRY(b, launch_batch(ba, l, b->stream));
+            BHIP_TRY(b, launch_batch(ba, l, b->stream, &b->ran));
         }
     }
     return MPPI_OK;
@@ -1382,6 +1389,7 @@ static mppi_status batch_solve(mppi_batch *b, const int32_t *active, int32_t n_a
     // arithmetic: the same results.
     const bool wide = !b->groups.empty() && b->groups[0].launch.rollout_waves == 4 && !b->fp64 &&
                       most_tiles > 2 * b->n_cu;
+    b->ran = 0;
     if (b->cfg.use_graph) {
         hipGraphExec_t &exec = b->exec[wide ? 1 : 0];
         if (!exec) {
@@ -1392,8 +1400,10 @@ static mppi_status batch_solve(mppi_batch *b, const int32_t *active, int32_t n_a
             if (st != MPPI_OK) { if (graph) (void)hipGraphDestroy(graph); return st; }
             if (e != hipSuccess) return bfail(b, MPPI_E_DEVICE, "graph capture failed: %s", hipGetErrorString(e));
             b->graph[wide ? 1 : 0] = graph;
+            b->graph_ran[wide ? 1 : 0] = b->ran;
             BHIP_TRY(b, hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
         }
+        b->ran = b->graph_ran[wide ? 1 : 0];
         BHIP_TRY(b, hipGraphLaunch(exec, b->stream));
         return MPPI_OK;
     }

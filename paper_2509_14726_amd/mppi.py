@@ -33,7 +33,7 @@ EXPORTS = ["mppi_create", "mppi_destroy", "mppi_solve", "mppi_solve_device",
            "mppi_solve_device_noalloc", "mppi_read_info",
            "mppi_read_samples", "mppi_get_warm", "mppi_set_warm", "mppi_last_error",
            "mppi_status_string", "mppi_plant_step", "mppi_plant_step_rate", "mppi_set_profiling",
-           "mppi_read_profile", "mppi_autotune",
+           "mppi_read_profile", "mppi_autotune", "mppi_layout_ran", "mppi_batch_layout_ran",
            "mppi_batch_create", "mppi_batch_solve_device", "mppi_batch_set_cfg", "mppi_batch_get_cfg",
            "mppi_batch_autotune", "mppi_batch_destroy", "mppi_batch_last_error",
            "mppi_server_create", "mppi_server_submit", "mppi_server_progress", "mppi_server_poll",
@@ -68,6 +68,7 @@ class mppi_params(C.Structure):
 FLAG_EXTERNAL_WORKSPACE = 1
 FLAG_REGEN_AVERAGE = 2
 TUNE_FORCE = 1
+RAN_PAIR, RAN_RATE_PIPE, RAN_WIDE = 1, 2, 4
 
 
 class mppi_problem(C.Structure):
@@ -167,6 +168,10 @@ def _load():
     L.mppi_solve_device.restype = C.c_int
     L.mppi_solve_device_noalloc.argtypes = [_P, _P, _P]
     L.mppi_solve_device_noalloc.restype = C.c_int
+    L.mppi_layout_ran.argtypes = [_P]
+    L.mppi_layout_ran.restype = C.c_int32
+    L.mppi_batch_layout_ran.argtypes = [_P]
+    L.mppi_batch_layout_ran.restype = C.c_int32
     L.mppi_read_info.argtypes = [_P, C.POINTER(mppi_info)]
     L.mppi_read_info.restype = C.c_int
     L.mppi_read_samples.argtypes = [_P, _D, _D]
@@ -374,6 +379,10 @@ class Solver:
         st = lib.mppi_read_info(self.ctx, C.byref(info))
         return st, info.as_dict()
 
+    def layout_ran(self) -> int:
+        """RAN_* bits of the latest solve (mppi_layout_ran)."""
+        return lib.mppi_layout_ran(self.ctx)
+
     def read_samples(self, want_U: bool = False):
         J = np.zeros(self.K)
         U = np.zeros((self.N, self.K, 4)) if want_U else None
@@ -451,6 +460,10 @@ class Batch:
         cfg = mppi_batch_cfg()
         _bcheck(lib.mppi_batch_get_cfg(self.b, C.byref(cfg)), self.b)
         return cfg.as_dict()
+
+    def layout_ran(self) -> int:
+        """RAN_* bits of the latest step (mppi_batch_layout_ran)."""
+        return lib.mppi_batch_layout_ran(self.b)
 
     def autotune(self, d_reqs: int, d_u0s: int, reps: int = 3, cache_path=None, force=False):
         """mppi_batch_autotune: (best launch shape, its mean step ms, whether

@@ -1,0 +1,124 @@
+"""Which rollout a solve ran, at the sizes where the tests of the pair, of the
+rate input's pipeline and of wide batch steps compare two layouts bit for bit:
+the layout under test in one arm, its counterpart in the other."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2509_14726_amd import mppi as M
+from paper_2509_14726_amd import synth
+
+
+def say(*a):
+    print("[gpu-case] layouts", *a, flush=True)
+    sys.stdout.flush()
+
+
+def n_cu():
+    import torch
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def solver(K, N, objective, precision=M.FP32, rate=False, flags=0):
+    over = dict(flags=flags)
+    if rate:
+        over.update(sigma=(8.0,) * 4, sigma_v=5.0, input_model=M.INPUT_RATE, rate_lim=(-10.0, 10.0), dv_lim=(-20.0, 20.0))
+    w = synth.single_solve_workload(K=K, N=N, objective=objective, seed=5, track_seed=3, **{"lambda": 20.0})
+    w["params"] = dict(w["params"], **over)
+    if rate:
+        w["x0"] = np.concatenate([w["x0"], np.full(4, synth.hover_thrust())])
+    sv = M.Solver(w["quad"], w["params"], gates=w["gates"], path=w.get("path"), path_len=w.get("path_len", 0.0),
+                  xref=w.get("xref"), ref_dt=w.get("ref_dt", 0.0), precision=precision)
+    return sv, w
+
+
+def ran(*args, **kw):
+    """(layout bits, report) of one solve."""
+    sv, w = solver(*args, **kw)
+    assert sv.layout_ran() == 0
+    _, _, info = sv.solve(w["x0"])
+    bits = sv.layout_ran()
+    sv.close()
+    return bits, info
+
+
+@pytest.fixture(autouse=True)
+def automatic(monkeypatch):
+    for k in ("MPPI_ROLLOUT_WAVES", "MPPI_ROLLOUT_DRAW"):
+        monkeypatch.delenv(k, raising=False)
+
+
+def test_nothing_solved():
+    assert M.lib.mppi_layout_ran(None) == 0 and M.lib.mppi_batch_layout_ran(None) == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("objective,limit", [("gate", 12), ("contour", 8), ("track", 12)])
+def test_pair(objective, limit, monkeypatch):
+    tile_row = 64 * n_cu()
+    for extra in (0, 70, 37):
+        say("pair", objective, "K", 2 * tile_row + extra)
+        bits, info = ran(2 * tile_row + extra, 2, objective)
+        assert bits == M.RAN_PAIR and info["rollout_waves"] == 1 and info["rollout_draw"] == 0
+    # the last tile count of the pipeline, and both sides of the pair's limit
+    assert ran(2 * tile_row - 1, 2, objective)[0] == 0
+    assert ran(limit * tile_row - 1, 1, objective)[0] == M.RAN_PAIR
+    assert ran(limit * tile_row, 1, objective)[0] == 0
+    monkeypatch.setenv("MPPI_ROLLOUT_WAVES", "1")
+    assert ran(2 * tile_row, 2, objective)[0] == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("objective", ["gate", "contour", "track"])
+def test_pair_in_place_of_the_drawing_wave(objective, monkeypatch):
+    tile_row = 64 * n_cu()
+    K, N = 4 * tile_row + 1000, 256
+    say("pair, large tensor", objective, "K", K, "N", N)
+    assert 16 * K * N > 256 * 2 ** 20
+    for flags in (0, M.FLAG_REGEN_AVERAGE):
+        bits, info = ran(K, N, objective, flags=flags)
+        assert bits == M.RAN_PAIR and info["rollout_draw"] == 1 and info["regen_average"] == (1 if flags else 0)
+    monkeypatch.setenv("MPPI_ROLLOUT_WAVES", "1")
+    bits, info = ran(K, N, objective)
+    assert bits == 0 and info["rollout_draw"] == 1
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", [M.FP32, M.FP64], ids=["fp32", "fp64"])
+@pytest.mark.parametrize("objective", ["gate", "contour", "track"])
+def test_rate_input_pipeline(objective, precision, monkeypatch):
+    say("rate pipeline", objective, precision)
+    fits = precision == M.FP32 or objective != "contour"
+    bits, info = ran(200, 5, objective, precision=precision, rate=True)
+    assert bits == (M.RAN_RATE_PIPE if fits else 0) and info["rollout_waves"] == 1
+    assert ran(64 * n_cu(), 2, objective, precision=precision, rate=True)[0] == 0   # more tiles than CUs
+    monkeypatch.setenv("MPPI_ROLLOUT_WAVES", "1")
+    assert ran(200, 5, objective, precision=precision, rate=True)[0] == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("use_graph", [True, False])
+def test_wide_steps(use_graph, monkeypatch):
+    """The contexts of the wide-step test: all of them, then too few tiles."""
+    import torch
+    monkeypatch.setenv("MPPI_ROLLOUT_WAVES", "4")
+    sizes = [(128 * n_cu() + 70, 5), (8192, 9), (64, 1), (2500, 6)]
+    sw = [solver(K, N, objective) for objective in ("gate", "contour", "track") for K, N in sizes]
+    B = M.Batch([s for s, _ in sw], rollout_waves=4, use_graph=use_graph)
+    assert B.layout_ran() == 0
+    reqs = torch.zeros((len(sw), M.REQ_DOUBLES), dtype=torch.float64, device="cuda")
+    u0s = torch.zeros((len(sw), 4), dtype=torch.float64, device="cuda")
+    for i, (_, w) in enumerate(sw):
+        reqs[i, :13] = torch.from_numpy(w["x0"][:13])
+    torch.cuda.synchronize()
+    say("wide", "graph", use_graph)
+    for _ in range(2):
+        B.solve_device(reqs.data_ptr(), u0s.data_ptr())
+        assert B.layout_ran() == M.RAN_WIDE
+        B.solve_device(reqs.data_ptr(), u0s.data_ptr(), active=[1, 2, 3])
+        assert B.layout_ran() == 0
+    torch.cuda.synchronize()
+    B.close()
+    for s, _ in sw:
+        s.close()
