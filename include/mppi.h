@@ -411,8 +411,11 @@ mppi_status mppi_batch_get_cfg(const mppi_batch *b, mppi_batch_cfg *cfg);
 /* Autotuner cache: a JSON object in the file cache_path, one entry per key
  * "<kind>|<gfx arch>|<objective(s)>|<fp32|fp64>|<size buckets>" (size
  * buckets: floor(log2) of K and N for a context; of the instance count and of
- * sum K*N for a batch), each holding the chosen launch settings and the mean
- * time measured for them.  Written through a temporary file and a rename.
+ * sum K*N for a batch), followed by what else decides a choice: a context's
+ * layout, the iterations per solve, the rate input and the control-cost term
+ * of a batch, floor(log2) of lambda and of the largest sigma (the mean over a
+ * batch), and a number that changes with the kernels.  Each entry holds the
+ * chosen launch settings and the mean time measured for them.  Written through a temporary file and a rename.
  * cache_path NULL: no cache.  MPPI_TUNE_FORCE: time even on a cache hit. */
 #define MPPI_TUNE_FORCE 1
 

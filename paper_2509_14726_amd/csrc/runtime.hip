@@ -116,6 +116,33 @@ static std::string arch_of(int dev)
 
 static int bucket(double x) { return x >= 1.0 ? (int)floor(log2(x)) : 0; }
 
+// Part of every key: choices timed on other kernels are not taken over.  To be
+// raised with every change that moves the candidates against each other.
+constexpr int kGeneration = 2;
+
+// The sharpness of the weights, which decides how many samples the average
+// reads: floor(log2) of the temperature and of the largest noise deviation, the
+// mean over the contexts of a batch.
+struct Sharpness {
+    double lam = 0.0, sig = 0.0;
+    int n = 0;
+    static double scale(double x) { return x > 0.0 ? log2(x) : -1100.0; }
+    void add(const KArgs &a)
+    {
+        double s = a.objective == OBJ_CONTOUR ? a.sigma_v : 0.0;
+        for (int i = 0; i < 4; ++i) s = a.sigma[i] > s ? a.sigma[i] : s;
+        lam += scale(a.lambda);
+        sig += scale(s);
+        ++n;
+    }
+    std::string text() const
+    {
+        char buf[64];
+        snprintf(buf, sizeof buf, "|lam%d|sig%d|gen%d", (int)floor(lam / n), (int)floor(sig / n), kGeneration);
+        return buf;
+    }
+};
+
 static const char *prec_name(bool fp64) { return fp64 ? "fp64" : "fp32"; }
 
 static bool field(const std::string &line, const char *name, double &out)
@@ -793,10 +820,15 @@ mppi_status mppi_autotune(mppi_ctx *ctx, const double *d_req, int32_t reps, cons
         if (out) *out = r;
         return MPPI_OK;
     }
+    // cache key: architecture, objective, precision, sizes, layout, iterations,
+    // sharpness of the weights
+    tune::Sharpness sharp;
+    sharp.add(ctx->args);
     char key[256];
-    snprintf(key, sizeof key, "ctx|%s|%s|%s|K%d|N%d|w%d", tune::arch_of(ctx->device).c_str(),
+    snprintf(key, sizeof key, "ctx|%s|%s|%s|K%d|N%d|w%d%s%s|it%d%s", tune::arch_of(ctx->device).c_str(),
              objective_name(ctx->objective), tune::prec_name(ctx->fp64), tune::bucket(ctx->K), tune::bucket(ctx->N),
-             ctx->args.rollout_waves);
+             ctx->args.rollout_waves, ctx->args.rollout_draw ? "|draw" : "", ctx->args.rollout_pair ? "|pair" : "",
+             ctx->n_iter, sharp.text().c_str());
     tune::Entry e;
     if (!(flags & MPPI_TUNE_FORCE) && tune::load(cache_path, key, e)) {
         ctx->args.regen = e.regen ? 1 : 0;
@@ -1427,12 +1459,14 @@ mppi_status mppi_batch_autotune(mppi_batch *b, const double *d_reqs, double *d_u
     if (from_cache) *from_cache = 0;
     // cache key: architecture, objectives, precision, instance count and
     // total rollout steps; then the rate input, several iterations and the
-    // control-cost term where a context has them
+    // control-cost term where a context has them; the sharpness of the weights
     int objs = 0;
     double kn = 0.0;
+    tune::Sharpness sharp;
     for (const mppi_ctx *c : b->ctxs) {
         objs |= 1 << c->objective;
         kn += (double)c->K * (double)c->N;
+        sharp.add(c->args);
     }
     char key[256];
     snprintf(key, sizeof key, "batch|%s|obj%d|%s|n%d|KN%d%s%s", tune::arch_of(b->ctxs[0]->device).c_str(), objs,
@@ -1441,6 +1475,10 @@ mppi_status mppi_batch_autotune(mppi_batch *b, const double *d_reqs, double *d_u
     if (b->n_iter > 1) {
         const size_t used = strlen(key);
         snprintf(key + used, sizeof key - used, "|it%d", b->n_iter);
+    }
+    {
+        const size_t used = strlen(key);
+        snprintf(key + used, sizeof key - used, "%s", sharp.text().c_str());
     }
     tune::Entry ce;
     if (!(flags & MPPI_TUNE_FORCE) && tune::load(cache_path, key, ce)) {
