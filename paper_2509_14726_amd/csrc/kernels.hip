@@ -3844,8 +3844,12 @@ template <int OBJ, typename Real> __global__ __launch_bounds__(192) void kb_roll
     }
 }
 
+// Rings of 4 steps in binary32 leave LDS for two workgroups on a CU, the bound
+// of four waves per SIMD the registers too (without it 168 and 165 for
+// contouring and tracking: one workgroup.  One context in a batch, K = 20000,
+// N = 50: contouring 96 -> 75 us a step, tracking 82 -> 70).
 template <int OBJ, typename Real, int R>
-__global__ __launch_bounds__(64 * pipe_waves(OBJ, sizeof(Real))) void kb_rollout4(BArgs b)
+__global__ __launch_bounds__(64 * pipe_waves(OBJ, sizeof(Real)), sizeof(Real) == 4 && R == 4 ? 4 : 1) void kb_rollout4(BArgs b)
 {
     __shared__ KArgs s_a;
     __shared__ HeadVals h;
