@@ -57,6 +57,17 @@ __device__ __forceinline__ void store_nt(double4 *p, const double4 v)
 __device__ __forceinline__ void store_nt(float *p, const float v) { __builtin_nontemporal_store(v, p); }
 __device__ __forceinline__ void store_nt(double *p, const double v) { __builtin_nontemporal_store(v, p); }
 
+// Arguments that a batched kernel holds in LDS.  The compiler does not know the
+// address space of a pointer read from there: its accesses would be flat ones,
+// each of which waits for all that went before (a load behind the streaming
+// store of a sample for that store).  in_global() names it.
+struct StagedArgs : KArgs {};
+template <typename Args, typename T> __device__ __forceinline__ T *in_global(const Args &, T *p)
+{
+    if constexpr (std::is_same<Args, StagedArgs>::value) return (T *)(__attribute__((address_space(1))) T *)(uintptr_t)p;
+    else return p;
+}
+
 // ---------------------------------------------------------------- setup
 
 template <typename Real> __global__ void k_setup(KArgs a)
@@ -559,8 +570,8 @@ template <int OBJ, typename Real, bool DRAW> struct DrawLds {
 };
 
 // The shifted warm start of every step, staged once by the NT threads.
-template <int NT, int OBJ, typename Real, bool DRAW, typename Head>
-__device__ __forceinline__ void stage_warm_start(const KArgs &a, int blk, const Head &h, DrawLds<OBJ, Real, DRAW> &lds)
+template <int NT, int OBJ, typename Real, bool DRAW, typename Head, typename Args>
+__device__ __forceinline__ void stage_warm_start(const Args &a, int blk, const Head &h, DrawLds<OBJ, Real, DRAW> &lds)
 {
     typedef typename Vec4<Real>::T R4;
     constexpr bool HAS_V = OBJ == OBJ_CONTOUR;
@@ -569,20 +580,21 @@ __device__ __forceinline__ void stage_warm_start(const KArgs &a, int blk, const 
     const int K = a.K, N = a.N;
     const int shift = h.shift, warm = h.warm;
     const bool rows = a.regen && blk == (K >> 6);
+    const double *const wU = in_global(a, a.wU), *const wV = in_global(a, a.wV);
     for (int k = (int)threadIdx.x; k < N; k += NT) {
         int src = k + shift;
         if (src > N - 1) src = N - 1;
         R4 o;
-        o.x = warm ? (Real)a.wU[4 * src + 0] : (Real)a.hover;
-        o.y = warm ? (Real)a.wU[4 * src + 1] : (Real)a.hover;
-        o.z = warm ? (Real)a.wU[4 * src + 2] : (Real)a.hover;
-        o.w = warm ? (Real)a.wU[4 * src + 3] : (Real)a.hover;
+        o.x = warm ? (Real)wU[4 * src + 0] : (Real)a.hover;
+        o.y = warm ? (Real)wU[4 * src + 1] : (Real)a.hover;
+        o.z = warm ? (Real)wU[4 * src + 2] : (Real)a.hover;
+        o.w = warm ? (Real)wU[4 * src + 3] : (Real)a.hover;
         s_us[k] = o;
-        if (HAS_V) s_vs[k] = warm ? (Real)a.wV[src] : Real(0);
+        if (HAS_V) s_vs[k] = warm ? (Real)wV[src] : Real(0);
         // the weighted average draws the samples again from these rows
         if (rows) {
-            ((R4 *)a.nomU)[k] = o;
-            if (HAS_V) ((Real *)a.nomV)[k] = s_vs[k];
+            in_global(a, (R4 *)a.nomU)[k] = o;
+            if (HAS_V) in_global(a, (Real *)a.nomV)[k] = s_vs[k];
         }
     }
     __syncthreads();
@@ -599,8 +611,8 @@ __device__ __forceinline__ void stage_warm_start(const KArgs &a, int blk, const 
 // NOM: the tile holds the nominal alone (K a multiple of 64) and draws nothing.
 // PART: the whole rollout or one wave's part of a pair.
 template <int OBJ, typename Real, bool DRAW, bool PIPE, bool RATE, bool DRAG, bool NOM, int PART = PART_ALL,
-          typename Head, typename Pair = NoPair>
-__device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const Head &h, DrawLds<OBJ, Real, DRAW> &lds,
+          typename Head, typename Args, typename Pair = NoPair>
+__device__ __forceinline__ void rollout1_steps(const Args &a, int blk, const Head &h, DrawLds<OBJ, Real, DRAW> &lds,
                                                Pair &&pr = Pair())
 {
     typedef typename Vec4<Real>::T R4;
@@ -632,10 +644,10 @@ __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const He
 
         // the inputs (u, V) of step k: drawn (and stored, unless the weighted
         // average draws them again) or read
-        const R4 *urow = nominal ? (const R4 *)a.nomU : (const R4 *)a.ctrl + m;
+        const R4 *urow = in_global(a, nominal ? (const R4 *)a.nomU : (const R4 *)a.ctrl + m);
         const size_t ustride = nominal ? 1 : (size_t)K;
         const Real *vrow = nullptr;
-        if (HAS_V) vrow = nominal ? (const Real *)a.nomV : (const Real *)a.vctrl + m;
+        if (HAS_V) vrow = in_global(a, nominal ? (const Real *)a.nomV : (const Real *)a.vctrl + m);
         const bool keep = DRAW && !a.regen && (PART == PART_ALL ? !nominal : m < K);
         const bool quiet = PART == PART_ALL ? nominal : m >= K;
         const uint32_t s_solve = h.s, key0 = a.seed_lo, key1 = a.seed_hi;
@@ -645,8 +657,8 @@ __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const He
         const Real sig0 = in_vgpr(quiet ? Real(0) : (Real)a.sigma[0]), sig1 = in_vgpr(quiet ? Real(0) : (Real)a.sigma[1]);
         const Real sig2 = in_vgpr(quiet ? Real(0) : (Real)a.sigma[2]), sig3 = in_vgpr(quiet ? Real(0) : (Real)a.sigma[3]);
         const Real sigv = in_vgpr(quiet ? Real(0) : (Real)a.sigma_v);
-        R4 *rec = (R4 *)a.ctrl + m;                 // the sample's record, advanced step by step
-        Real *vrec = HAS_V ? (Real *)a.vctrl + m : nullptr;
+        R4 *rec = in_global(a, (R4 *)a.ctrl + m);      // the sample's record, advanced step by step
+        Real *vrec = HAS_V ? in_global(a, (Real *)a.vctrl + m) : nullptr;
         auto put = [&](const R4 &uo, const Real vo) {
             if (PART == PART_COSTS) {
                 if (keep) {
@@ -681,7 +693,7 @@ __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const He
         };
 
         // gate objective state
-        const Real *gtab = (const Real *)a.gates_r;
+        const Real *gtab = in_global(a, (const Real *)a.gates_r);
         GateRegs<Real> gt, g0r;
         int g = 0, passes = 0;
         Real q_near = 0, r_near2 = 0, half = 0;
@@ -700,8 +712,8 @@ __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const He
         Real rdt[4];
         for (int i = 0; i < 4; ++i) rdt[i] = in_vgpr((Real)(a.R_dT[i] / (a.dt * a.dt)));
         const int i0 = h.i0, R = a.R;
-        const Real *xref = (const Real *)a.xref_r;
-        const Real *path = (const Real *)a.path_r;
+        const Real *xref = in_global(a, (const Real *)a.xref_r);
+        const Real *path = in_global(a, (const Real *)a.path_r);
         // arc length theta = th_hi + th_lo (th_lo stays 0 in binary64)
         Real th_hi = 0, th_lo = 0;
         Real ds = 0, inv_ds = 0, L = 0, q_l = 0, q_c = 0, qw[3] = {}, r_dv = 0, mu = 0;
@@ -827,7 +839,7 @@ __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const He
                 const Real bz = p[2] - g0r.cz;
                 const Real d2 = bx * bx + by * by + bz * bz;
                 if (d2 < r_near2) term += q_near * d2;  // Eq. (7), current gate
-                if (nominal) a.front8[k] = (bx * g0r.nx + by * g0r.ny) < Real(0);
+                if (nominal) in_global(a, a.front8)[k] = (bx * g0r.nx + by * g0r.ny) < Real(0);
             } else if (TRACK) {
                 int r = i0 + k;
                 if (r > R - 1) r = R - 1;
@@ -1124,22 +1136,22 @@ __device__ __forceinline__ void rollout1_steps(const KArgs &a, int blk, const He
         if (GATE && nominal) {
             const Real bx = p[0] - g0r.cx;
             const Real by = p[1] - g0r.cy;
-            a.front8[N] = (bx * g0r.nx + by * g0r.ny) < Real(0);
+            in_global(a, a.front8)[N] = (bx * g0r.nx + by * g0r.ny) < Real(0);
         }
         Jfinal = PIPE ? ((J0.value() + J1.value()) + J2.value()) + J.value() : J.value();
-        if (nominal) a.cur->J_nom = (double)Jfinal;
-        else if (PART == PART_ALL || m < K) ((Real *)a.J)[m] = Jfinal;
+        if (nominal) in_global(a, a.cur)->J_nom = (double)Jfinal;
+        else if (PART == PART_ALL || m < K) in_global(a, (Real *)a.J)[m] = Jfinal;
     }
     // smallest finite sample cost of the tile
-    store_tile_min(Jfinal, active && !nominal && isfinite(Jfinal), a.tmin, blk);
+    store_tile_min(Jfinal, active && !nominal && isfinite(Jfinal), in_global(a, (Real *)a.tmin), blk);
 }
 
 // Drag is a launch constant: the variant is chosen once.  A last tile that
 // holds the nominal alone skips the draws: where K fills the chip's waves to
 // the last lane it runs after them, alone (K = 262144, N = 200: 523 -> 454 us
 // a solve).
-template <int OBJ, typename Real, bool DRAW, bool PIPE, bool RATE, typename Head>
-__device__ __forceinline__ void rollout1_body(const KArgs &a, int blk, const Head &h, DrawLds<OBJ, Real, DRAW> &lds)
+template <int OBJ, typename Real, bool DRAW, bool PIPE, bool RATE, typename Head, typename Args>
+__device__ __forceinline__ void rollout1_body(const Args &a, int blk, const Head &h, DrawLds<OBJ, Real, DRAW> &lds)
 {
     const bool nom = DRAW && !RATE && blk * 64 == a.K;
     constexpr bool NOM = DRAW && !RATE;
@@ -3746,7 +3758,7 @@ __device__ __forceinline__ int advance_item(const int32_t *prefix, int n, int u,
 
 // Stage the kernel arguments of an item's context in LDS, with the item's
 // request and output pointers.
-__device__ __forceinline__ void stage_args(KArgs &s_a, int &s_ctx, const BArgs &b, int item)
+__device__ __forceinline__ void stage_args(StagedArgs &s_a, int &s_ctx, const BArgs &b, int item)
 {
     const BatchItem it = b.items[item];
     if (it.ctx != s_ctx) {
@@ -3778,7 +3790,7 @@ __device__ __forceinline__ void stage_args(KArgs &s_a, int &s_ctx, const BArgs &
 // are taken from a device queue in order (longest horizons first).
 template <typename Real, bool HAS_V> __global__ __launch_bounds__(256) void kb_sample(BArgs b)
 {
-    __shared__ KArgs s_a;
+    __shared__ StagedArgs s_a;
     __shared__ int s_ctx, s_unit;
     if (threadIdx.x == 0) s_ctx = -1;
     if (blockIdx.x == 0 && threadIdx.x == 0) b.desc->queue = 0u;
@@ -3799,7 +3811,7 @@ template <typename Real, bool HAS_V> __global__ __launch_bounds__(256) void kb_s
 template <int OBJ, typename Real, int WAVES> __global__ __launch_bounds__(64 * WAVES) void kb_rollout(BArgs b)
 {
     __shared__ DrawLds<OBJ, Real, false> lds;
-    __shared__ KArgs s_a;
+    __shared__ StagedArgs s_a;
     __shared__ int s_ctx, s_unit;
     if (threadIdx.x == 0) s_ctx = -1;
     const int n = b.desc->n, total = b.desc->n_tiles;
@@ -3823,7 +3835,7 @@ template <int OBJ, typename Real, int WAVES> __global__ __launch_bounds__(64 * W
 
 template <int OBJ, typename Real> __global__ __launch_bounds__(192) void kb_rollout3(BArgs b)
 {
-    __shared__ KArgs s_a;
+    __shared__ StagedArgs s_a;
     __shared__ HeadVals h;
     __shared__ int s_ctx, s_unit;
     if (threadIdx.x == 0) s_ctx = -1;
@@ -3851,7 +3863,7 @@ template <int OBJ, typename Real> __global__ __launch_bounds__(192) void kb_roll
 template <int OBJ, typename Real, int R>
 __global__ __launch_bounds__(64 * pipe_waves(OBJ, sizeof(Real)), sizeof(Real) == 4 && R == 4 ? 4 : 1) void kb_rollout4(BArgs b)
 {
-    __shared__ KArgs s_a;
+    __shared__ StagedArgs s_a;
     __shared__ HeadVals h;
     __shared__ int s_ctx, s_unit;
     if (threadIdx.x == 0) s_ctx = -1;
@@ -3877,15 +3889,19 @@ __global__ __launch_bounds__(64 * pipe_waves(OBJ, sizeof(Real)), sizeof(Real) ==
 // whose tiles fill the chip several times over: a tile then costs the issue
 // of one wave's operations instead of the pipeline's latency and handoffs.
 // The contexts of a launch share the input model.
-// Two waves per SIMD with all their registers where the pipeline's sums or
-// the thrust chain need them (four waves spill: 64 served drones, half of them
-// on thrust rates, 694 -> 614 us), else four (half as many workgroups: 256
-// uneven instances 1281 -> 1427 us).
+// As many waves per SIMD as spill no register (a spilled value is read behind
+// the sample's store and waits for it, in every step): two where the
+// pipeline's sums or the thrust chain need the registers, else three.  Against
+// four, with flat accesses: 256 uneven instances 1231 -> 1201 us; where a SIMD
+// has one tile or two and nothing hides the wait: 12 contexts of K = 4096,
+// N = 100, tracking 246 -> 190, gate 228 -> 175 (235 by a sample kernel and a
+// rollout that reads its samples); 32 contouring contexts of K = 4096, N = 100
+// 404 -> 304.
 template <int OBJ, typename Real, bool PIPE, bool RATE>
-__global__ __launch_bounds__(64, RATE || PIPE ? 2 : 4) void kb_rollout_draw(BArgs b)
+__global__ __launch_bounds__(64, draw_waves(RATE || PIPE)) void kb_rollout_draw(BArgs b)
 {
     __shared__ DrawLds<OBJ, Real, true> lds;
-    __shared__ KArgs s_a;
+    __shared__ StagedArgs s_a;
     __shared__ HeadVals h;
     __shared__ int s_ctx, s_unit;
     if (threadIdx.x == 0) s_ctx = -1;
@@ -3910,7 +3926,7 @@ __global__ __launch_bounds__(64, RATE || PIPE ? 2 : 4) void kb_rollout_draw(BArg
 // without the term are skipped.
 template <typename Real, bool HAS_V> __global__ __launch_bounds__(64) void kb_ctrl_cost(BArgs b)
 {
-    __shared__ KArgs s_a;
+    __shared__ StagedArgs s_a;
     __shared__ int s_ctx;
     if (threadIdx.x == 0) s_ctx = -1;
     __syncthreads();
@@ -3934,7 +3950,7 @@ template <typename Real, typename Acc, bool HAS_V> __global__ __launch_bounds__(
     // 1223 -> 1213 us), else final_loads()
     constexpr int UR = S > 1 ? 1 : final_loads<Real>;
     __shared__ FinalLds<Acc, HAS_V, S> lds;
-    __shared__ KArgs s_a;
+    __shared__ StagedArgs s_a;
     __shared__ int s_ctx;
     if (threadIdx.x == 0) s_ctx = -1;
     if (blockIdx.x == 0 && threadIdx.x == 0) {

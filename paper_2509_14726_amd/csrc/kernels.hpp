@@ -25,6 +25,10 @@ hipError_t launch_solve(const KArgs &a, bool fp64, bool acc64, hipStream_t st, h
 // (with that device current) and later calls return the cached address.
 hipError_t scratch_address(void **ptr);
 
+// Waves per SIMD of the batched one-wave rollouts that draw (binary32): few,
+// where the pipeline's arithmetic or the rate input needs the registers.
+constexpr int draw_waves(bool few) { return few ? 2 : 3; }
+
 // Launch shape of one batch group.
 struct BatchLaunch {
     int objective;

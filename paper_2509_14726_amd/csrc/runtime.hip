@@ -1135,8 +1135,8 @@ static hipError_t resolve_cfg(mppi_batch *b)
     // persistent rollout workgroups: what fits one CU times the CUs (one
     // pipelined workgroup with rings of 8 steps or in binary64, two with rings
     // of 4 in binary32, one three-wave, two two-wave, eight one-wave that read
-    // their samples, sixteen that draw them)
-    int per_cu = b->fp64 ? 8 : 16;
+    // their samples, four times the waves per SIMD of those that draw them)
+    int per_cu = b->fp64 ? 8 : 4 * draw_waves(false);
     if (waves == 4) per_cu = (!b->fp64 && ring == 4) ? 2 : 1;
     else if (waves == 3) per_cu = 1;
     else if (waves == 2) per_cu = 2;
@@ -1153,9 +1153,8 @@ static hipError_t resolve_cfg(mppi_batch *b)
         // sample pass)
         g.launch.draw = waves == 1 && !b->fp64;
         g.launch.rollout_groups = rg;
-        // one-wave workgroups: four per SIMD; two where the kernel is built for two
         g.launch.draw_groups = c.rollout_groups > 0 && waves == 1 ? c.rollout_groups
-                                                                  : (waves == 4 || g.rate ? 8 : 16) * cu;
+                                                                  : 4 * draw_waves(waves == 4 || g.rate) * cu;
         g.launch.sample_groups = sg;
         // kFinalThreads-thread workgroups, two per CU
         g.launch.final_groups = 2 * b->n_cu;

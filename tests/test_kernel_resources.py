@@ -64,3 +64,13 @@ def test_two_pipelines_with_short_rings_share_a_cu(kernels, objective):
         waves = k["max_flat_workgroup_size"] // 64
         assert 4 * waves_per_simd(k) >= 2 * waves
         assert 2 * k["group_segment_fixed_size"] <= LDS_PER_CU
+
+
+@pytest.mark.parametrize("pipe,rate", [(0, 0), (1, 0), (0, 1)])
+@pytest.mark.parametrize("objective", [0, 1, 2])
+def test_batched_drawing_rollouts_spill_nothing(kernels, objective, pipe, rate):
+    """A spilled value would be read behind the sample's store in every step.
+    The grid counts three (two with PIPE or the rate input) waves per SIMD."""
+    for k in matching(kernels, r"kb_rollout_drawILi%dEfLb%dELb%dE" % (objective, pipe, rate)).values():
+        assert k["vgpr_spill_count"] == 0 and k["private_segment_fixed_size"] == 0
+        assert waves_per_simd(k) >= (2 if pipe or rate else 3)
