@@ -297,6 +297,7 @@ mppi_status mppi_solve_device_noalloc(mppi_ctx *ctx, const double *d_req, double
 #define MPPI_RAN_PAIR 1       /* rollout_waves 1 as a pair of waves per tile        */
 #define MPPI_RAN_RATE_PIPE 2  /* the rate input's one wave as a pipeline            */
 #define MPPI_RAN_WIDE 4       /* a batch's pipelines as drawing one-wave rollouts   */
+#define MPPI_RAN_MIXED 8      /* contexts of both input models in one launch        */
 int32_t mppi_layout_ran(const mppi_ctx *ctx);
 
 /* Wait for the context stream and copy the report of the latest solve. */
@@ -353,7 +354,7 @@ mppi_status mppi_read_profile(mppi_ctx *ctx, double mean_ms[3], int32_t *n_solve
  * context has the term (one unit per context and 64-sample tile), and a
  * grid-stride weighted-average kernel (one unit per context and horizon
  * step), repeated n_iter times (the contexts' shared n_iter), per group
- * of contexts sharing an objective, accumulation type and input model.
+ * of contexts sharing an objective and accumulation type.
  * One-wave rollouts of binary32 contexts draw their samples themselves (no
  * sample kernel), and one block of the average takes several horizon steps;
  * pipelined binary32 contexts run one-wave rollouts of the same results in a

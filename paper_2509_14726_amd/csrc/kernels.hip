@@ -3888,7 +3888,11 @@ __global__ __launch_bounds__(64 * pipe_waves(OBJ, sizeof(Real)), sizeof(Real) ==
 // sample kernel.  PIPE: with the pipelined rollout's arithmetic, for launches
 // whose tiles fill the chip several times over: a tile then costs the issue
 // of one wave's operations instead of the pipeline's latency and handoffs.
-// The contexts of a launch share the input model.
+// RATE: the launch holds contexts of the rate input; MIXED: beside those of the
+// thrust input (12 contexts of K = 4096, N = 50 and three objectives, half of
+// them on rates: 575 us a step with a launch per input model, 297 together; a
+// launch of rates alone does without the branch: 64 contouring contexts of
+// K = 8192 509 -> 489).
 // As many waves per SIMD as spill no register (a spilled value is read behind
 // the sample's store and waits for it, in every step): two where the
 // pipeline's sums or the thrust chain need the registers, else three.  Against
@@ -3897,7 +3901,7 @@ __global__ __launch_bounds__(64 * pipe_waves(OBJ, sizeof(Real)), sizeof(Real) ==
 // N = 100, tracking 246 -> 190, gate 228 -> 175 (235 by a sample kernel and a
 // rollout that reads its samples); 32 contouring contexts of K = 4096, N = 100
 // 404 -> 304.
-template <int OBJ, typename Real, bool PIPE, bool RATE>
+template <int OBJ, typename Real, bool PIPE, bool RATE, bool MIXED = false>
 __global__ __launch_bounds__(64, draw_waves(RATE || PIPE)) void kb_rollout_draw(BArgs b)
 {
     __shared__ DrawLds<OBJ, Real, true> lds;
@@ -3918,7 +3922,8 @@ __global__ __launch_bounds__(64, draw_waves(RATE || PIPE)) void kb_rollout_draw(
         const int blk = u - b.tile_prefix[item];
         compute_head<OBJ == OBJ_CONTOUR>(s_a, h);
         if (blk == 0 && threadIdx.x == 0) publish_head(s_a, h);
-        rollout1_body<OBJ, Real, true, PIPE, RATE>(s_a, blk, h, lds);
+        if (RATE && (!MIXED || s_a.input_model == INPUT_RATE)) rollout1_body<OBJ, Real, true, PIPE, RATE>(s_a, blk, h, lds);
+        else rollout1_body<OBJ, Real, true, PIPE, false>(s_a, blk, h, lds);
     }
 }
 
@@ -3981,6 +3986,9 @@ static hipError_t launch_batch_t(const BArgs &b, const BatchLaunch &L, hipStream
             if (L.rollout_waves == 4) {
                 *ran |= MPPI_RAN_WIDE;
                 hipLaunchKernelGGL((kb_rollout_draw<OBJ, Real, true, false>), dim3(L.draw_groups), dim3(64), 0, st, b);
+            } else if (L.rate && L.thrust) {
+                *ran |= MPPI_RAN_MIXED;
+                hipLaunchKernelGGL((kb_rollout_draw<OBJ, Real, false, true, true>), dim3(L.draw_groups), dim3(64), 0, st, b);
             } else if (L.rate)
                 hipLaunchKernelGGL((kb_rollout_draw<OBJ, Real, false, true>), dim3(L.draw_groups), dim3(64), 0, st, b);
             else

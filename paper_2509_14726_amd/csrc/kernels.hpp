@@ -37,7 +37,7 @@ struct BatchLaunch {
     int ring_steps;       // rings of the pipeline (binary32): 8 steps, one workgroup per CU; 4, two
     bool draw;            // one-wave rollouts that draw their samples (binary32); with rollout_waves 4
                           // in the pipeline's arithmetic
-    bool rate;            // the group's contexts take the rate input
+    bool rate, thrust;    // the group has contexts of the rate input, of the thrust input
     int rollout_groups;   // persistent rollout workgroups
     int draw_groups;      // the same for the drawing one-wave rollouts
     int sample_groups;    // grid-stride workgroups of the sample kernel

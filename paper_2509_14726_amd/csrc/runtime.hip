@@ -1035,7 +1035,7 @@ namespace {
 
 struct BatchGroup {
     int objective = 0;
-    bool acc64 = false, rate = false;
+    bool acc64 = false, rate = false, thrust = false;
     std::vector<int> regs;       // registered contexts of this group
     int cap = 0;                 // = regs.size()
     size_t bytes = 0;
@@ -1147,6 +1147,7 @@ static hipError_t resolve_cfg(mppi_batch *b)
         g.launch.fp64 = b->fp64;
         g.launch.acc64 = g.acc64;
         g.launch.rate = g.rate;
+        g.launch.thrust = g.thrust;
         g.launch.rollout_waves = waves;
         g.launch.ring_steps = ring;
         // one-wave rollouts draw their samples themselves in binary32 (no
@@ -1226,24 +1227,23 @@ mppi_status mppi_batch_create(mppi_ctx *const *ctxs, int32_t n, void *stream, co
         release_batch(b);
         return bfail(nullptr, MPPI_E_DEVICE, "hipEventCreate failed");
     }
-    // groups by (objective, accumulation type, input model)
+    // groups by (objective, accumulation type); both input models together, so
+    // that their tiles share the chip instead of one launch waiting for the other
     b->group_of.resize(n);
     b->tiles_of.resize(n);
     for (int i = 0; i < n; ++i) {
         const mppi_ctx *c = ctxs[i];
         int gi = -1;
         for (size_t g = 0; g < b->groups.size(); ++g)
-            if (b->groups[g].objective == c->objective && b->groups[g].acc64 == c->acc64 &&
-                b->groups[g].rate == (c->args.input_model == INPUT_RATE))
-                gi = (int)g;
+            if (b->groups[g].objective == c->objective && b->groups[g].acc64 == c->acc64) gi = (int)g;
         if (gi < 0) {
             b->groups.emplace_back();
             b->groups.back().objective = c->objective;
             b->groups.back().acc64 = c->acc64;
-            b->groups.back().rate = c->args.input_model == INPUT_RATE;
             gi = (int)b->groups.size() - 1;
         }
         b->groups[gi].regs.push_back(i);
+        (c->args.input_model == INPUT_RATE ? b->groups[gi].rate : b->groups[gi].thrust) = true;
         b->groups[gi].ctrl = b->groups[gi].ctrl || c->args.ctrl_cost != 0.0;
         b->group_of[i] = gi;
         b->tiles_of[i] = (c->K + 1 + 63) / 64;

@@ -122,3 +122,24 @@ def test_wide_steps(use_graph, monkeypatch):
     B.close()
     for s, _ in sw:
         s.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rates", [(False, True), (True, True), (False, False)])
+def test_both_input_models_share_a_launch(rates, monkeypatch):
+    import torch
+    sw = [solver(700, 6, "gate", rate=r) for r in rates]
+    B = M.Batch([s for s, _ in sw], rollout_waves=1)
+    reqs = torch.zeros((2, M.REQ_DOUBLES), dtype=torch.float64, device="cuda")
+    u0s = torch.zeros((2, 4), dtype=torch.float64, device="cuda")
+    for i, (_, w) in enumerate(sw):
+        reqs[i, :13] = torch.from_numpy(w["x0"][:13])
+        reqs[i, M.REQ_THRUST:M.REQ_THRUST + 4] = synth.hover_thrust()
+    torch.cuda.synchronize()
+    say("input models", rates)
+    B.solve_device(reqs.data_ptr(), u0s.data_ptr())
+    torch.cuda.synchronize()
+    assert B.layout_ran() == (M.RAN_MIXED if rates == (False, True) else 0)
+    B.close()
+    for s, _ in sw:
+        s.close()

@@ -71,6 +71,6 @@ def test_two_pipelines_with_short_rings_share_a_cu(kernels, objective):
 def test_batched_drawing_rollouts_spill_nothing(kernels, objective, pipe, rate):
     """A spilled value would be read behind the sample's store in every step.
     The grid counts three (two with PIPE or the rate input) waves per SIMD."""
-    for k in matching(kernels, r"kb_rollout_drawILi%dEfLb%dELb%dE" % (objective, pipe, rate)).values():
+    for k in matching(kernels, r"kb_rollout_drawILi%dEfLb%dELb%dELb[01]E" % (objective, pipe, rate)).values():
         assert k["vgpr_spill_count"] == 0 and k["private_segment_fixed_size"] == 0
         assert waves_per_simd(k) >= (2 if pipe or rate else 3)
