@@ -298,6 +298,7 @@ mppi_status mppi_solve_device_noalloc(mppi_ctx *ctx, const double *d_req, double
 #define MPPI_RAN_RATE_PIPE 2  /* the rate input's one wave as a pipeline            */
 #define MPPI_RAN_WIDE 4       /* a batch's pipelines as drawing one-wave rollouts   */
 #define MPPI_RAN_MIXED 8      /* contexts of both input models in one launch        */
+#define MPPI_RAN_SINGLE 16    /* binary32 averages of one horizon step per block    */
 int32_t mppi_layout_ran(const mppi_ctx *ctx);
 
 /* Wait for the context stream and copy the report of the latest solve. */
@@ -352,15 +353,16 @@ mppi_status mppi_read_profile(mppi_ctx *ctx, double mean_ms[3], int32_t *n_solve
  * persistent rollout kernel that pulls 64-sample tiles from a device queue in
  * order of decreasing horizon, a grid-stride control-cost kernel where a
  * context has the term (one unit per context and 64-sample tile), and a
- * grid-stride weighted-average kernel (one unit per context and horizon
- * step), repeated n_iter times (the contexts' shared n_iter), per group
+ * grid-stride weighted-average kernel (one unit per context and horizon step
+ * or, with binary32 sums where a group's steps outnumber the CUs, several of
+ * them), repeated n_iter times (the contexts' shared n_iter), per group
  * of contexts sharing an objective and accumulation type.
  * One-wave rollouts of binary32 contexts draw their samples themselves (no
- * sample kernel), and one block of the average takes several horizon steps;
- * pipelined binary32 contexts run one-wave rollouts of the same results in a
- * step whose tiles exceed what the chip holds.  Grids are fixed and the work
- * description lives in device memory, so the sequence is captured once in a
- * HIP graph (cfg.use_graph) and replayed for any subset.
+ * sample kernel); pipelined binary32 contexts run one-wave rollouts of the
+ * same results where a group's tiles exceed what the chip holds.  Grids are
+ * fixed and the work description lives in device memory, so the sequences for
+ * those sizes are captured in HIP graphs at the first step (cfg.use_graph) and
+ * replayed for any subset.
  * Each context's result, report and warm-start state are the same as those
  * of mppi_solve_device on that context alone with the same rollout layout. */
 typedef struct mppi_batch mppi_batch;

@@ -117,8 +117,9 @@ struct KArgs {
     double *U_host;             // N x 4
 };
 
-// Horizon steps of one block of the batched average: what two blocks' LDS
-// holds on a CU (binary32 sums: 72 KB, 68 KB contouring).
+// Horizon steps of one block of the batched average, where the steps outnumber
+// the CUs: what two blocks' LDS holds on a CU (binary32 sums: 72 KB, 68 KB
+// contouring).
 constexpr int final_steps(bool has_v, size_t acc) { return acc == 8 ? 1 : (has_v ? 3 : 4); }
 
 // Whether the rate input's pipelined rollout fits the LDS.
@@ -164,7 +165,7 @@ struct BatchDesc {
     int32_t n;                  // items
     int32_t n_sample_units;     // sum over items of ceil((K+1)/256)
     int32_t n_tiles;            // sum over items of ceil((K+1)/64)
-    int32_t n_steps;            // units of the weighted-average kernel: sum over items of ceil(N / final_steps)
+    int32_t n_steps;            // units of the weighted-average kernel: sum over items of ceil(N / steps of a block)
     uint32_t queue;             // rollout tile counter, reset by the sample kernel
     uint32_t sample_queue;      // sample unit counter (both also reset by the
                                 // average kernel, for the step's next iteration)

@@ -3945,15 +3945,23 @@ template <typename Real, bool HAS_V> __global__ __launch_bounds__(64) void kb_ct
     }
 }
 
-// One unit per (item, final_steps() steps) of the weighted average.  The sample and rollout
+// One unit per (item, S steps) of the weighted average.  The sample and rollout
 // kernels of this step have finished, so their work queues are reset here
 // for the next iteration of the step.
-template <typename Real, typename Acc, bool HAS_V> __global__ __launch_bounds__(kFinalThreads) void kb_final(BArgs b)
+// S = final_steps() where the steps outnumber the CUs, else 1: blocks of several
+// steps would then leave CUs without one (4 contexts of K = 16384, N = 50, all
+// weights alive: 35 us in 52 blocks, 12 in 200; 3 of K = 8192, N = 100, sharp
+// weights: 5 us more in 300 blocks than in 75).  With so few blocks binary32
+// sums read all samples, without waiting for their weights (samples that are
+// drawn again cost only where they weigh something).
+// (With both averages in one kernel its registers spill: 12 us a launch -> 17.)
+template <typename Real, typename Acc, bool HAS_V, int S, bool REGEN>
+__global__ __launch_bounds__(kFinalThreads) void kb_final(BArgs b)
 {
-    constexpr int S = final_steps(HAS_V, sizeof(Acc));
     // loads in flight: of several steps one (two spill: 256 uneven instances
     // 1223 -> 1213 us), else final_loads()
     constexpr int UR = S > 1 ? 1 : final_loads<Real>;
+    constexpr bool SKIP = REGEN || S > 1 || sizeof(Acc) == 8;
     __shared__ FinalLds<Acc, HAS_V, S> lds;
     __shared__ StagedArgs s_a;
     __shared__ int s_ctx;
@@ -3969,12 +3977,17 @@ template <typename Real, typename Acc, bool HAS_V> __global__ __launch_bounds__(
     for (int u = blockIdx.x; u < total; u += gridDim.x) {
         item = advance_item(b.step_prefix, n, u, item);
         stage_args(s_a, s_ctx, b, item);
-        // a context whose rollout left no sample tensor: draw the samples again
-        const int k = S * (u - b.step_prefix[item]);
-        if (s_a.regen) final_body<Real, Acc, HAS_V, true, UR, true, S>(s_a, k, lds);
-        else final_body<Real, Acc, HAS_V, false, UR, true, S>(s_a, k, lds);
+        final_body<Real, Acc, HAS_V, REGEN, UR, SKIP, S>(s_a, S * (u - b.step_prefix[item]), lds);
         __syncthreads();
     }
+}
+
+// REGEN: the rollouts left no sample tensor, draw the samples again.
+template <typename Real, typename Acc, bool HAS_V, int S>
+static void launch_batch_average(const BArgs &b, const BatchLaunch &L, hipStream_t st)
+{
+    if (L.regen) hipLaunchKernelGGL((kb_final<Real, Acc, HAS_V, S, true>), dim3(L.final_groups), dim3(kFinalThreads), 0, st, b);
+    else hipLaunchKernelGGL((kb_final<Real, Acc, HAS_V, S, false>), dim3(L.final_groups), dim3(kFinalThreads), 0, st, b);
 }
 
 template <typename Real, int OBJ>
@@ -4015,10 +4028,16 @@ static hipError_t launch_batch_t(const BArgs &b, const BatchLaunch &L, hipStream
         hipLaunchKernelGGL((kb_rollout<OBJ, Real, 1>), dim3(L.rollout_groups), dim3(64), 0, st, b);
     if (L.ctrl_groups > 0)
         hipLaunchKernelGGL((kb_ctrl_cost<Real, HAS_V>), dim3(L.ctrl_groups), dim3(64), 0, st, b);
-    if (L.acc64 || sizeof(Real) == 8)
-        hipLaunchKernelGGL((kb_final<Real, double, HAS_V>), dim3(L.final_groups), dim3(kFinalThreads), 0, st, b);
-    else
-        hipLaunchKernelGGL((kb_final<Real, float, HAS_V>), dim3(L.final_groups), dim3(kFinalThreads), 0, st, b);
+    if (L.acc64 || sizeof(Real) == 8) {
+        launch_batch_average<Real, double, HAS_V, final_steps(HAS_V, 8)>(b, L, st);
+    } else if constexpr (sizeof(Real) == 4) {
+        if (L.single) {
+            *ran |= MPPI_RAN_SINGLE;
+            launch_batch_average<Real, float, HAS_V, 1>(b, L, st);
+        } else {
+            launch_batch_average<Real, float, HAS_V, final_steps(HAS_V, 4)>(b, L, st);
+        }
+    }
     return hipGetLastError();
 }
 

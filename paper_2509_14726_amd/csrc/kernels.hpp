@@ -42,6 +42,8 @@ struct BatchLaunch {
     int draw_groups;      // the same for the drawing one-wave rollouts
     int sample_groups;    // grid-stride workgroups of the sample kernel
     int final_groups;     // grid-stride workgroups of the weighted-average kernel
+    bool regen;           // it draws the samples again
+    bool single;          // its units are single horizon steps, else final_steps() of them
     int ctrl_groups;      // grid-stride workgroups of the control-cost kernel (0: no item has the term)
 };
 

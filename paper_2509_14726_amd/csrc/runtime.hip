@@ -1045,7 +1045,25 @@ struct BatchGroup {
     BatchLaunch launch{};
     int active = 0;              // items in the current step
     bool ctrl = false;           // a context of the group adds the control-cost term
+    int64_t tiles = 0, steps = 0;  // of all its contexts: rollout tiles, horizon steps
+    int variant = 0;             // what the size of the current step decides: V_WIDE, V_SINGLE
 };
+
+// A captured launch sequence of a whole step.
+struct Captured {
+    std::vector<int> variants;   // of the groups
+    hipGraph_t graph = nullptr;
+    hipGraphExec_t exec = nullptr;
+    int32_t ran = 0;             // MPPI_RAN_* bits of what it launches
+};
+// sequences kept by a batch
+constexpr size_t kCaptured = 32;
+
+// a pipelined group with more tiles than the chip holds pipelines (two per CU):
+// one-wave rollouts in the pipeline's arithmetic, the same results
+constexpr int V_WIDE = 1;
+// the average's blocks take one horizon step each
+constexpr int V_SINGLE = 2;
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
@@ -1061,10 +1079,8 @@ struct mppi_batch {
     std::vector<KArgs> h_table;  // host copy of d_table
     std::vector<BatchGroup> groups;
     mppi_batch_cfg cfg{};
-    hipGraphExec_t exec[2] = {};  // captured launch sequences: [1] for steps with wide groups
-    hipGraph_t graph[2] = {};
-    int32_t graph_ran[2] = {};   // MPPI_RAN_* bits of what they launch
-    int32_t ran = 0;             // and of the last step
+    std::vector<Captured> captured;
+    int32_t ran = 0;             // MPPI_RAN_* bits of the last step
     hipEvent_t copy_done = nullptr;
     bool copy_pending = false;
     int n_cu = 256;
@@ -1097,12 +1113,11 @@ static mppi_status bfail(mppi_batch *b, mppi_status s, const char *fmt, ...)
 
 static void drop_graph(mppi_batch *b)
 {
-    for (int w = 0; w < 2; ++w) {
-        if (b->exec[w]) (void)hipGraphExecDestroy(b->exec[w]);
-        if (b->graph[w]) (void)hipGraphDestroy(b->graph[w]);
-        b->exec[w] = nullptr;
-        b->graph[w] = nullptr;
+    for (auto &c : b->captured) {
+        if (c.exec) (void)hipGraphExecDestroy(c.exec);
+        if (c.graph) (void)hipGraphDestroy(c.graph);
     }
+    b->captured.clear();
 }
 
 // Resolve automatic fields of the launch shape for this batch.
@@ -1157,6 +1172,7 @@ static hipError_t resolve_cfg(mppi_batch *b)
         g.launch.draw_groups = c.rollout_groups > 0 && waves == 1 ? c.rollout_groups
                                                                   : 4 * draw_waves(waves == 4 || g.rate) * cu;
         g.launch.sample_groups = sg;
+        g.launch.regen = regen != 0;
         // kFinalThreads-thread workgroups, two per CU
         g.launch.final_groups = 2 * b->n_cu;
         // one-wave workgroups of the control-cost term, eight per CU
@@ -1248,6 +1264,8 @@ mppi_status mppi_batch_create(mppi_ctx *const *ctxs, int32_t n, void *stream, co
         b->group_of[i] = gi;
         b->tiles_of[i] = (c->K + 1 + 63) / 64;
         b->total_tiles += b->tiles_of[i];
+        b->groups[gi].tiles += b->tiles_of[i];
+        b->groups[gi].steps += c->N;
     }
     // device table of kernel arguments; whether the average draws the samples
     // again is the batch's choice (its layout is its own).  With several
@@ -1324,21 +1342,95 @@ mppi_status mppi_batch_get_cfg(const mppi_batch *b, mppi_batch_cfg *cfg)
     return MPPI_OK;
 }
 
+// The variant of a group's step with this many rollout tiles and horizon steps.
+static int variant_of(const mppi_batch *b, const BatchGroup &g, int64_t tiles, int64_t steps)
+{
+    const bool wide = g.launch.rollout_waves == 4 && !b->fp64 && tiles > 2 * b->n_cu;
+    const bool single = final_steps(g.objective == OBJ_CONTOUR, g.acc64 ? 8 : 4) == 1 || steps <= b->n_cu;
+    return (wide ? V_WIDE : 0) | (single ? V_SINGLE : 0);
+}
+
 // The launch sequence of one step: n_iter iterations, the later ones reading
 // the inner copy of the argument table (no shift, the first iteration's last
 // applied input), each group's kernels in turn.
-static mppi_status enqueue_groups(mppi_batch *b, bool skip_empty, bool wide)
+static mppi_status enqueue_groups(mppi_batch *b, bool skip_empty, const std::vector<int> &variants, int32_t *ran)
 {
     for (int it = 0; it < b->n_iter; ++it) {
-        for (auto &g : b->groups) {
+        for (size_t i = 0; i < b->groups.size(); ++i) {
+            const BatchGroup &g = b->groups[i];
             if (skip_empty && g.active == 0) continue;
             BArgs ba = g.bargs;
             if (it > 0) ba.table = b->d_table + b->ctxs.size();
             BatchLaunch l = g.launch;
-            if (wide) l.draw = true;
-            BHIP_TRY(b, launch_batch(ba, l, b->stream, &b->ran));
+            if (variants[i] & V_WIDE) l.draw = true;
+            l.single = (variants[i] & V_SINGLE) != 0;
+            BHIP_TRY(b, launch_batch(ba, l, b->stream, ran));
         }
     }
+    return MPPI_OK;
+}
+
+static mppi_status capture(mppi_batch *b, const std::vector<int> &variants)
+{
+    Captured c;
+    c.variants = variants;
+    BHIP_TRY(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
+    const mppi_status st = enqueue_groups(b, false, variants, &c.ran);
+    hipError_t e = hipStreamEndCapture(b->stream, &c.graph);
+    if (st == MPPI_OK && e == hipSuccess) e = hipGraphInstantiate(&c.exec, c.graph, nullptr, nullptr, 0);
+    if (st != MPPI_OK || e != hipSuccess) {
+        if (c.graph) (void)hipGraphDestroy(c.graph);
+        return st != MPPI_OK ? st : bfail(b, MPPI_E_DEVICE, "graph capture failed: %s", hipGetErrorString(e));
+    }
+    b->captured.push_back(c);
+    return MPPI_OK;
+}
+
+// The captured sequence of the current step.  The first step captures all
+// that the batch's subsets can need, so that none is captured while requests
+// wait: each group's variants lie between those of its smallest step (one
+// tile, one horizon step) and of all its contexts at once.  (Groups that differ
+// so much that these are too many are captured as they are met.)
+static mppi_status captured_step(mppi_batch *b, const Captured **out)
+{
+    std::vector<int> now;
+    for (const auto &g : b->groups) now.push_back(g.variant);
+    auto find = [&]() -> const Captured * {
+        for (const auto &c : b->captured)
+            if (c.variants == now) return &c;
+        return nullptr;
+    };
+    if ((*out = find())) return MPPI_OK;
+    if (b->captured.empty()) {
+        std::vector<std::vector<int>> all(1);
+        for (const auto &g : b->groups) {
+            const int few = variant_of(b, g, 0, 0), most = variant_of(b, g, g.tiles, g.steps);
+            std::vector<std::vector<int>> next;
+            for (int v = 0; v < 4; ++v) {
+                if (((v ^ few) & ~(few ^ most)) != 0) continue;   // a bit that no subset changes
+                for (auto k : all) {
+                    k.push_back(v);
+                    next.push_back(k);
+                }
+            }
+            all.swap(next);
+            if (all.size() > kCaptured / 2) break;
+        }
+        if (all[0].size() == b->groups.size() && all.size() <= kCaptured / 2) {
+            for (const auto &k : all) {
+                const mppi_status st = capture(b, k);
+                if (st != MPPI_OK) return st;
+            }
+        }
+        if ((*out = find())) return MPPI_OK;
+    }
+    if (b->captured.size() >= kCaptured) {
+        BHIP_TRY(b, hipStreamSynchronize(b->stream));
+        drop_graph(b);
+    }
+    const mppi_status st = capture(b, now);
+    if (st != MPPI_OK) return st;
+    *out = &b->captured.back();
     return MPPI_OK;
 }
 
@@ -1357,7 +1449,6 @@ static mppi_status batch_solve(mppi_batch *b, const int32_t *active, int32_t n_a
     std::vector<char> seen(n, 0);
     for (auto &g : b->groups) g.active = 0;
     std::vector<std::vector<std::pair<int, int>>> per(b->groups.size());  // (registered index, slot)
-    int64_t most_tiles = 0;      // of one group's launch
     for (int i = 0; i < n_active; ++i) {
         const int r = active ? active[i] : i;
         if (r < 0 || r >= n) return bfail(b, MPPI_E_INVAL, "active[%d]=%d outside [0, %d)", i, r, n);
@@ -1386,7 +1477,13 @@ static mppi_status batch_solve(mppi_batch *b, const int32_t *active, int32_t n_a
         int32_t *tp = (int32_t *)(h + ((const char *)g.bargs.tile_prefix - d));
         int32_t *ap = (int32_t *)(h + ((const char *)g.bargs.step_prefix - d));
         int64_t s_units = 0, t_units = 0, a_units = 0;
-        const int per_block = final_steps(g.objective == OBJ_CONTOUR, g.acc64 || b->fp64 ? 8 : 4);
+        int64_t tiles = 0, steps = 0;
+        for (const auto &x : lst) {
+            tiles += b->tiles_of[x.first];
+            steps += b->ctxs[x.first]->N;
+        }
+        g.variant = variant_of(b, g, tiles, steps);
+        const int per_block = g.variant & V_SINGLE ? 1 : final_steps(g.objective == OBJ_CONTOUR, g.acc64 ? 8 : 4);
         sp[0] = tp[0] = ap[0] = 0;
         for (size_t j = 0; j < lst.size(); ++j) {
             const mppi_ctx *c = b->ctxs[lst[j].first];
@@ -1406,7 +1503,6 @@ static mppi_status batch_solve(mppi_batch *b, const int32_t *active, int32_t n_a
         desc->n = (int32_t)lst.size();
         desc->n_sample_units = (int32_t)s_units;
         desc->n_tiles = (int32_t)t_units;
-        if (t_units > most_tiles) most_tiles = t_units;
         desc->n_steps = (int32_t)a_units;
         desc->queue = 0u;
         desc->sample_queue = 0u;
@@ -1415,30 +1511,18 @@ static mppi_status batch_solve(mppi_batch *b, const int32_t *active, int32_t n_a
     }
     BHIP_TRY(b, hipEventRecord(b->copy_done, b->stream));
     b->copy_pending = true;
-    // Pipelined contexts in a step with more tiles than the chip holds
-    // pipelines (two per CU) run one-wave rollouts in the pipeline's
-    // arithmetic: the same results.
-    const bool wide = !b->groups.empty() && b->groups[0].launch.rollout_waves == 4 && !b->fp64 &&
-                      most_tiles > 2 * b->n_cu;
     b->ran = 0;
     if (b->cfg.use_graph) {
-        hipGraphExec_t &exec = b->exec[wide ? 1 : 0];
-        if (!exec) {
-            BHIP_TRY(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-            mppi_status st = enqueue_groups(b, false, wide);
-            hipGraph_t graph = nullptr;
-            hipError_t e = hipStreamEndCapture(b->stream, &graph);
-            if (st != MPPI_OK) { if (graph) (void)hipGraphDestroy(graph); return st; }
-            if (e != hipSuccess) return bfail(b, MPPI_E_DEVICE, "graph capture failed: %s", hipGetErrorString(e));
-            b->graph[wide ? 1 : 0] = graph;
-            b->graph_ran[wide ? 1 : 0] = b->ran;
-            BHIP_TRY(b, hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
-        }
-        b->ran = b->graph_ran[wide ? 1 : 0];
-        BHIP_TRY(b, hipGraphLaunch(exec, b->stream));
+        const Captured *c = nullptr;
+        const mppi_status st = captured_step(b, &c);
+        if (st != MPPI_OK) return st;
+        BHIP_TRY(b, hipGraphLaunch(c->exec, b->stream));
+        b->ran = c->ran;
         return MPPI_OK;
     }
-    return enqueue_groups(b, true, wide);
+    std::vector<int> variants;
+    for (const auto &g : b->groups) variants.push_back(g.variant);
+    return enqueue_groups(b, true, variants, &b->ran);
 }
 
 extern "C" {

@@ -68,7 +68,7 @@ class mppi_params(C.Structure):
 FLAG_EXTERNAL_WORKSPACE = 1
 FLAG_REGEN_AVERAGE = 2
 TUNE_FORCE = 1
-RAN_PAIR, RAN_RATE_PIPE, RAN_WIDE, RAN_MIXED = 1, 2, 4, 8
+RAN_PAIR, RAN_RATE_PIPE, RAN_WIDE, RAN_MIXED, RAN_SINGLE = 1, 2, 4, 8, 16
 
 
 class mppi_problem(C.Structure):

@@ -115,9 +115,9 @@ def test_wide_steps(use_graph, monkeypatch):
     say("wide", "graph", use_graph)
     for _ in range(2):
         B.solve_device(reqs.data_ptr(), u0s.data_ptr())
-        assert B.layout_ran() == M.RAN_WIDE
+        assert B.layout_ran() & M.RAN_WIDE
         B.solve_device(reqs.data_ptr(), u0s.data_ptr(), active=[1, 2, 3])
-        assert B.layout_ran() == 0
+        assert not B.layout_ran() & M.RAN_WIDE
     torch.cuda.synchronize()
     B.close()
     for s, _ in sw:
@@ -139,7 +139,7 @@ def test_both_input_models_share_a_launch(rates, monkeypatch):
     say("input models", rates)
     B.solve_device(reqs.data_ptr(), u0s.data_ptr())
     torch.cuda.synchronize()
-    assert B.layout_ran() == (M.RAN_MIXED if rates == (False, True) else 0)
+    assert bool(B.layout_ran() & M.RAN_MIXED) == (rates == (False, True))
     B.close()
     for s, _ in sw:
         s.close()
