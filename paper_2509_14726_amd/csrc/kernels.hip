@@ -3405,13 +3405,21 @@ __device__ __forceinline__ double wave_sum(double v)
 // above J_min) is neither read nor drawn: it adds nothing to any sum, so the
 // result is the same bit for bit.  With sharp weights (lambda = 1 at the
 // benchmark's noise) almost no sample is read: K = 262144, N = 200, binary64
-// sums: 157 -> 48 us; with all weights alive the samples of a round are
-// still in flight while the previous round is summed.  Used wherever a thread
+// sums: 157 -> 48 us.  Used wherever a thread
 // has several rounds of samples; with one round the samples are loaded at
 // once with the costs, which saves a round trip to memory.
 // A round is final_loads samples a thread (binary64: four spill, K = 8192,
 // N = 100: 59.3 us a solve against 54.2).
 template <typename Real> constexpr int final_loads = sizeof(Real) == 8 ? 2 : 4;
+// A block of whose first round at least one sample in sixteen weighs something
+// (the samples of a solve are alike, so all blocks find the same) reads all its
+// samples: the conditional loads of skipping are waited for one by one.
+// Binary32 samples with binary64 sums, skipping -> reading all: contouring with
+// all weights alive K = 131072, N = 20 111 -> 98 us a solve, K = 500000
+// 330 -> 279 (107 and 310 before samples were skipped); gate, one in ten
+// alive, K = 500000 249 -> 240.  Fewer samples (binary32 sums) and binary64
+// samples lose nothing worth it by skipping.
+constexpr int kDenseLanes = 4;
 template <typename Real> constexpr Real kWeightCut = sizeof(Real) == 4 ? Real(105) : Real(750);
 
 // S: horizon steps k .. k + S - 1 in one block.  The weights depend on the
@@ -3431,6 +3439,8 @@ __device__ __forceinline__ void final_body(const KArgs &a, int k, FinalLds<Acc, 
     constexpr int NT = kFinalThreads, NWV = NT / 64;
     typedef typename Vec4<Real>::T R4;
     static_assert(SKIP || S == 1, "several steps share the weights of a round");
+    constexpr bool DENSE = SKIP && !REGEN && sizeof(Real) < sizeof(Acc);
+    __shared__ int s_live[DENSE ? NWV : 1];
     auto &s_part = lds.part;
     auto &s_tot = lds.tot;
 
@@ -3590,6 +3600,61 @@ __device__ __forceinline__ void final_body(const KArgs &a, int k, FinalLds<Acc, 
                 }
             }
         };
+        // All samples, two a round: no load depends on a weight, so
+        // the next round's are in flight while this one is summed.
+        auto dense_rounds = [&] {
+            constexpr int D = 2;
+            struct Round { R4 u[D]; Real v[D]; };
+            auto load_costs = [&](const int m0, Real *Jr) {
+#pragma unroll
+                for (int i = 0; i < D; ++i) Jr[i] = J[min(m0 + NT * i, K - 1)];
+            };
+            auto weigh = [&](const int m0, Real *Jr) {
+#pragma unroll
+                for (int i = 0; i < D; ++i) {
+                    const Real wr = exp(-(Jr[i] - jmin) * inv_lambda);
+                    Jr[i] = m0 + NT * i < K && isfinite(Jr[i]) ? wr : Real(0);
+                }
+            };
+            auto load = [&](const int m0, Round &r) {
+#pragma unroll
+                for (int i = 0; i < D; ++i) {
+                    const int m = min(m0 + NT * i, K - 1);
+                    r.u[i] = ctrl[m];
+                    if (HAS_V) r.v[i] = vctrl[m];
+                }
+            };
+            auto add = [&](const Real *wr, const Round &r) {
+#pragma unroll
+                for (int i = 0; i < D; ++i) {
+                    const Acc wa = (Acc)wr[i];
+                    v[0] += wa * (Acc)r.u[i].x;
+                    v[1] += wa * (Acc)r.u[i].y;
+                    v[2] += wa * (Acc)r.u[i].z;
+                    v[3] += wa * (Acc)r.u[i].w;
+                    if (HAS_V) v[C - 1] += wa * (Acc)r.v[i];
+                    v[C] += wa;
+                    v[C + 1] += wa * wa;
+                }
+            };
+            constexpr int step = NT * D;
+            Real w0[D], w1[D];
+            Round r0, r1;
+            load_costs(tid, w0);
+            load_costs(tid + step, w1);
+            load(tid, r0);
+            for (int r = 0; r < K; r += 2 * step) {     // (the same for every thread)
+                const int m0 = tid + r, m1 = m0 + step, m2 = m1 + step;
+                weigh(m0, w0);
+                load(m1, r1);
+                add(w0, r0);
+                load_costs(m2, w0);
+                weigh(m1, w1);
+                load(m2, r0);
+                add(w1, r1);
+                load_costs(m2 + step, w1);
+            }
+        };
         // the costs two rounds ahead, the samples one step or round ahead of
         // the sums; two rounds unrolled so that both buffers stay in registers
         Weights wa, wb;
@@ -3599,8 +3664,21 @@ __device__ __forceinline__ void final_body(const KArgs &a, int k, FinalLds<Acc, 
         const int rounds = (K + step - 1) / step;   // the same for every thread
         costs(tid + step, Jb);
         sort_out(Jm, wa);
-        fetch(tid, 0, wa, x[0]);
-        for (int r = 0; r < rounds; r += 2) {
+        bool dense = false;
+        if constexpr (DENSE) {
+            int n_live = 0;
+#pragma unroll
+            for (int i = 0; i < UR; ++i) n_live += __builtin_popcountll(__builtin_amdgcn_ballot_w64(wa.live[i]));
+            if (lane == 0) s_live[wv] = n_live;
+            __syncthreads();
+            n_live = 0;
+#pragma unroll
+            for (int i = 0; i < NWV; ++i) n_live += s_live[i];
+            dense = n_live >= kDenseLanes * UR * NWV;
+            if (dense) dense_rounds();
+        }
+        if (!dense) fetch(tid, 0, wa, x[0]);
+        for (int r = 0; r < rounds && !dense; r += 2) {
             const int m0 = tid + r * step, m1 = m0 + step, m2 = m1 + step;
             costs(m2, Jm);
 #pragma unroll
