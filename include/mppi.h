@@ -378,9 +378,17 @@ typedef struct {
                                   0: automatic (binary32: 4 for at most two
                                   64-sample tiles per CU, else 1; binary64: 4
                                   for at most one, 2 for at most two, else 1;
-                                  the same rule picks a context's layout) */
-    int32_t rollout_groups;    /* persistent rollout workgroups; 0: automatic    */
-    int32_t sample_groups;     /* workgroups of the sample and reduction kernels;
+                                  the same rule picks a context's layout).
+                                  With 4 and the automatic rollout_groups, a
+                                  group of more tiles than the chip holds
+                                  pipelines runs binary32 one-wave rollouts of
+                                  the same results (MPPI_RAN_WIDE)              */
+    int32_t rollout_groups;    /* persistent rollout workgroups (one-wave rollouts
+                                  that draw: at most what fits); 0, or the number
+                                  that mppi_batch_get_cfg then reports: automatic.
+                                  Another number holds pipelines to themselves   */
+    int32_t sample_groups;     /* workgroups of the sample kernel (two-wave
+                                  rollouts, and one-wave ones in binary64);
                                   0: automatic                                   */
     int32_t use_graph;         /* 1: capture the launch sequence in a HIP graph  */
     int32_t regen_average;     /* 1: with three- or four-wave rollouts, no sample
@@ -423,10 +431,10 @@ mppi_status mppi_batch_get_cfg(const mppi_batch *b, mppi_batch_cfg *cfg);
 #define MPPI_TUNE_FORCE 1
 
 /* Autotuner: time every candidate launch shape (rollout waves x persistent
- * rollout workgroups x reduction workgroups, and with three- or four-wave
- * rollouts the stored and the regenerating average) over `reps` steps of the
- * whole batch with the given requests, keep the fastest, and report it and
- * its mean step time in ms; on a cache hit (no MPPI_TUNE_FORCE) apply the
+ * rollout workgroups x sample workgroups where a sample kernel runs, and with
+ * three- or four-wave rollouts the stored and the regenerating average) over
+ * `reps` steps of the whole batch with the given requests, keep the fastest, and
+ * report it and its mean step time in ms; on a cache hit (no MPPI_TUNE_FORCE) apply the
  * cached shape and time nothing (*best_ms: the cached time, *from_cache 1).
  * The timed solves are real solves (they write d_u0s), but the warm-start
  * state and report of every context are restored afterwards. */

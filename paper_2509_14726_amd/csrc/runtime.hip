@@ -1080,12 +1080,14 @@ struct mppi_batch {
     std::vector<BatchGroup> groups;
     mppi_batch_cfg cfg{};
     std::vector<Captured> captured;
+    bool own_groups = false;     // cfg names a number of rollout workgroups that is not the automatic one
     int32_t ran = 0;             // MPPI_RAN_* bits of the last step
     hipEvent_t copy_done = nullptr;
     bool copy_pending = false;
     int n_cu = 256;
     int total_tiles = 0;
     bool has_rate = false;       // a context takes the rate input: one-wave rollouts only
+    bool has_thrust = false;     // a context takes the thrust input
     bool any_ctrl = false;       // a context adds the control-cost term: the tensor is kept
     int n_iter = 1;              // MPPI iterations per step, shared by the contexts
     std::string err;
@@ -1155,7 +1157,10 @@ static hipError_t resolve_cfg(mppi_batch *b)
     if (waves == 4) per_cu = (!b->fp64 && ring == 4) ? 2 : 1;
     else if (waves == 3) per_cu = 1;
     else if (waves == 2) per_cu = 2;
-    int rg = c.rollout_groups > 0 ? c.rollout_groups : per_cu * cu;
+    // (given as the automatic number it is the automatic one: what get_cfg
+    // reports can be set again and changes nothing)
+    b->own_groups = c.rollout_groups > 0 && c.rollout_groups != per_cu * cu;
+    int rg = b->own_groups ? c.rollout_groups : per_cu * cu;
     int sg = c.sample_groups > 0 ? c.sample_groups : 4 * b->n_cu;
     for (auto &g : b->groups) {
         g.launch.objective = g.objective;
@@ -1169,8 +1174,9 @@ static hipError_t resolve_cfg(mppi_batch *b)
         // sample pass)
         g.launch.draw = waves == 1 && !b->fp64;
         g.launch.rollout_groups = rg;
-        g.launch.draw_groups = c.rollout_groups > 0 && waves == 1 ? c.rollout_groups
-                                                                  : 4 * draw_waves(waves == 4 || g.rate) * cu;
+        // the drawing kernels: no more than what fits
+        g.launch.draw_groups = 4 * draw_waves(waves == 4 || g.rate) * cu;
+        if (waves == 1) g.launch.draw_groups = std::min(g.launch.draw_groups, rg);
         g.launch.sample_groups = sg;
         g.launch.regen = regen != 0;
         // kFinalThreads-thread workgroups, two per CU
@@ -1221,7 +1227,7 @@ mppi_status mppi_batch_create(mppi_ctx *const *ctxs, int32_t n, void *stream, co
     b->ctxs.assign(ctxs, ctxs + n);
     b->fp64 = ctxs[0]->fp64;
     for (int i = 0; i < n; ++i) {
-        b->has_rate = b->has_rate || ctxs[i]->args.input_model == MPPI_INPUT_RATE;
+        (ctxs[i]->args.input_model == MPPI_INPUT_RATE ? b->has_rate : b->has_thrust) = true;
         b->any_ctrl = b->any_ctrl || ctxs[i]->args.ctrl_cost != 0.0;
     }
     b->n_iter = ctxs[0]->n_iter;
@@ -1345,7 +1351,7 @@ mppi_status mppi_batch_get_cfg(const mppi_batch *b, mppi_batch_cfg *cfg)
 // The variant of a group's step with this many rollout tiles and horizon steps.
 static int variant_of(const mppi_batch *b, const BatchGroup &g, int64_t tiles, int64_t steps)
 {
-    const bool wide = g.launch.rollout_waves == 4 && !b->fp64 && tiles > 2 * b->n_cu;
+    const bool wide = g.launch.rollout_waves == 4 && !b->fp64 && !b->own_groups && tiles > 2 * b->n_cu;
     const bool single = final_steps(g.objective == OBJ_CONTOUR, g.acc64 ? 8 : 4) == 1 || steps <= b->n_cu;
     return (wide ? V_WIDE : 0) | (single ? V_SINGLE : 0);
 }
@@ -1577,10 +1583,13 @@ mppi_status mppi_batch_autotune(mppi_batch *b, const double *d_reqs, double *d_u
     std::vector<mppi_batch_cfg> cand;
     const int cu = b->n_cu;
     for (int waves = 1; waves <= (b->has_rate ? 1 : 4); ++waves) {
-        const int rg_mult[] = {1, 2, 4, 8, 16};
+        // what fits a CU: one or two LDS rings, else so many waves
+        const int fit = waves >= 2 ? 2 : (b->fp64 ? 8 : 4 * draw_waves(!b->has_thrust));
+        const bool samples = waves == 2 || (waves == 1 && b->fp64);   // a sample kernel runs
+        const int rg_mult[] = {1, 2, 4, 8, 12};
         for (int rm : rg_mult) {
-            if (waves >= 2 && rm > 2) continue;  // one or two LDS rings fit one CU
-            for (int sm : {1, 4})
+            if (rm > fit) continue;
+            for (int sm : samples ? std::vector<int>{1, 4} : std::vector<int>{4})
                 for (int regen = 0; regen <= (waves >= 3 && !b->any_ctrl ? 1 : 0); ++regen)
                     cand.push_back(mppi_batch_cfg{waves, rm * cu, sm * cu, saved.use_graph, regen});
         }

@@ -143,3 +143,39 @@ def test_both_input_models_share_a_launch(rates, monkeypatch):
     B.close()
     for s, _ in sw:
         s.close()
+
+
+@pytest.mark.gpu
+def test_a_number_of_rollout_workgroups_holds_the_pipeline(monkeypatch):
+    """A batch with more tiles than pipelines: wide with the automatic number of
+    rollout workgroups, also when that number is set again, pipelines with
+    another one; the same results either way."""
+    import torch
+    monkeypatch.setenv("MPPI_ROLLOUT_WAVES", "4")
+    sizes = [(128 * n_cu() + 70, 5), (3000, 9)]
+    reqs = torch.zeros((2, M.REQ_DOUBLES), dtype=torch.float64, device="cuda")
+    out = []
+    for how in ("automatic", "as reported", "others"):
+        sw = [solver(K, N, "gate") for K, N in sizes]
+        u0s = torch.zeros((2, 4), dtype=torch.float64, device="cuda")
+        for i, (_, w) in enumerate(sw):
+            reqs[i, :13] = torch.from_numpy(w["x0"][:13])
+        torch.cuda.synchronize()
+        B = M.Batch([s for s, _ in sw], rollout_waves=4, rollout_groups=100 if how == "others" else 0)
+        if how == "as reported":
+            cfg = B.get_cfg()
+            B.set_cfg(**dict(cfg, use_graph=True, regen_average=False))
+            assert B.get_cfg() == cfg
+        say("rollout workgroups", how)
+        B.solve_device(reqs.data_ptr(), u0s.data_ptr())
+        torch.cuda.synchronize()
+        assert B.get_cfg()["rollout_groups"] == 100 if how == "others" else B.get_cfg()["rollout_groups"] > 100
+        assert bool(B.layout_ran() & M.RAN_WIDE) == (how != "others")
+        out.append((u0s.cpu().numpy(), [s.read_samples()[0] for s, _ in sw]))
+        B.close()
+        for s, _ in sw:
+            s.close()
+    for u0, J in out[1:]:
+        np.testing.assert_array_equal(u0, out[0][0])
+        for a, b in zip(J, out[0][1]):
+            np.testing.assert_array_equal(a, b)
