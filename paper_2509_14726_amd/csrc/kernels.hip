@@ -439,28 +439,15 @@ template <typename Real, bool HAS_V> __global__ __launch_bounds__(256) void k_sa
     sample_body<Real, HAS_V>(a, blockIdx.x, k0, min(a.N, k0 + kSampleSteps));
 }
 
-// The head and the nominal's clipped inputs, for a rollout that draws its
-// samples itself (one-wave layout): one block.
-template <typename Real, bool HAS_V> __global__ __launch_bounds__(256) void k_head(KArgs a)
+// The head, for a rollout that draws its samples itself (one-wave layout): one
+// block.
+template <bool CONTOUR> __global__ __launch_bounds__(256) void k_head(KArgs a)
 {
-    typedef typename Vec4<Real>::T R4;
     __shared__ HeadVals h;
-    compute_head(a, h);
+    compute_head<CONTOUR>(a, h);
     if (threadIdx.x == 0) {
         publish_head(a, h);
         a.cur->J_nom = 0.0;
-    }
-    const Real tmin = (Real)a.t_min, tmax = (Real)a.t_max;
-    for (int k = threadIdx.x; k < a.N; k += blockDim.x) {
-        int src = k + h.shift;
-        if (src > a.N - 1) src = a.N - 1;
-        R4 o;
-        o.x = clampT(h.warm ? (Real)a.wU[4 * src + 0] : (Real)a.hover, tmin, tmax);
-        o.y = clampT(h.warm ? (Real)a.wU[4 * src + 1] : (Real)a.hover, tmin, tmax);
-        o.z = clampT(h.warm ? (Real)a.wU[4 * src + 2] : (Real)a.hover, tmin, tmax);
-        o.w = clampT(h.warm ? (Real)a.wU[4 * src + 3] : (Real)a.hover, tmin, tmax);
-        ((R4 *)a.nomU)[k] = o;
-        if (HAS_V) ((Real *)a.nomV)[k] = clampT(h.warm ? (Real)a.wV[src] : Real(0), Real(0), (Real)a.v_max);
     }
 }
 
@@ -4197,7 +4184,7 @@ static hipError_t launch_solve_t(const KArgs &a, bool acc64, hipStream_t st, hip
     // a one-wave rollout that draws its samples (binary32) needs only the head first
     const bool draw = sizeof(Real) == 4 && a.rollout_draw && !a.rollout_pair;
     if (draw) {
-        if constexpr (sizeof(Real) == 4) hipLaunchKernelGGL((k_head<Real, HAS_V>), dim3(1), dim3(256), 0, st, a);
+        if constexpr (sizeof(Real) == 4) hipLaunchKernelGGL(k_head<HAS_V>, dim3(1), dim3(256), 0, st, a);
     } else if (a.rollout_waves < 3 && !a.rate_pipe && !a.rollout_pair) {
         hipLaunchKernelGGL((k_sample<Real, HAS_V>), gs, dim3(256), 0, st, a);
     }
