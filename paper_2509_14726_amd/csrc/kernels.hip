@@ -4160,18 +4160,18 @@ static hipError_t launch_average_t(const KArgs &a, hipStream_t st)
     // at most eight, else (and in binary64, whose registers hold half as
     // many) rounds of final_loads with the next round's loads in flight; the
     // accumulation order, and so the result, is the same either way
-    const bool one_round = sizeof(Real) == 4 && a.K <= 8 * kFinalThreads;
-    if (a.regen) {
-        if (one_round)
-            hipLaunchKernelGGL((k_final<Real, Acc, HAS_V, true, 8, false>), dim3(a.N), dim3(kFinalThreads), 0, st, a);
-        else
-            hipLaunchKernelGGL((k_final<Real, Acc, HAS_V, true, final_loads<Real>, true>), dim3(a.N), dim3(kFinalThreads), 0, st, a);
-    } else {
-        if (one_round)
-            hipLaunchKernelGGL((k_final<Real, Acc, HAS_V, false, 8, false>), dim3(a.N), dim3(kFinalThreads), 0, st, a);
-        else
-            hipLaunchKernelGGL((k_final<Real, Acc, HAS_V, false, final_loads<Real>, true>), dim3(a.N), dim3(kFinalThreads), 0, st, a);
+    if constexpr (sizeof(Real) == 4) {
+        if (a.K <= 8 * kFinalThreads) {
+            // (K < 65536 takes binary32 sums)
+            if (a.regen) hipLaunchKernelGGL((k_final<Real, Real, HAS_V, true, 8, false>), dim3(a.N), dim3(kFinalThreads), 0, st, a);
+            else hipLaunchKernelGGL((k_final<Real, Real, HAS_V, false, 8, false>), dim3(a.N), dim3(kFinalThreads), 0, st, a);
+            return hipGetLastError();
+        }
     }
+    if (a.regen)
+        hipLaunchKernelGGL((k_final<Real, Acc, HAS_V, true, final_loads<Real>, true>), dim3(a.N), dim3(kFinalThreads), 0, st, a);
+    else
+        hipLaunchKernelGGL((k_final<Real, Acc, HAS_V, false, final_loads<Real>, true>), dim3(a.N), dim3(kFinalThreads), 0, st, a);
     return hipGetLastError();
 }
 
@@ -4224,8 +4224,9 @@ static hipError_t launch_solve_t(const KArgs &a, bool acc64, hipStream_t st, hip
     if (a.ctrl_cost != 0.0)
         hipLaunchKernelGGL((k_ctrl_cost<Real, HAS_V>), dim3(a.n_tiles), dim3(64), 0, st, a);
     if (ev) (void)hipEventRecord(ev[2], st);
-    hipError_t e = (acc64 || sizeof(Real) == 8) ? launch_average_t<Real, double, HAS_V>(a, st)
-                                                : launch_average_t<Real, float, HAS_V>(a, st);
+    hipError_t e;
+    if constexpr (sizeof(Real) == 8) e = launch_average_t<Real, double, HAS_V>(a, st);
+    else e = acc64 ? launch_average_t<Real, double, HAS_V>(a, st) : launch_average_t<Real, float, HAS_V>(a, st);
     if (ev) (void)hipEventRecord(ev[3], st);
     return e;
 }

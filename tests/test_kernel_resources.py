@@ -74,3 +74,11 @@ def test_batched_drawing_rollouts_spill_nothing(kernels, objective, pipe, rate):
     for k in matching(kernels, r"kb_rollout_drawILi%dEfLb%dELb%dELb[01]E" % (objective, pipe, rate)).values():
         assert k["vgpr_spill_count"] == 0 and k["private_segment_fixed_size"] == 0
         assert waves_per_simd(k) >= (2 if pipe or rate else 3)
+
+
+def test_no_kernels_that_nothing_launches(kernels):
+    """Binary64 samples always take binary64 sums, and rounds of loads; all of a
+    thread's samples at once are loaded up to 8192 binary32 samples, below the
+    65536 from which sums are binary64."""
+    assert not [k for k in kernels if re.search(r"k_finalId[^d]|kb_finalId[^d]", k)]
+    assert not [k for k in kernels if re.search(r"k_finalI(d|fd).*Li8E", k)]
