@@ -359,7 +359,8 @@ mppi_status mppi_read_profile(mppi_ctx *ctx, double mean_ms[3], int32_t *n_solve
  * of contexts sharing an objective and accumulation type.
  * One-wave rollouts of binary32 contexts draw their samples themselves (no
  * sample kernel); pipelined binary32 contexts run one-wave rollouts of the
- * same results where a group's tiles exceed what the chip holds.  Grids are
+ * same results where a group has more than three tiles per CU (six with rings
+ * of 4 steps).  Grids are
  * fixed and the work description lives in device memory, so the sequences for
  * those sizes are captured in HIP graphs at the first step (cfg.use_graph) and
  * replayed for any subset.
@@ -380,9 +381,9 @@ typedef struct {
                                   for at most one, 2 for at most two, else 1;
                                   the same rule picks a context's layout).
                                   With 4 and the automatic rollout_groups, a
-                                  group of more tiles than the chip holds
-                                  pipelines runs binary32 one-wave rollouts of
-                                  the same results (MPPI_RAN_WIDE)              */
+                                  binary32 group of many tiles per CU runs
+                                  one-wave rollouts of the same results
+                                  (MPPI_RAN_WIDE)                               */
     int32_t rollout_groups;    /* persistent rollout workgroups (one-wave rollouts
                                   that draw: at most what fits); 0, or the number
                                   that mppi_batch_get_cfg then reports: automatic.

@@ -1059,8 +1059,8 @@ struct Captured {
 // sequences kept by a batch
 constexpr size_t kCaptured = 32;
 
-// a pipelined group with more tiles than the chip holds pipelines (two per CU):
-// one-wave rollouts in the pipeline's arithmetic, the same results
+// a pipelined group with many tiles: one-wave rollouts in the pipeline's
+// arithmetic, the same results
 constexpr int V_WIDE = 1;
 // the average's blocks take one horizon step each
 constexpr int V_SINGLE = 2;
@@ -1351,7 +1351,16 @@ mppi_status mppi_batch_get_cfg(const mppi_batch *b, mppi_batch_cfg *cfg)
 // The variant of a group's step with this many rollout tiles and horizon steps.
 static int variant_of(const mppi_batch *b, const BatchGroup &g, int64_t tiles, int64_t steps)
 {
-    const bool wide = g.launch.rollout_waves == 4 && !b->fp64 && !b->own_groups && tiles > 2 * b->n_cu;
+    // Wide beyond three tiles per CU, six with rings of 4 steps, of which a CU
+    // holds two.  Pipelines -> wide, us a step, N = 50 (100): rings of 8,
+    // K = 4096, 2.3 tiles per CU gate 91 -> 106 (134 -> 141), tracking 93 -> 114;
+    // 3.0: gate 111 -> 108 (172 -> 167), contouring 139 -> 120, tracking
+    // 114 -> 118; 4.1: gate 132 -> 114, contouring 172 -> 144, tracking
+    // 137 -> 123.  Rings of 4, K = 20000, 3.7: gate 89 -> 119 (122 -> 178),
+    // tracking 98 -> 129; 6.1: gate 131 -> 145 (186 -> 200), contouring
+    // 164 -> 180 (244 -> 225); 8.6: gate 154 -> 148, contouring 192 -> 182.
+    const int limit = (g.launch.ring_steps == 4 ? 6 : 3) * b->n_cu;
+    const bool wide = g.launch.rollout_waves == 4 && !b->fp64 && !b->own_groups && tiles > limit;
     const bool single = final_steps(g.objective == OBJ_CONTOUR, g.acc64 ? 8 : 4) == 1 || steps <= b->n_cu;
     return (wide ? V_WIDE : 0) | (single ? V_SINGLE : 0);
 }

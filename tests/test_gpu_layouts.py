@@ -99,28 +99,41 @@ def test_rate_input_pipeline(objective, precision, monkeypatch):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("use_graph", [True, False])
-def test_wide_steps(use_graph, monkeypatch):
-    """The contexts of the wide-step test: all of them, then too few tiles."""
+@pytest.mark.parametrize("K,per_cu", [(4000, 3), (20000, 6)], ids=["rings of 8", "rings of 4"])
+@pytest.mark.parametrize("objective", ["gate", "contour", "track"])
+def test_wide_steps(objective, K, per_cu, use_graph, monkeypatch):
+    """A step with more tiles than the wide limit, then one with fewer, against
+    the contexts alone."""
     import torch
     monkeypatch.setenv("MPPI_ROLLOUT_WAVES", "4")
-    sizes = [(128 * n_cu() + 70, 5), (8192, 9), (64, 1), (2500, 6)]
-    sw = [solver(K, N, objective) for objective in ("gate", "contour", "track") for K, N in sizes]
+    tiles = (K + 64) // 64
+    n = per_cu * n_cu() // tiles + 1
+    assert (n - 1) * tiles <= per_cu * n_cu() < n * tiles and (tiles > n_cu()) == (per_cu == 6)
+    Ns = [(5, 9, 1, 6)[i % 4] for i in range(n)]
+    sw = [solver(K, N, objective) for N in Ns]
+    alone = [solver(K, N, objective)[0] for N in Ns]
     B = M.Batch([s for s, _ in sw], rollout_waves=4, use_graph=use_graph)
     assert B.layout_ran() == 0
-    reqs = torch.zeros((len(sw), M.REQ_DOUBLES), dtype=torch.float64, device="cuda")
-    u0s = torch.zeros((len(sw), 4), dtype=torch.float64, device="cuda")
+    reqs = torch.zeros((n, M.REQ_DOUBLES), dtype=torch.float64, device="cuda")
+    u0s = torch.zeros((n, 4), dtype=torch.float64, device="cuda")
     for i, (_, w) in enumerate(sw):
         reqs[i, :13] = torch.from_numpy(w["x0"][:13])
-    torch.cuda.synchronize()
-    say("wide", "graph", use_graph)
-    for _ in range(2):
-        B.solve_device(reqs.data_ptr(), u0s.data_ptr())
-        assert B.layout_ran() & M.RAN_WIDE
-        B.solve_device(reqs.data_ptr(), u0s.data_ptr(), active=[1, 2, 3])
-        assert not B.layout_ran() & M.RAN_WIDE
-    torch.cuda.synchronize()
+    for step, wide in enumerate([True, False, True]):
+        reqs[:, 13] = 0.02 * step
+        torch.cuda.synchronize()
+        say("wide", objective, "K", K, "graph", use_graph, "step", step)
+        ids = list(range(n if wide else n - 1))
+        B.solve_device(reqs.data_ptr(), u0s.data_ptr(), active=ids)
+        assert bool(B.layout_ran() & M.RAN_WIDE) == wide
+        torch.cuda.synchronize()
+        got = u0s.cpu().numpy()
+        for i in ids:
+            u0, _, _ = alone[i].solve(sw[i][1]["x0"], 0.02 * step)
+            np.testing.assert_array_equal(got[i], u0)
+            np.testing.assert_array_equal(sw[i][0].read_samples()[0], alone[i].read_samples()[0])
+            np.testing.assert_array_equal(np.array(sw[i][0].get_warm().U), np.array(alone[i].get_warm().U))
     B.close()
-    for s, _ in sw:
+    for s in [s for s, _ in sw] + alone:
         s.close()
 
 
@@ -152,7 +165,7 @@ def test_a_number_of_rollout_workgroups_holds_the_pipeline(monkeypatch):
     another one; the same results either way."""
     import torch
     monkeypatch.setenv("MPPI_ROLLOUT_WAVES", "4")
-    sizes = [(128 * n_cu() + 70, 5), (3000, 9)]
+    sizes = [(384 * n_cu() + 70, 5), (3000, 9)]
     reqs = torch.zeros((2, M.REQ_DOUBLES), dtype=torch.float64, device="cuda")
     out = []
     for how in ("automatic", "as reported", "others"):
