@@ -116,12 +116,14 @@ typedef struct {
      * clipped to rate_lim and then to the range that keeps its thrust within
      * [t_min, t_max] over the step; the contouring acceleration likewise to
      * dv_lim and to the range that keeps the progress speed within
-     * [0, v_max].  The rate model runs the one-wave rollout with a separate
-     * sampling kernel; a context on its own with at most one 64-sample tile
-     * per CU runs a pipelined rollout whose results are those bit for bit
-     * (its report keeps rollout_waves 1).  A batch holding such a context runs
-     * all its contexts with one-wave rollouts (a server launches each layout
-     * on its own). */
+     * [0, v_max].  The rate model has the one-wave layout: a context on its
+     * own follows a separate sampling kernel or, with at most one 64-sample
+     * tile per CU, runs a pipelined rollout (MPPI_RAN_RATE_PIPE; its report
+     * keeps rollout_waves 1); in a batch the rollout draws the samples itself
+     * (binary32; in binary64 it follows the sampling kernel).  The results are
+     * the same bit for bit.  A batch holding such a context runs all its
+     * contexts with one-wave rollouts (a server launches each layout on its
+     * own). */
     int32_t input_model;
     int32_t pad_;
     double rate_lim[2];   /* thrust-rate bounds, N/s (lower <= 0 <= upper)    */
@@ -360,10 +362,9 @@ mppi_status mppi_read_profile(mppi_ctx *ctx, double mean_ms[3], int32_t *n_solve
  * One-wave rollouts of binary32 contexts draw their samples themselves (no
  * sample kernel); pipelined binary32 contexts run one-wave rollouts of the
  * same results where a group has more than three tiles per CU (six with rings
- * of 4 steps).  Grids are
- * fixed and the work description lives in device memory, so the sequences for
- * those sizes are captured in HIP graphs at the first step (cfg.use_graph) and
- * replayed for any subset.
+ * of 4 steps).  Grids are fixed and the work description lives in device
+ * memory, so the sequences for those sizes are captured in HIP graphs at the
+ * first step (cfg.use_graph) and replayed for any subset.
  * Each context's result, report and warm-start state are the same as those
  * of mppi_solve_device on that context alone with the same rollout layout. */
 typedef struct mppi_batch mppi_batch;
@@ -398,9 +399,9 @@ typedef struct {
                                   with one- and two-wave rollouts             */
 } mppi_batch_cfg;
 
-/* Register ctxs[0..n-1] (distinct, same precision and n_iter, each used by
- * no other batch or call while the batch runs: MPPI_E_INVAL otherwise).  stream: hipStream_t of the batch's
- * launches (NULL: one owned by the batch).  cfg NULL: all automatic, graph on.
+/* Register ctxs[0..n-1] (distinct, same precision and n_iter, each used by no
+ * other batch or call while the batch runs: MPPI_E_INVAL otherwise).  stream:
+ * hipStream_t of the batch's launches (NULL: one owned by the batch).  cfg NULL: all automatic, graph on.
  * The contexts must outlive the batch. */
 mppi_status mppi_batch_create(mppi_ctx *const *ctxs, int32_t n, void *stream, const mppi_batch_cfg *cfg,
                               mppi_batch **out);

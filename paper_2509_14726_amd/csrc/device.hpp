@@ -70,7 +70,8 @@ struct KArgs {
     int32_t rollout_waves;      // 1: one wave per 64 samples; 2: attitude and translation on two waves; 3;
                                 // 4: the pipeline
     int32_t regen;              // 1: no sample tensor; the weighted average draws the samples again
-                                // (three- and four-wave layouts, whose rollout draws them)
+                                // (three- and four-wave layouts and the drawing one-wave layout,
+                                // whose rollouts draw them)
     int32_t rollout_draw;       // 1: the one-wave rollout draws its samples (no sample kernel)
     int32_t inner;              // 1: an inner iteration of a control step (no shift, the first
                                 // iteration's last applied input)
@@ -166,9 +167,9 @@ struct BatchDesc {
     int32_t n_sample_units;     // sum over items of ceil((K+1)/256)
     int32_t n_tiles;            // sum over items of ceil((K+1)/64)
     int32_t n_steps;            // units of the weighted-average kernel: sum over items of ceil(N / steps of a block)
-    uint32_t queue;             // rollout tile counter, reset by the sample kernel
-    uint32_t sample_queue;      // sample unit counter (both also reset by the
-                                // average kernel, for the step's next iteration)
+    uint32_t queue;             // rollout tile counter
+    uint32_t sample_queue;      // sample unit counter (both uploaded as 0 with a step and
+                                // reset by the average kernel, for the next iteration)
     uint32_t pad[2];
 };
 

@@ -19,6 +19,7 @@
 //                    softmax weights (Eq. (4)), the weighted average (Eq. (5)),
 //                    the first input, the report and the warm-start hand-over
 //   kb_*             the same bodies as persistent kernels over a batch
+//                    (kb_rollout_draw: the one-wave rollouts that draw)
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -3392,9 +3393,11 @@ __device__ __forceinline__ double wave_sum(double v)
 // above J_min) is neither read nor drawn: it adds nothing to any sum, so the
 // result is the same bit for bit.  With sharp weights (lambda = 1 at the
 // benchmark's noise) almost no sample is read: K = 262144, N = 200, binary64
-// sums: 157 -> 48 us.  Used wherever a thread
-// has several rounds of samples; with one round the samples are loaded at
-// once with the costs, which saves a round trip to memory.
+// sums: 157 -> 48 us.  Used wherever a thread has several rounds of samples
+// (where a part of them weighs something it costs a little: rate input,
+// K = 33000, N = 20 37.7 -> 39 us a solve; reading all costs up to 18 us more
+// there with sharp weights); with one round the samples are loaded at once
+// with the costs, which saves a round trip to memory.
 // A round is final_loads samples a thread (binary64: four spill, K = 8192,
 // N = 100: 59.3 us a solve against 54.2).
 template <typename Real> constexpr int final_loads = sizeof(Real) == 8 ? 2 : 4;

@@ -486,8 +486,9 @@ mppi_status mppi_create(const mppi_params *params, const mppi_quad *quad, const 
     a.ref_dt = problem->ref_dt;
     plan_layout(c);
     if (p.input_model == MPPI_INPUT_RATE) {
-        // a rate sample follows its thrust chain along the horizon, which the
-        // sampling kernel walks per sample: the one-wave rollout reads it
+        // a rate sample follows its thrust chain along the horizon, which is
+        // the rollout's own recurrence: one wave per tile, behind the sample
+        // kernel's draws (a batch's binary32 rollouts draw themselves)
         a.rollout_waves = 1;
         a.rollout_draw = 0;
         a.rollout_pair = 0;
@@ -1129,8 +1130,8 @@ static hipError_t resolve_cfg(mppi_batch *b)
     int waves = c.rollout_waves;
     const int cu = b->n_cu, tiles = b->total_tiles;
     if (waves < 1 || waves > 4) waves = tiles <= cu ? 4 : (tiles <= 2 * cu ? (b->fp64 ? 2 : 4) : 1);
-    // a rate sample follows its thrust chain, which the sample kernel walks
-    // per sample: the one-wave rollout reads it
+    // a rate sample follows its thrust chain, the rollout's own recurrence:
+    // only the one-wave rollouts walk it for a batch
     if (b->has_rate) waves = 1;
     // the regenerating average where the batch's rollout draws the samples,
     // unless a context's control-cost term reads the sample tensor
