@@ -46,10 +46,10 @@ PEAK_HBM_GBPS = 8000.0
 # or drawing the samples again) and the device sources they were taken on
 # (sha256 of kernels.hip, device.hpp, rollout.hpp, noise.hpp in that order);
 # otherwise the traffic is reported as null.
-TRAFFIC_SOURCES = "5ff7005c999fb96acdda0333b91d5fea564581377eeda34788f6119a1c94eef0"
+TRAFFIC_SOURCES = "f7af8d09db695e965465eab377838d0f14154903ed286907223ddd3693c790c9"
 FETCH_SCALE, WRITE_SCALE = 262144.0 / 131085.3, 262144.0 / 262144.0
 TRAFFIC_KIB = {("k_rollout4", 0): (139.7, 12836.4), ("k_final", 0): (6576.2, 6.8),
-               ("k_rollout4", 1): (139.6, 38.0), ("k_final", 1): (213.0, 6.8)}
+               ("k_rollout4", 1): (139.6, 38.0), ("k_final", 1): (210.4, 6.8)}
 TRAFFIC_WORKLOADS = {(8192, 100, "fp32", 0), (8192, 100, "fp32", 1)}
 ROLLOUT_KERNELS = {1: "k_rollout", 2: "k_rollout_split", 3: "k_rollout3", 4: "k_rollout4"}
 
